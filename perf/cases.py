@@ -1,0 +1,276 @@
+"""Performance cases of the FOCUS decode step: what a serving program has the library do, over the range it does it in.
+
+A case is one pass through the public entry points of paper_2601_23278_amd:
+
+  step      a batch of requests whose prefix K/V is in the paged pool is admitted into the slots (focus_prefill_kv without prompt
+            tokens) and takes its first denoising step (focus_step).  Admission belongs to the pass: it puts the blocks back to all
+            masked, so that every pass does the same work, and a server pays for it with every new request.
+  prefill   a batch of prompts is admitted and the K/V of every layer computed (focus_prefill_kv with prompt tokens).
+  generate  prefill, then several denoising steps in one call (focus_run_steps with block finalisation).
+
+The shapes are those of the configurations in focus_inputs with fewer layers: depth repeats the same launches, and every layer
+adds bf16 rounding differences of its own between two correct implementations.
+
+Decisions.  With random weights scores lie close together: two implementations that round differently keep another token in about
+6 % of the sequences and route a tenth of the rows to another expert, and everything after that is another computation.  So that
+results can be compared, the bf16 steps take their decisions from integers: the pick of the K retained positions by the library's
+random selection (the scores are computed all the same and are outputs), or retained sets handed in, and forced expert routes.  The
+launches and their sizes are those of the normal path.  The fp32 model makes all decisions itself.
+"""
+import math
+import random
+
+import torch
+
+from paper_2601_23278_amd import binding as fb
+
+DENSE_8B = dict(hidden=4096, n_q_heads=32, n_kv_heads=8, head_dim=128, ffn=12288, vocab=151936, dtype=fb.FOCUS_BF16, rope_base=1.0e6,
+                mask_token_id=151935, page_size=64)
+MOE = dict(hidden=2048, n_q_heads=16, n_kv_heads=4, head_dim=128, ffn=5120, vocab=157184, dtype=fb.FOCUS_BF16, rope_base=6.0e5,
+           mask_token_id=157183, page_size=64, n_experts=256, experts_per_token=8, expert_ffn=512, shared_ffn=512, first_moe_layer=1,
+           route_scale=2.5)
+TINY = dict(hidden=256, n_q_heads=4, n_kv_heads=4, head_dim=64, ffn=1024, vocab=1024, dtype=fb.FOCUS_F32, rope_base=1.0e4,
+            mask_token_id=0, page_size=16)
+MODELS = {"dense": DENSE_8B, "moe": MOE, "tiny": TINY}
+STEPS = 4          # denoising steps of a "generate" pass
+EVICT = 1          # eviction layer
+
+# budget: "ratio" keeps ceil(keep * block) positions, "topk" keep of them; "per_request" takes a budget per request from the caller, who
+# therefore knows how many rows to expect; "sets" takes retained sets from the caller and, like the dynamic budget of Eq. 4-5 and the
+# structural constraints, leaves the row count to the device: the caller passes on an estimate.
+BUDGETS = {"topk": 0, "ratio": 1, "per_request": 3, "sets": 1}
+
+
+def _case(kind, model, layers, batch, block, lo, hi, budget, keep, **more):
+    return dict(dict(kind=kind, model=model, layers=layers, batch=batch, block=block, prefix_lo=lo, prefix_hi=hi, log_lengths=False,
+                     shuffled_pages=False, budget=budget, keep=keep, block_cache=False, logits=False), **more)
+
+
+def listed():
+    return [
+        # The tiny fp32 model: prompts, then four steps.  Latency and launch count.
+        _case("generate", "tiny", 2, 4, 16, 32, 64, "ratio", 0.25, name="tiny_fp32_generate"),
+        # One interactive request with an odd context length: every projection streams its weights for a few rows.
+        _case("step", "dense", 4, 1, 32, 1117, 1117, "ratio", 0.25, name="one_request"),
+        # 32 requests with blocks of 4 tokens, two kept: 128 rows, then 64.
+        _case("step", "dense", 4, 32, 4, 512, 512, "topk", 2, name="small_blocks"),
+        # A lightly loaded server: ragged short contexts, an odd block, half of each block kept; the caller samples from the logits itself.
+        _case("step", "dense", 4, 23, 24, 65, 1500, "ratio", 0.5, logits=True, shuffled_pages=True, name="ragged_logits"),
+        # Ragged retained sets, as the paper's own budget rule with its structural constraints leaves them, and the intra-block K/V cache.
+        _case("step", "dense", 6, 96, 32, 200, 2048, "sets", 0.45, block_cache=True, name="ragged_sets"),
+        # Batch 128, contexts up to 2048, a quarter kept.
+        _case("step", "dense", 8, 128, 32, 256, 2048, "ratio", 0.25, name="batch128"),
+        # The headline batch: 256 requests, contexts up to 4096, a quarter kept.
+        _case("step", "dense", 10, 256, 32, 512, 4096, "ratio", 0.25, name="batch256"),
+        # The same batch decoded densely: nothing is evicted.
+        _case("step", "dense", 6, 256, 32, 512, 4096, "ratio", 1.0, name="batch256_dense"),
+        # Long, very uneven contexts over scattered pages, blocks of 64, a budget per request.
+        _case("step", "dense", 6, 64, 64, 1024, 32768, "per_request", 0.5, log_lengths=True, shuffled_pages=True, name="long_ragged"),
+        # A couple of requests with very long contexts.
+        _case("step", "dense", 4, 2, 32, 30011, 32768, "ratio", 0.25, name="long_context"),
+        # Mixture of experts at the headline batch.
+        _case("step", "moe", 6, 256, 32, 512, 4096, "ratio", 0.25, name="moe_batch256"),
+        # A dozen prompts of a few hundred tokens, computed block by block.
+        _case("prefill", "dense", 4, 12, 32, 100, 700, "ratio", 0.25, name="prefill"),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return min(hi, int(math.exp(rng.uniform(math.log(lo), math.log(hi + 1)))))
+
+
+def draw(rng):
+    most = max(_cost(c) for c in listed())
+    while True:
+        kind = rng.choice(["step"] * 8 + ["prefill", "generate"])
+        if kind == "generate":
+            lo = rng.randint(8, 48)
+            return _case(kind, "tiny", 2, rng.randint(1, 8), rng.choice([8, 11, 16]), lo, lo + rng.randint(0, 32), "ratio", rng.choice([0.25, 0.5]))
+        if kind == "prefill":
+            lo = _log_int(rng, 32, 400)
+            c = _case(kind, "dense", rng.randint(2, 4), _log_int(rng, 1, 24), rng.choice([16, 32, 40, 64]), lo, lo + rng.randint(0, 600), "ratio", 0.25)
+        else:
+            model = rng.choice(["dense"] * 4 + ["moe"])
+            block = rng.choice([4, 8, 16, 24, 29, 32, 32, 32, 48, 64])
+            lo = _log_int(rng, 64, 8192)
+            hi = min(32768, lo + _log_int(rng, 1, 8 * lo))
+            budget = rng.choice(["ratio", "ratio", "ratio", "topk", "per_request", "sets"])
+            keep = (rng.randint(1, max(1, block // 2)) if budget == "topk" else rng.uniform(0.3, 0.7) if budget in ("per_request", "sets")
+                    else rng.choice([0.125, 0.25, 0.25, 0.5, 1.0]))
+            c = _case(kind, model, rng.randint(3, 8), _log_int(rng, 1, 256), block, lo, hi, budget, keep, log_lengths=rng.random() < 0.5,
+                      shuffled_pages=rng.random() < 0.5, block_cache=rng.random() < 0.2, logits=rng.random() < 0.15)
+        if _cost(c) <= most and sum(_geometry(c)[1]) * c["layers"] < 120_000:
+            return c
+
+
+def _cost(case):
+    w = work(case)
+    return max(w["bytes"] / 4.5e12, w["flops"] / 1.2e15)
+
+
+def _geometry(case):
+    """Prefix lengths, pages per request and rows retained per request: properties of the case and not of the seed, so that every seed is
+    the same amount of work."""
+    rng = random.Random("%s %d %d %d %d" % (case["model"], case["batch"], case["block"], case["prefix_lo"], case["prefix_hi"]))
+    n, B, lo, hi = case["batch"], case["block"], case["prefix_lo"], case["prefix_hi"]
+    lens = [_log_int(rng, lo, hi) if case["log_lengths"] else rng.randint(lo, hi) for _ in range(n)]
+    page = MODELS[case["model"]]["page_size"]
+    pages = [-(-(x + B) // page) for x in lens]
+    if case["budget"] in ("per_request", "sets"):
+        top = min(B, max(1, round(2 * case["keep"] * B)))
+        kept = [rng.randint(0 if case["budget"] == "per_request" else max(0, round(2 * case["keep"] * B) - B), top) for _ in range(n)]
+        kept[0] = max(1, kept[0])
+    else:
+        kept = [min(B, case["keep"] if case["budget"] == "topk" else math.ceil(case["keep"] * B))] * n
+    return lens, pages, kept
+
+
+def _layer_weights(m, layer):
+    """Elements of one layer's weights: (those every row uses, the routed experts)."""
+    h, qd, kd = m["hidden"], m["n_q_heads"] * m["head_dim"], m["n_kv_heads"] * m["head_dim"]
+    attn = (qd + 2 * kd) * h + h * qd
+    if m.get("n_experts") and layer >= m["first_moe_layer"]:
+        return attn + m["n_experts"] * h + 3 * m["shared_ffn"] * h, m["n_experts"] * 3 * m["expert_ffn"] * h
+    return attn + 3 * m["ffn"] * h, 0
+
+
+def work(case):
+    """Every weight and every cached key and value once per layer and forward, new keys and values written once, and the outputs; two flops
+    per multiply-add of the projections and of the attention of every row over its whole context."""
+    m, L, B, n = MODELS[case["model"]], case["layers"], case["block"], case["batch"]
+    es = 4 if m["dtype"] == fb.FOCUS_F32 else 2
+    kv_token = 2 * m["n_kv_heads"] * m["head_dim"] * es
+    active = m.get("experts_per_token", 0) * 3 * m.get("expert_ffn", 0) * m["hidden"]
+    lens, _, kept = _geometry(case)
+
+    def layer(l, rows, keys_seen, tokens_read):
+        dense, experts = _layer_weights(m, l)
+        return (2.0 * rows * (dense + (active if experts else 0)) + 4.0 * m["n_q_heads"] * m["head_dim"] * keys_seen,
+                es * (dense + min(experts, rows * active if experts else 0)) + kv_token * (tokens_read + rows))
+
+    flops = nbytes = 0.0
+    if case["kind"] != "step":                    # every prompt token through every layer, block by block
+        for c in range(0, max(lens), B):
+            live = [min(B, x - c) for x in lens if x > c]
+            for l in range(L):
+                f, b = layer(l, sum(live), sum(r * (c + r) for r in live), c * len(live))
+                flops, nbytes = flops + f, nbytes + b
+    for _ in range({"prefill": 0, "step": 1, "generate": STEPS}[case["kind"]]):
+        full, packed = n * B, sum(kept)
+        for l in range(L):
+            f, b = layer(l, full if l < EVICT else packed, sum((B if l < EVICT else k) * (x + B) for k, x in zip(kept, lens)), sum(lens))
+            flops, nbytes = flops + f, nbytes + b
+        qkv = (m["n_q_heads"] + 2 * m["n_kv_heads"]) * m["head_dim"] * m["hidden"]
+        flops += 2.0 * (full - packed) * qkv + 2.0 * packed * m["vocab"] * m["hidden"]
+        nbytes += es * m["vocab"] * m["hidden"] + 16.0 * full + 4.0 * packed * (m["hidden"] + (m["vocab"] if case["logits"] else 0))
+    return {"bytes": nbytes, "flops": flops}
+
+
+def tolerance(case):
+    """bf16 models: results of the same kernels on the same inputs with other reduction orders (a batch of 256 against the same
+    sequences in batches of 32, which splits K of the projections and the context of the attention) differ by 0.9 % (4 layers) to 1.5 %
+    (10 layers) in the residual stream, 1.2 to 1.9 % in the confidences, 0.9 % in the importance delta; single values by up to 0.08 of the
+    root mean square.  Committed tokens then differ in 0.1 to 0.3 % of the block positions.  fp32: 32-bit sums."""
+    if case["model"] == "tiny":
+        return {"rel": 2e-5, "max": 1e-3, "differ": 0.0}
+    return {"rel": 0.03, "max": 0.3, "differ": 0.01}
+
+
+def _config(case, lens, n_pages, seed):
+    c = fb.focus_config()
+    for k, v in MODELS[case["model"]].items():
+        setattr(c, k, v)
+    c.n_layers, c.block_size, c.max_batch = case["layers"], case["block"], case["batch"]
+    c.max_prefix_len, c.n_pages = max(lens), n_pages
+    c.rms_eps, c.evict_layer, c.importance_mode, c.maxpool_k, c.alpha = 1e-6, EVICT, 0, 3, 1.5
+    c.budget_mode = BUDGETS[case["budget"]]
+    c.topk, c.keep_ratio = (case["keep"], 0.25) if case["budget"] == "topk" else (0, case["keep"])
+    c.conf_threshold, c.intra_block_cache = 0.9, int(case["block_cache"])
+    if case["model"] != "tiny":
+        c.selection, c.selection_seed = 1, seed & 0xFFFFFFFF
+    return c
+
+
+def prepare(case, seed):
+    """The model, the paged pool with the prefix K/V (weights N(0, 0.02), keys and values N(0, 1)), the context and the output buffers."""
+    dev, m, rng = "cuda:0", MODELS[case["model"]], random.Random(seed)
+    gen = torch.Generator(dev).manual_seed(seed)
+    dt = torch.float32 if m["dtype"] == fb.FOCUS_F32 else torch.bfloat16
+    lens, pages, kept = _geometry(case)
+    n, B, L, h = case["batch"], case["block"], case["layers"], m["hidden"]
+    qd, kd = m["n_q_heads"] * m["head_dim"], m["n_kv_heads"] * m["head_dim"]
+
+    def normal(std, *shape):
+        return torch.empty(shape, dtype=dt, device=dev).normal_(0.0, std, generator=gen)
+
+    norm = torch.ones(h, dtype=dt, device=dev)
+    embed, lm_head = normal(0.02, m["vocab"], h), normal(0.02, m["vocab"], h)
+    layers = []
+    for l in range(L):
+        w = dict(attn_norm=norm, mlp_norm=norm, w_qkv=normal(0.02, qd + 2 * kd, h), w_o=normal(0.02, h, qd))
+        if m.get("n_experts") and l >= m["first_moe_layer"]:
+            E, Fe, Fs = m["n_experts"], m["expert_ffn"], m["shared_ffn"]
+            w.update(w_router=normal(0.02, E, h), w_expert_gate_up=normal(0.02, E, 2 * Fe, h), w_expert_down=normal(0.02, E, h, Fe),
+                     w_shared_gate_up=normal(0.02, 2 * Fs, h), w_shared_down=normal(0.02, h, Fs))
+        else:
+            w.update(w_gate_up=normal(0.02, 2 * m["ffn"], h), w_down=normal(0.02, h, m["ffn"]))
+        layers.append(w)
+    pool = torch.zeros((L, sum(pages), 2, m["n_kv_heads"], m["page_size"], m["head_dim"]), dtype=dt, device=dev)
+    if case["kind"] == "step":
+        pool.normal_(0.0, 1.0, generator=gen)
+    phys = list(range(sum(pages)))
+    if case["shuffled_pages"]:
+        rng.shuffle(phys)
+    tables, at = [], 0
+    for c in pages:
+        tables.append(phys[at:at + c])
+        at += c
+    s = dict(kind=case["kind"], n=n, lens=lens, tables=tables, pool=pool, prompts=None, budgets=None, sets=None)
+    s["focus"] = f = fb.Focus(_config(case, lens, sum(pages), seed), embed, lm_head, norm, layers, pool)
+    if case["kind"] != "step":
+        s["prompts"] = [[rng.randrange(1, m["vocab"] - 1) for _ in range(x)] for x in lens]
+    if case["kind"] == "prefill":
+        return s
+    if case["budget"] == "per_request":
+        s["budgets"] = torch.tensor(kept, dtype=torch.int32, device=dev)
+    if case["budget"] == "sets":
+        sets = [sum(1 << p for p in rng.sample(range(B), k)) for k in kept]
+        s["sets"] = torch.tensor([x - (1 << 64) if x >> 63 else x for x in sets], dtype=torch.int64, device=dev)
+    device_rows = case["budget"] in ("per_request", "sets") or case["block_cache"]     # the library plans for whole blocks, unless told
+    if device_rows:
+        f.focus_set_row_hint(sum(kept), max(kept))
+    if m.get("n_experts"):
+        routes = torch.rand((L, n * B, m["n_experts"]), device=dev, generator=gen).topk(m["experts_per_token"], dim=2).indices
+        f.focus_set_route_override(routes.to(torch.int32).contiguous())
+
+    def out(dtype, *shape):
+        return torch.zeros(shape, dtype=dtype, device=dev)
+
+    rows, valid = n * B if device_rows else sum(kept), sum(kept)       # buffer rows, rows of them that a step writes
+    o = s["out"] = dict(n_decoded=out(torch.int32, n), importance_prev=out(torch.float32, n, B), importance=out(torch.float32, n, B),
+                        delta_I=out(torch.float32, n, B), K=out(torch.int32, n), keep_bits=out(torch.int64, n), cu_seqlens=out(torch.int32, n + 1),
+                        conf=out(torch.float32, rows), hidden_packed=out(torch.float32, rows, h))
+    if case["logits"] or case["kind"] == "generate":
+        o["logits"] = out(torch.float32, rows, m["vocab"])
+    tokens = out(torch.int32, n, B)
+    s["step_out"] = fb.make_step_out(tokens=tokens, **o)
+    for k in ("conf", "hidden_packed", "logits"):
+        if k in o:
+            o[k] = o[k][:valid]
+    if case["model"] == "tiny" or (n >= 64 and B >= 24):     # one differing token of a smaller batch is more than `differ` allows
+        o["tokens"] = tokens
+    if pool.numel() <= 1 << 30:                   # with the block's new keys and values (the larger pools are too much to compare)
+        o["kv"] = pool
+    return s
+
+
+def run(s):
+    f = s["focus"]
+    f.focus_prefill_kv(s["lens"], s["tables"], s["prompts"])
+    if s["kind"] == "prefill":
+        return {"kv": s["pool"]}
+    if s["kind"] == "generate":
+        f.focus_run_steps(s["n"], STEPS, finalize=True, out=s["step_out"])
+        return s["out"]
+    f.focus_step(s["n"], k_override=s["budgets"], keep_override=s["sets"], out=s["step_out"])
+    return s["out"]
