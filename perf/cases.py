@@ -149,18 +149,18 @@ def work(case):
                 es * (dense + min(experts, rows * active if experts else 0)) + kv_token * (tokens_read + rows))
 
     flops = nbytes = 0.0
-    if case["kind"] != "step":                    # every prompt token through every layer, block by block
-        for c in range(0, max(lens), B):
-            live = [min(B, x - c) for x in lens if x > c]
-            for l in range(L):
-                f, b = layer(l, sum(live), sum(r * (c + r) for r in live), c * len(live))
-                flops, nbytes = flops + f, nbytes + b
+    qkv = (m["n_q_heads"] + 2 * m["n_kv_heads"]) * m["head_dim"] * m["hidden"]
+    if case["kind"] != "step":      # every prompt token through every layer, of the last one only its keys and values; the cache is written
+        tokens, seen = sum(lens), sum(min(B, x - c) * min(c + B, x) for x in lens for c in range(0, x, B))
+        for l in range(L - 1):
+            f, b = layer(l, tokens, seen, 0)
+            flops, nbytes = flops + f, nbytes + b
+        flops, nbytes = flops + 2.0 * tokens * qkv, nbytes + es * qkv + kv_token * tokens
     for _ in range({"prefill": 0, "step": 1, "generate": STEPS}[case["kind"]]):
         full, packed = n * B, sum(kept)
         for l in range(L):
             f, b = layer(l, full if l < EVICT else packed, sum((B if l < EVICT else k) * (x + B) for k, x in zip(kept, lens)), sum(lens))
             flops, nbytes = flops + f, nbytes + b
-        qkv = (m["n_q_heads"] + 2 * m["n_kv_heads"]) * m["head_dim"] * m["hidden"]
         flops += 2.0 * (full - packed) * qkv + 2.0 * packed * m["vocab"] * m["hidden"]
         nbytes += es * m["vocab"] * m["hidden"] + 16.0 * full + 4.0 * packed * (m["hidden"] + (m["vocab"] if case["logits"] else 0))
     return {"bytes": nbytes, "flops": flops}
