@@ -99,7 +99,8 @@ def draw(rng):
                     else rng.choice([0.125, 0.25, 0.25, 0.5, 1.0]))
             c = _case(kind, model, rng.randint(3, 8), _log_int(rng, 1, 256), block, lo, hi, budget, keep, log_lengths=rng.random() < 0.5,
                       shuffled_pages=rng.random() < 0.5, block_cache=rng.random() < 0.2, logits=rng.random() < 0.15)
-        if _cost(c) <= most and sum(_geometry(c)[1]) * c["layers"] < 120_000:
+        lens, pages, _ = _geometry(c)
+        if _cost(c) <= most and sum(pages) * c["layers"] < 120_000 and (kind == "step" or sum(lens) * c["layers"] <= 20_000):
             return c
 
 
