@@ -95,19 +95,22 @@ struct Scratch {
 };
 void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, Rows rows, int epilogue,
           void *out, int ldo, Warm warm = Warm(), Scratch scratch = Scratch());
-// Warm-up helper for kernels with one- or two-dimensional grids of short workgroups: the workgroups of the last round
-// (the last min(grid, 256) in launch order) each read one dword of every 128-byte line of their share.  Returns a value
-// the caller must keep alive (e.g. store it under a condition that never holds).
-__device__ __forceinline__ unsigned warm_touch(const void *ptr, size_t bytes, int n_threads) {
-  if (!ptr || !bytes) return 0;
-  const long n_groups = (long)gridDim.x * gridDim.y, id = blockIdx.x + (long)blockIdx.y * gridDim.x;
-  const long shares = n_groups < 256 ? n_groups : 256, share = id - (n_groups - shares);
-  if (share < 0) return 0;
+// Warm-up helpers: one dword of every 128-byte line of workgroup `share`'s part of `shares`.  They return a value the caller must keep
+// alive (e.g. store it under a condition that never holds).
+__device__ __forceinline__ unsigned warm_share(const void *ptr, size_t bytes, long share, long shares, int n_threads) {
   const size_t lines = (bytes + 127) / 128, per = (lines + shares - 1) / shares;
   const size_t l0 = (size_t)share * per, l1 = l0 + per < lines ? l0 + per : lines;
   unsigned acc = 0;
   for (size_t l = l0 + threadIdx.x; l < l1; l += n_threads) acc ^= __builtin_nontemporal_load((const unsigned *)((const char *)ptr + l * 128));
   return acc;
+}
+// For kernels with one-dimensional grids of short workgroups: the workgroups of the last round (the last min(grid, 256) in launch
+// order) share the work.
+__device__ __forceinline__ unsigned warm_touch(const void *ptr, size_t bytes, int n_threads) {
+  if (!ptr || !bytes) return 0;
+  const long n_groups = (long)gridDim.x, id = blockIdx.x;
+  const long shares = n_groups < 256 ? n_groups : 256, share = id - (n_groups - shares);
+  return share < 0 ? 0 : warm_share(ptr, bytes, share, shares, n_threads);
 }
 // Rotates q and k rows of the fused qkv buffer in place and stores k, v of every row into its cache slot.
 // n_seq, cu: the row range of every batch entry (rows cu[b] .. cu[b + 1]), or 0 / null when not known.
@@ -137,6 +140,10 @@ struct AttnArgs {
   float *imp_partial = nullptr;
   int imp_pool_k = 3;
 };
+// Wavefronts of a workgroup for `pairs` (row, group head) pairs per kv head, and the workgroups of that shape a compute unit holds:
+// five of one wavefront (LDS), else eight wavefronts (registers).
+inline int attention_wavefronts(int pairs) { return pairs <= 32 ? 1 : pairs <= 64 ? 2 : pairs <= 128 ? 4 : 8; }
+inline long attention_groups_per_cu(int pairs) { const int nw = attention_wavefronts(pairs); return nw == 1 ? 5 : 8 / nw; }
 // Returns true when imp_partial was asked for and has been written by the attention launch itself.
 bool attention(hipStream_t s, const AttnArgs &a);
 // Eq. 2 per (sequence, query head): partial[b, h, j] = sum over the sequence's query rows (rows cu[b] .. cu[b + 1] of the

@@ -3,6 +3,8 @@
 // A query row (sequence b, block position p) attends to the sequence's whole prefix [0, L) and to the
 // in-block positions whose bit is set in the sequence's visibility set (all B in the layers up to the
 // eviction layer; the processed positions above it).  There is no mask inside the block (Sec. 1-2).
+#include <algorithm>
+
 #include "focus_internal.h"
 
 namespace fk {
@@ -99,7 +101,14 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_imp[];
   unsigned char *const lds = IMP ? lds_imp : lds_fixed;
   const int Hkv = a.kv.n_kv_heads, Hq = a.n_q_heads, g = Hq / Hkv;
-  const int bo = blockIdx.x / Hkv, hk = blockIdx.x % Hkv, split = blockIdx.y;
+  const int groups = a.n_seq * Hkv, split = blockIdx.x / groups, group = blockIdx.x % groups;
+  if (split >= a.launch_splits) {                        // a workgroup beyond the attention's own: it only warms the next weights
+    const int n_warm = (int)gridDim.x - groups * a.launch_splits;
+    const unsigned acc = warm_share(a.warm.ptr, a.warm.bytes, (int)blockIdx.x - groups * a.launch_splits, n_warm, NW * 64);
+    if (acc == 0x9e3779b9u && a.chunk < 0) ((unsigned *)a.out)[0] = acc;   // never true: keeps the loads
+    return;
+  }
+  const int bo = group / Hkv, hk = group % Hkv;
   const int b = a.order ? a.order[bo] : bo;
   const int r0 = a.cu[b], nr = a.cu[b + 1] - r0;
   if (nr <= 0) {
@@ -112,7 +121,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
   // Splits that have tokens: the sequence's own length decides (it is read here, on the device), bounded by the number of
   // split workgroups this launch has; the last one takes everything that is left.  So a launch whose geometry was fixed when
   // the prefixes were shorter (a captured graph replayed after blocks became prefix) still attends to every token.
-  const int nsplit = min((total + a.chunk - 1) / a.chunk, (int)gridDim.y);
+  const int nsplit = min((total + a.chunk - 1) / a.chunk, a.launch_splits);
   if (split >= nsplit) return;
   const int t0 = split * a.chunk;
   const int t1 = split == nsplit - 1 ? total : t0 + a.chunk;
@@ -399,31 +408,91 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
   }
   // the last workgroups to start (the shortest sequences), once through their own K/V, pull the next projection's
   // weights into the memory-side cache: any earlier and the K/V stream would push them out again
-  const unsigned warm_acc = warm_touch(a.warm.ptr, a.warm.bytes, NW * 64);
+  const int n_attn = groups * a.launch_splits;
+  const unsigned warm_acc = (int)gridDim.x > n_attn ? 0u : warm_touch(a.warm.ptr, a.warm.bytes, NW * 64);
   if (warm_acc == 0x9e3779b9u && a.chunk < 0) ((unsigned *)a.out)[0] = warm_acc;   // never true: keeps the loads
 }
 
-// Merge of the K/V splits of one (row, head): out = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), in split order.
-__global__ __launch_bounds__(128) void k_attn_combine(AttnArgs a) {
-  const int r = blockIdx.x, hq = blockIdx.y, d = threadIdx.x;
+// Merge of the K/V splits of one (row, head): out = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M).  Latency-bound: one thread per
+// output value that walks the splits one after the other waits for memory that often (20 us for the 54 splits of a 31 000-token
+// context).  32 lanes read a split's 128 values as 16-byte pieces; the weights of all splits are computed side by side first.
+//   k_attn_combine_few   up to 16 splits: 32 lanes per (row, head), eight heads per workgroup
+//   k_attn_combine       more: a workgroup per (row, head), its eight groups of 32 lanes add every eighth split and the eight sums
+//                        are added in group order
+// Either order is fixed, so the result does not depend on timing.  9 us for 64 rows and 31 splits, 6.5 us for 16 rows and 70.
+__device__ __forceinline__ int combine_splits(const AttnArgs &a, int r) {     // as in k_attn_mfma; 0: no such row
   const int M = a.rows.count ? min(*a.rows.count, a.rows.cap) : a.rows.cap;
-  if (r >= M) return;
-  const int b = a.ri.row_map[r] / a.ri.B;
-  const int slot = slot_of(a.ri.seq_slot, b, a.st);
-  const int total = a.st.prefix_len[slot] + a.ri.B;
-  const int nsplit = min((total + a.chunk - 1) / a.chunk, a.max_splits);   // as in k_attn_mfma
+  if (r >= M) return 0;
+  const int slot = slot_of(a.ri.seq_slot, a.ri.row_map[r] / a.ri.B, a.st);
+  return min((a.st.prefix_len[slot] + a.ri.B + a.chunk - 1) / a.chunk, a.max_splits);
+}
+constexpr int kCombineFew = 16;
+__global__ __launch_bounds__(256) void k_attn_combine_few(AttnArgs a) {
+  const int r = blockIdx.x, hq = blockIdx.y * 8 + (threadIdx.x >> 5), col = threadIdx.x & 31;
+  const int nsplit = combine_splits(a, r);
+  if (nsplit <= 1 || hq >= a.n_q_heads) return;
+  const size_t pi = ((size_t)r * a.n_q_heads + hq) * a.max_splits;
+  const float2 ml = col < nsplit ? *(const float2 *)(a.part_ml + (pi + col) * 2) : make_float2(-INFINITY, 0.f);
+  float mm = ml.x;
+  for (int o = 16; o > 0; o >>= 1) mm = fmaxf(mm, __shfl_xor(mm, o));
+  const float w = ml.x == -INFINITY ? 0.f : exp2f(ml.x - mm);
+  float den = ml.y * w;
+  for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o);
+  float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+  for (int s = 0; s < nsplit; ++s) {
+    const float4 v = *(const float4 *)(a.part_o + (pi + s) * 128 + col * 4);
+    const float ws = __shfl(w, s, 32);
+    num.x += v.x * ws; num.y += v.y * ws; num.z += v.z * ws; num.w += v.w * ws;
+  }
+  const float inv = den > 0.f ? 1.0f / den : 0.f;
+  bf16x4 o4;
+  o4[0] = (bf16_t)(num.x * inv); o4[1] = (bf16_t)(num.y * inv); o4[2] = (bf16_t)(num.z * inv); o4[3] = (bf16_t)(num.w * inv);
+  *(bf16x4 *)((bf16_t *)a.out + ((size_t)r * a.n_q_heads + hq) * 128 + col * 4) = o4;
+}
+__global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
+  __shared__ float wsh[256], osh[8][128], red[8];
+  const int r = blockIdx.x, hq = blockIdx.y, tid = threadIdx.x, grp = tid >> 5, col = tid & 31;
+  const int nsplit = combine_splits(a, r);
   if (nsplit <= 1) return;
   const size_t pi = ((size_t)r * a.n_q_heads + hq) * a.max_splits;
   float mm = -INFINITY;
-  for (int s = 0; s < nsplit; ++s) mm = fmaxf(mm, a.part_ml[(pi + s) * 2]);
-  float num = 0.f, den = 0.f;
-  for (int s = 0; s < nsplit; ++s) {
-    const float ms = a.part_ml[(pi + s) * 2];
-    const float w = ms == -INFINITY ? 0.f : exp2f(ms - mm);
-    num += a.part_o[(pi + s) * 128 + d] * w;
-    den += a.part_ml[(pi + s) * 2 + 1] * w;
+  for (int s = tid; s < nsplit; s += 256) mm = fmaxf(mm, a.part_ml[(pi + s) * 2]);
+  for (int o = 32; o > 0; o >>= 1) mm = fmaxf(mm, __shfl_xor(mm, o));
+  if ((tid & 63) == 0) red[tid >> 6] = mm;
+  __syncthreads();
+  mm = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+  float den = 0.f;
+  for (int s0 = 0; s0 < nsplit; s0 += 256) {
+    const int ns = min(256, nsplit - s0);
+    __syncthreads();
+    float w = 0.f;
+    if (tid < ns) {
+      const float2 ml = *(const float2 *)(a.part_ml + (pi + s0 + tid) * 2);
+      w = ml.x == -INFINITY ? 0.f : exp2f(ml.x - mm);
+      den += ml.y * w;
+    }
+    wsh[tid] = w;
+    __syncthreads();
+#pragma unroll 4
+    for (int s = grp; s < ns; s += 8) {
+      const float4 v = *(const float4 *)(a.part_o + (pi + s0 + s) * 128 + col * 4);
+      const float ws = wsh[s];
+      num.x += v.x * ws; num.y += v.y * ws; num.z += v.z * ws; num.w += v.w * ws;
+    }
   }
-  ((bf16_t *)a.out)[((size_t)r * a.n_q_heads + hq) * 128 + d] = (bf16_t)(den > 0.f ? num / den : 0.f);
+  for (int o = 32; o > 0; o >>= 1) den += __shfl_xor(den, o);
+  if ((tid & 63) == 0) red[4 + (tid >> 6)] = den;
+  *(float4 *)&osh[grp][col * 4] = num;
+  __syncthreads();
+  if (tid < 128) {
+    float v = osh[0][tid];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) v += osh[i][tid];
+    den = red[4] + red[5] + red[6] + red[7];
+    ((bf16_t *)a.out)[((size_t)r * a.n_q_heads + hq) * 128 + tid] = (bf16_t)(den > 0.f ? v / den : 0.f);
+  }
 }
 
 template <int NW, int BJ>
@@ -443,25 +512,32 @@ bool attention(hipStream_t s, const AttnArgs &a) {
   const int g = a.n_q_heads / a.kv.n_kv_heads;
   const bool mfma = a.dtype == FOCUS_BF16 && a.kv.head_dim == 128 && a.kv.page_size == 64 && a.q_stride % 8 == 0 && a.part_o != nullptr;
   if (mfma) {
-    dim3 grid(a.n_seq * a.kv.n_kv_heads, a.launch_splits);
-    const int R = a.max_rows_per_seq * g;
+    const int R = a.max_rows_per_seq * g, nw = attention_wavefronts(R);
+    // One workgroup per (sequence, kv head, split), and, when these are too few to pull the next weights in on the side (less than one
+    // per CU), workgroups of their own for that, sixteen 128-byte lines per thread: the launch leaves most CUs and most of the memory
+    // bandwidth idle anyway.  (One request, 1149 tokens: 16 workgroups warming 33 MB of weights on the side took 160 us.)
+    const int n_attn = a.n_seq * a.kv.n_kv_heads * a.launch_splits;
+    const size_t lines = a.warm.ptr ? (a.warm.bytes + 127) / 128 : 0;
+    const int n_warm = n_attn < 256 ? (int)std::min<size_t>(512, (lines + nw * 64 * 16 - 1) / (nw * 64 * 16)) : 0;
+    const dim3 grid(n_attn + n_warm);
     bool fused = false;
     // importance rides along when the group size divides the 32 pairs of a wavefront (rows of one head are then the lanes with
     // equal lane % g) and the score patches fit the LDS
     if (a.imp_partial && (g == 1 || g == 2 || g == 4 || g == 8) && a.ri.B <= 64) {
       const bool small = a.ri.B <= 32;
-      if (R <= 32) fused = small ? launch_attn_imp<1, 32>(s, grid, a, g) : launch_attn_imp<1, 64>(s, grid, a, g);
-      else if (R <= 64) fused = small ? launch_attn_imp<2, 32>(s, grid, a, g) : launch_attn_imp<2, 64>(s, grid, a, g);
-      else if (R <= 128) fused = small ? launch_attn_imp<4, 32>(s, grid, a, g) : launch_attn_imp<4, 64>(s, grid, a, g);
+      if (nw == 1) fused = small ? launch_attn_imp<1, 32>(s, grid, a, g) : launch_attn_imp<1, 64>(s, grid, a, g);
+      else if (nw == 2) fused = small ? launch_attn_imp<2, 32>(s, grid, a, g) : launch_attn_imp<2, 64>(s, grid, a, g);
+      else if (nw == 4) fused = small ? launch_attn_imp<4, 32>(s, grid, a, g) : launch_attn_imp<4, 64>(s, grid, a, g);
       else fused = small ? launch_attn_imp<8, 32>(s, grid, a, g) : launch_attn_imp<8, 64>(s, grid, a, g);
     }
     if (!fused) {
-      if (R <= 32) k_attn_mfma<1><<<grid, 64, 0, s>>>(a);
-      else if (R <= 64) k_attn_mfma<2><<<grid, 128, 0, s>>>(a);
-      else if (R <= 128) k_attn_mfma<4><<<grid, 256, 0, s>>>(a);
+      if (nw == 1) k_attn_mfma<1><<<grid, 64, 0, s>>>(a);
+      else if (nw == 2) k_attn_mfma<2><<<grid, 128, 0, s>>>(a);
+      else if (nw == 4) k_attn_mfma<4><<<grid, 256, 0, s>>>(a);
       else k_attn_mfma<8><<<grid, 512, 0, s>>>(a);
     }
-    if (a.launch_splits > 1) k_attn_combine<<<dim3(a.rows.cap, a.n_q_heads), 128, 0, s>>>(a);
+    if (a.launch_splits > kCombineFew) k_attn_combine<<<dim3(a.rows.cap, a.n_q_heads), 256, 0, s>>>(a);
+    else if (a.launch_splits > 1) k_attn_combine_few<<<dim3(a.rows.cap, (a.n_q_heads + 7) / 8), 256, 0, s>>>(a);
     return fused;
   }
   dim3 grid(a.rows.cap, a.n_q_heads);
