@@ -328,7 +328,7 @@ void swiglu_ffn(focus_ctx *c, hipStream_t s, const RowSet &rs, const void *norme
                 float *resid, fk::Warm warm_after) {
   const focus_config &g = c->cfg;
   void *gate_up = c->at<char>(c->plan.off_gate_up), *act = c->at<char>(c->plan.off_act);
-  if (fk::gemm_fuses_silu_mul(g.dtype, normed, w_gate_up, 2 * ffn, g.hidden)) {
+  if (fk::gemm_fuses_silu_mul(g.dtype, normed, w_gate_up, 2 * ffn, g.hidden, rs.rows.cap)) {
     Timed t(c, s, FOCUS_KC_GEMM);
     fk::gemm(s, g.dtype, normed, w_gate_up, 2 * ffn, g.hidden, rs.rows, fk::EPI_SILU_MUL, act, ffn,
              fk::Warm{w_down, (size_t)g.hidden * ffn * esize(g.dtype)}, c->scratch());

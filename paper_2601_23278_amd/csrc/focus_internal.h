@@ -77,7 +77,7 @@ enum Epilogue {
 bool gemm_conf_partials(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, Rows rows, float *part, size_t part_bytes,
                         int *n_slots);
 void confidence_from_partials(hipStream_t s, const float *part, int n_slots, Rows rows, float *conf, int32_t *argmax);
-bool gemm_fuses_silu_mul(int dtype, const void *A, const void *W, int N, int K);
+bool gemm_fuses_silu_mul(int dtype, const void *A, const void *W, int N, int K, int rows_cap);
 
 void embed(hipStream_t s, int dtype, const void *table, int hidden, Rows rows, RowIndex ri, SlotState st,
            int mask_id, float *resid);

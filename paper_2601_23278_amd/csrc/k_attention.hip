@@ -12,51 +12,90 @@ namespace fk {
 template <typename T> __device__ __forceinline__ float to_f(T v) { return (float)v; }
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float wave_sum(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-
 // ---------------------------------------------------------------------------------------------
-// One wavefront per (row, query head): lanes split the head dimension, tokens are visited in order with an
-// online softmax.  Exact to fp32 rounding; used for fp32 models and as the fallback path.
-template <typename T, int NE>   // NE = D / 64 elements per lane
-__global__ __launch_bounds__(64) void k_attn_rowwave(const T *__restrict__ q, int q_stride, int Hq, Rows rows, RowIndex ri,
-                                                     SlotState st, const uint64_t *vis_by_b, KvLayer kv, T *out) {
+// fp32 models and the fallback path: one workgroup of four wavefronts per (row, query head), exact to fp32 rounding.  A wavefront takes
+// every fourth tile of 16 tokens with an online softmax of its own; the four are merged in wavefront order.  The launch is bound by the
+// chain of dependent loads and reductions (one wavefront that walked the tokens one by one took 17 to 37 us for 64 to 96 of them), so a
+// tile reads everything side by side: lane l computes a quarter of the product with token l % 16, two exchanges finish it, and then
+// every lane adds its own output columns over the 16 tokens (V is cached transposed).
+template <typename T, int NE>   // NE = D / 64 output columns per lane
+__global__ __launch_bounds__(256) void k_attn_row(const T *__restrict__ q, int q_stride, int Hq, Rows rows, RowIndex ri,
+                                                  SlotState st, const uint64_t *vis_by_b, KvLayer kv, T *out) {
+  constexpr int D = NE * 64, DQ = D / 4, TT = 16;
+  __shared__ float osh[4][D], msh[4], lsh[4];
   const int r = blockIdx.x;
   const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
   if (r >= M) return;
-  const int hq = blockIdx.y, lane = threadIdx.x;
-  const int D = NE * 64, Hkv = kv.n_kv_heads, P = kv.page_size;
+  const int hq = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int Hkv = kv.n_kv_heads, P = kv.page_size;
   const int hk = hq / (Hq / Hkv);
   const int rm = ri.row_map[r], b = rm / ri.B;
   const int slot = slot_of(ri.seq_slot, b, st);
-  const int L = st.prefix_len[slot];
+  const int L = st.prefix_len[slot], total = L + ri.B;
   const uint64_t vis = vis_by_b ? vis_by_b[b] : ~0ull;
   const int32_t *pt = st.page_table + (size_t)slot * st.table_stride;
   const float scale = 1.0f / sqrtf((float)D);
+  const int tl = lane & (TT - 1), d0 = (lane >> 4) * DQ;
 
-  float qv[NE], o[NE];
-  const T *qr = q + (size_t)r * q_stride + (size_t)hq * D;
-  for (int e = 0; e < NE; ++e) qv[e] = to_f(qr[lane + 64 * e]) * scale, o[e] = 0.f;
+  float qv[DQ], o[NE];
+  const T *qr = q + (size_t)r * q_stride + (size_t)hq * D + d0;
+#pragma unroll
+  for (int i = 0; i < DQ; ++i) qv[i] = to_f(qr[i]) * scale;
+#pragma unroll
+  for (int e = 0; e < NE; ++e) o[e] = 0.f;
   float m = -INFINITY, l = 0.f;
   const size_t page_elems = (size_t)2 * Hkv * P * D;
-  for (int t = 0; t < L + ri.B; ++t) {
-    if (t >= L && !((vis >> (t - L)) & 1ull)) continue;
-    const T *kp = (const T *)kv.base + (size_t)pt[t / P] * page_elems + ((size_t)hk * P + (t % P)) * D;
-    const T *vp = (const T *)kv.base + (size_t)pt[t / P] * page_elems + (size_t)(Hkv + hk) * P * D + (t % P);
+  for (int t0 = wave * TT; t0 < total; t0 += 4 * TT) {
+    const int t = min(t0 + tl, total - 1), page = pt[t / P];
+    const T *kp = (const T *)kv.base + (size_t)page * page_elems + ((size_t)hk * P + (t % P)) * D + d0;
+    float vv[NE][TT];
+#pragma unroll
+    for (int j = 0; j < TT; ++j) {
+      const int tj = min(t0 + j, total - 1);
+      const T *vp = (const T *)kv.base + (size_t)__shfl(page, j) * page_elems + (size_t)(Hkv + hk) * P * D + (tj % P);
+#pragma unroll
+      for (int e = 0; e < NE; ++e) vv[e][j] = to_f(vp[(size_t)(lane + 64 * e) * P]);
+    }
     float s = 0.f;
-    for (int e = 0; e < NE; ++e) s += qv[e] * to_f(kp[lane + 64 * e]);
-    s = wave_sum(s);
-    float mn = fmaxf(m, s);
-    float corr = __expf(m - mn), pr = __expf(s - mn);
-    l = l * corr + pr;
-    for (int e = 0; e < NE; ++e) o[e] = o[e] * corr + pr * to_f(vp[(size_t)(lane + 64 * e) * P]);
+#pragma unroll
+    for (int i = 0; i < DQ; ++i) s += qv[i] * to_f(kp[i]);
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    const int tt = t0 + tl;
+    const bool seen = tt < L || (tt < total && ((vis >> (tt - L)) & 1ull));
+    const uint64_t seen_all = __ballot(seen);
+    if (!seen) s = -INFINITY;
+    float mn = s;
+    for (int x = 8; x > 0; x >>= 1) mn = fmaxf(mn, __shfl_xor(mn, x));
+    mn = fmaxf(m, mn);
+    const float mu = mn == -INFINITY ? 0.f : mn, corr = __expf(m - mu), pr = __expf(s - mu);
+    float ls = pr;
+    for (int x = 8; x > 0; x >>= 1) ls += __shfl_xor(ls, x);
+    l = l * corr + ls;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) o[e] *= corr;
+#pragma unroll
+    for (int j = 0; j < TT; ++j) {
+      const float pj = __shfl(pr, j);
+#pragma unroll
+      for (int e = 0; e < NE; ++e) o[e] += (seen_all >> j) & 1ull ? pj * vv[e][j] : 0.f;   // an unseen token adds nothing, whatever its V holds
+    }
     m = mn;
   }
-  T *orow = out + (size_t)r * Hq * D + (size_t)hq * D;
-  float inv = l > 0.f ? 1.0f / l : 0.f;
-  for (int e = 0; e < NE; ++e) orow[lane + 64 * e] = (T)(o[e] * inv);
+#pragma unroll
+  for (int e = 0; e < NE; ++e) osh[wave][lane + 64 * e] = o[e];
+  if (lane == 0) { msh[wave] = m; lsh[wave] = l; }
+  __syncthreads();
+  if (wave >= NE) return;
+  const float mm = fmaxf(fmaxf(msh[0], msh[1]), fmaxf(msh[2], msh[3]));
+  float num = 0.f, den = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float c = msh[w] == -INFINITY ? 0.f : __expf(msh[w] - mm);
+    den += lsh[w] * c;
+    num += osh[w][threadIdx.x] * c;
+  }
+  out[(size_t)r * Hq * D + (size_t)hq * D + threadIdx.x] = (T)(den > 0.f ? num / den : 0.f);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -543,11 +582,11 @@ bool attention(hipStream_t s, const AttnArgs &a) {
   dim3 grid(a.rows.cap, a.n_q_heads);
   const int ne = a.kv.head_dim / 64;
   if (a.dtype == FOCUS_F32) {
-    if (ne == 1) k_attn_rowwave<float, 1><<<grid, 64, 0, s>>>((const float *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (float *)a.out);
-    else k_attn_rowwave<float, 2><<<grid, 64, 0, s>>>((const float *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (float *)a.out);
+    if (ne == 1) k_attn_row<float, 1><<<grid, 256, 0, s>>>((const float *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (float *)a.out);
+    else k_attn_row<float, 2><<<grid, 256, 0, s>>>((const float *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (float *)a.out);
   } else {
-    if (ne == 1) k_attn_rowwave<bf16_t, 1><<<grid, 64, 0, s>>>((const bf16_t *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (bf16_t *)a.out);
-    else k_attn_rowwave<bf16_t, 2><<<grid, 64, 0, s>>>((const bf16_t *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (bf16_t *)a.out);
+    if (ne == 1) k_attn_row<bf16_t, 1><<<grid, 256, 0, s>>>((const bf16_t *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (bf16_t *)a.out);
+    else k_attn_row<bf16_t, 2><<<grid, 256, 0, s>>>((const bf16_t *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (bf16_t *)a.out);
   }
   return false;
 }
@@ -594,31 +633,21 @@ __global__ __launch_bounds__(256) void k_importance(ImpArgs a) {
   }
   __syncthreads();
   const float scale = 1.0f / sqrtf((float)D);
-  // thread -> query row i = tid / 4 and keys j = (tid % 4) + 4 * jj
-  const int i = threadIdx.x >> 2, j0 = threadIdx.x & 3;
-  if (i < nq) {
-    float acc[MAXB / 4];
-    for (int jj = 0; jj < MAXB / 4; ++jj) acc[jj] = 0.f;
+  // one (query, key) pair per thread and trip: a block of 16 positions is one trip of all 256 threads (by rows it kept 64 of them busy,
+  // four keys each: 23 us a launch)
+  for (int pair = threadIdx.x; pair < nq * B; pair += 256) {
+    const int i = pair / B, j = pair % B;
     const T *qi = base + (size_t)i * stride + (size_t)h * D;
+    const float *kj = ks + j * (D + 1);
     constexpr int VE = 16 / sizeof(T);            // the query row is read in 16-byte pieces
+    float acc = 0.f;
     for (int d0 = 0; d0 < D; d0 += VE) {
       T qv[VE];
       *(u32x4 *)qv = *(const u32x4 *)(qi + d0);
 #pragma unroll
-      for (int e = 0; e < VE; ++e) {
-        const float qd = to_f(qv[e]);
-#pragma unroll
-        for (int jj = 0; jj < MAXB / 4; ++jj) {
-          int j = j0 + 4 * jj;
-          if (j < B) acc[jj] += qd * ks[j * (D + 1) + d0 + e];
-        }
-      }
+      for (int e = 0; e < VE; ++e) acc += to_f(qv[e]) * kj[d0 + e];
     }
-#pragma unroll
-    for (int jj = 0; jj < MAXB / 4; ++jj) {
-      int j = j0 + 4 * jj;
-      if (j < B) S[i][j] = acc[jj] * scale;
-    }
+    S[i][j] = acc * scale;
   }
   __syncthreads();
   if ((int)threadIdx.x < nq) {

@@ -1,10 +1,10 @@
 // Dense projections  C[M, N] = A[M, K] * W[N, K]^T  (activations times [out, in] weights), fp32 accumulate.
 //
-// Two kernels:
+// Kernels:
 //   k_gemm_valu  any element type, any shape: LDS-tiled 64x64x16, 4x4 outputs per lane on the vector ALU.
-//                Used for fp32 models (the tiny oracle-check configuration) and for shapes the MFMA kernel
-//                does not take.
-//   k_gemm_mfma  bf16 on the matrix cores (see below).
+//                Used for large fp32 products and for shapes the matrix-core kernels do not take.
+//   k_gemm_f32   small fp32 products on the matrix cores (full fp32 products and sums).
+//   k_gemm_pipe, k_gemm_mfma  bf16 on the matrix cores (see below).
 // M is read from device memory when the row count is only known on the device (packed batch after eviction).
 #include <algorithm>
 
@@ -69,6 +69,82 @@ static void launch_valu(hipStream_t s, const void *A, const void *W, int N, int 
     k_gemm_valu<T, EPI_ADD_F32><<<grid, 256, 0, s>>>((const T *)A, (const T *)W, N, K, rows, out, ldo);
   else
     k_gemm_valu<T, EPI_STORE_F32><<<grid, 256, 0, s>>>((const T *)A, (const T *)W, N, K, rows, out, ldo);
+}
+
+// ---------------------------------------------------------------------------------------------
+// fp32 on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 products, fp32 sums).  The fp32 models are small, so a launch is bound by
+// latency: 64 x 64 tiles gave 64 rows x 256 columns four workgroups that walked K = 1024 alone (65 us).  Here a tile is 16 rows x 16
+// columns and the workgroup's wavefronts share its K: wavefront w takes the 16-wide K pieces w, w + NW, ..., four in flight, straight from
+// global memory (a 16-byte load per operand feeds four products; both operands permute k alike), and the partial tiles are added in
+// wavefront order through LDS: 5.2 us.
+// SiLU*up: the workgroup computes the gate and the up tile of the same columns and stores silu(gate) * up.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <int NW, int EPI>
+__global__ __launch_bounds__(NW * 64) void k_gemm_f32(const float *__restrict__ A, const float *__restrict__ W, int N, int K, Rows rows,
+                                                      float *out, int ldo) {
+  constexpr int NB = EPI == EPI_SILU_MUL ? 2 : 1, U = 4;
+  __shared__ f32x4 part[NB][NW][64];
+  const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
+  const int ncol = N / NB, n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
+  if (m0 >= M) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, kq = (lane >> 4) * 4;
+  const float *pa = A + (size_t)min(m0 + r, M - 1) * K, *pw[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) pw[b] = W + (size_t)(b * ncol + min(n0 + r, ncol - 1)) * K;
+  f32x4 acc[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) acc[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  for (int c = wave; c * 16 < K; c += NW * U) {
+    f32x4 va[U], vw[NB][U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = (c + u * NW) * 16 + kq;
+      const bool in = k < K;                              // K is a multiple of 4: a piece is inside or outside as a whole
+      va[u] = in ? *(const f32x4 *)(pa + k) : zero;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) vw[b][u] = in ? *(const f32x4 *)(pw[b] + k) : zero;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u][e], vw[b][u][e], acc[b], 0, 0, 0);
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b) part[b][wave][lane] = acc[b];
+  __syncthreads();
+  if (wave != 0) return;
+#pragma unroll
+  for (int w = 1; w < NW; ++w)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] += part[b][w][lane];
+  // register i of lane l is C[4 * (l / 16) + i][l % 16]
+  const int gn = n0 + r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int gm = m0 + kq + i;
+    if (gm >= M || gn >= ncol) continue;
+    float *o = out + (size_t)gm * ldo + gn;
+    if (EPI == EPI_SILU_MUL) *o = acc[0][i] / (1.0f + __expf(-acc[0][i])) * acc[NB - 1][i];
+    else if (EPI == EPI_ADD_F32) *o += acc[0][i];
+    else *o = acc[0][i];
+  }
+}
+
+template <int NW>
+static void launch_f32(hipStream_t s, const float *A, const float *W, int N, int K, Rows rows, int epi, float *out, int ldo) {
+  const dim3 grid(((epi == EPI_SILU_MUL ? N / 2 : N) + 15) / 16, (rows.cap + 15) / 16);
+  if (epi == EPI_SILU_MUL) k_gemm_f32<NW, EPI_SILU_MUL><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo);
+  else if (epi == EPI_ADD_F32) k_gemm_f32<NW, EPI_ADD_F32><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo);
+  else k_gemm_f32<NW, EPI_STORE_F32><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo);
+}
+// 16-byte loads need K a multiple of 4 and aligned operands.  A workgroup reads its operands without sharing them, so from about 1024
+// tiles of 64 x 64 on k_gemm_valu is the faster one (rows x N x K, us, valu / this: 64 x 1024 x 1024 136 / 6, 1024 x 1024 x 1024
+// 181 / 60, 256 x 4096 x 2048 366 / 117, 1024 x 4096 x 2048 428 / 449, 4096 x 4096 x 2048 1394 / 1772).
+static bool takes_f32(const void *A, const void *W, int N, int K, int rows_cap) {
+  return K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0 && (long)((rows_cap + 63) / 64) * ((N + 63) / 64) < 1024;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -644,14 +720,20 @@ bool gemm_conf_partials(hipStream_t s, int dtype, const void *A, const void *W, 
   return false;
 }
 
-bool gemm_fuses_silu_mul(int dtype, const void *A, const void *W, int N, int K) {
+bool gemm_fuses_silu_mul(int dtype, const void *A, const void *W, int N, int K, int rows_cap) {
+  if (dtype == FOCUS_F32) return N % 2 == 0 && takes_f32(A, W, N, K, rows_cap);
   return dtype == FOCUS_BF16 && K % 64 == 0 && N % 2 == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)W & 15) == 0;
 }
 
 void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, Rows rows, int epilogue,
           void *out, int ldo, Warm warm, Scratch scratch) {
   if (rows.cap <= 0) return;
-  if (dtype == FOCUS_F32) { launch_valu<float>(s, A, W, N, K, rows, epilogue, out, ldo); return; }
+  if (dtype == FOCUS_F32) {
+    if (!takes_f32(A, W, N, K, rows.cap)) launch_valu<float>(s, A, W, N, K, rows, epilogue, out, ldo);
+    else if (K >= 512) launch_f32<8>(s, (const float *)A, (const float *)W, N, K, rows, epilogue, (float *)out, ldo);
+    else launch_f32<4>(s, (const float *)A, (const float *)W, N, K, rows, epilogue, (float *)out, ldo);
+    return;
+  }
   const bool aligned = K % 64 == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)W & 15) == 0;
   if (!aligned) { launch_valu<bf16_t>(s, A, W, N, K, rows, epilogue, out, ldo); return; }
   // tile choice: the pipelined kernels run one workgroup per CU; take the largest tile that still gives every CU work

@@ -1,6 +1,7 @@
 """Sizes at which a launch changes its shape (splits, tiles, variants of a kernel), each against the CPU oracle on the same inputs."""
 import pytest
 
+import focus_inputs as fi
 from test_gpu_parity import compare_steps, small_bf16
 
 pytestmark = pytest.mark.gpu
@@ -13,3 +14,15 @@ def test_attention_context_splits_and_their_merge(prefix, batch, block):
     and with many share a launch.  The bf16 bound of the parity tests."""
     lengths = dict(prefix_lo=prefix, prefix_hi=prefix, prefix_dist="fixed") if batch == 1 else dict(prefix_lo=5, prefix_hi=prefix)
     compare_steps(small_bf16(batch=batch, n_q_heads=4, n_kv_heads=1, n_layers=3, block_size=block, steps=1, **lengths), 1, 2e-2, exact=False)
+
+
+@pytest.mark.parametrize("shape", [dict(hidden=264, ffn=40, vocab=1003, batch=3, block_size=5),            # remainders of the 16-wide tiles
+                                   dict(hidden=1032, ffn=520, vocab=515, batch=1, block_size=17),          # eight wavefronts, K not a multiple of 16
+                                   dict(hidden=64, ffn=64, vocab=17, batch=2, block_size=1),               # the smallest
+                                   dict(hidden=128, ffn=64, vocab=4100, batch=33, block_size=32),          # lm_head: 1072 tiles of 64 x 64
+                                   dict(prefix_lo=200, prefix_hi=203, page_size=8, head_dim=128, n_q_heads=4, n_kv_heads=2)])
+def test_fp32_projections_and_attention(shape):
+    """fp32 models at the remainders of the projection and attention tiles and on both sides of the projections' dispatch, decisions
+    exact and values within the fp32 bound of the parity tests."""
+    budget = dict(budget_mode=1, keep_ratio=1.0) if shape.get("batch") == 33 else {}
+    compare_steps(fi.workload("c1_tiny", **dict(shape, **budget)), 2, 1e-3, exact=True)
