@@ -30,7 +30,7 @@ struct Plan {
   size_t off_rope, off_resid, off_resid_p, off_normed, off_qkv, off_q_p, off_attn, off_gate_up, off_act, off_logits;
   size_t off_partial, off_delta, off_K, off_keep, off_n_keep, off_vis, off_cu, off_cu_full, off_row_map,
       off_row_map_full, off_total, off_total_full, off_conf, off_argmax, off_prompt, off_prompt_off, off_prompt_len,
-      off_slot_list, off_part_o, off_part_ml, off_order, off_uncached, off_finalized;
+      off_slot_list, off_admit, off_part_o, off_part_ml, off_order, off_uncached, off_finalized;
   // mixture-of-experts work buffers (zero-sized for a dense model)
   size_t off_moe_logits, off_moe_idx, off_moe_w, off_moe_list, off_moe_count, off_moe_offs, off_moe_tile_e, off_moe_tile_m0,
       off_moe_ntiles, off_moe_pos, off_moe_arow, off_moe_aexp, off_moe_act, off_moe_y;
@@ -86,6 +86,9 @@ Plan make_plan(const focus_config &c) {
   p.off_conf = take(rows * 4);
   p.off_argmax = take(rows * 4);
   p.off_prompt = take(nb * (size_t)c.max_prefix_len * 4);
+  // upload of an admission (page tables and four numbers per sequence): where the prompts go afterwards, if it fits
+  const size_t admit_bytes = nb * ((size_t)p.table_stride + 4) * 4;
+  p.off_admit = admit_bytes <= nb * (size_t)c.max_prefix_len * 4 ? p.off_prompt : take(admit_bytes);
   p.off_prompt_off = take(nb * 4);
   p.off_prompt_len = take(nb * 4);
   p.off_slot_list = take(nb * 4);
@@ -593,7 +596,9 @@ int focus_prefill_kv(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int3
   const int B = g.block_size;
   // host-side checks: slots distinct and in range, lengths in range, pages in range and enough of them
   std::vector<char> used(g.max_batch, 0);
-  std::vector<int32_t> slots(n_seq), table((size_t)n_seq * pl.table_stride, 0), offs(n_seq), counts(n_seq);
+  // one upload: per sequence slot, prefix length, first prompt token and page count, then the page tables
+  std::vector<int32_t> up((size_t)n_seq * (4 + pl.table_stride), 0);
+  int32_t *const slots = up.data(), *const lens = slots + n_seq, *const offs = lens + n_seq, *const counts = offs + n_seq, *const table = counts + n_seq;
   long long total_prompt = 0;
   int max_len = 0;
   for (int b = 0; b < n_seq; ++b) {
@@ -601,7 +606,7 @@ int focus_prefill_kv(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int3
     if (slot < 0 || slot >= g.max_batch || used[slot]) return fail(ctx, FOCUS_EINVAL, "sequence %d: slot %d out of range or repeated", b, slot);
     used[slot] = 1;
     slots[b] = slot;
-    int L = prefix_len[b];
+    int L = lens[b] = prefix_len[b];
     if (L < 0 || L > g.max_prefix_len) return fail(ctx, FOCUS_EINVAL, "sequence %d: prefix_len %d outside 0..%d", b, L, g.max_prefix_len);
     int need = (L + B + g.page_size - 1) / g.page_size;
     if (need > table_stride) return fail(ctx, FOCUS_EINVAL, "sequence %d: needs %d pages, table_stride is %d", b, need, table_stride);
@@ -625,20 +630,14 @@ int focus_prefill_kv(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int3
   }
   ctx->max_total = (max_len + B > ctx->max_total) ? max_len + B : ctx->max_total;
   fk::SlotState st = ctx->slots();
-  // page tables: one row per slot
-  for (int b = 0; b < n_seq; ++b)
-    HIP_TRY(ctx, hipMemcpyAsync(st.page_table + (size_t)slots[b] * pl.table_stride, table.data() + (size_t)b * pl.table_stride,
-                                (size_t)pl.table_stride * 4, hipMemcpyHostToDevice, s));
-  for (int b = 0; b < n_seq; ++b)
-    HIP_TRY(ctx, hipMemcpyAsync(st.page_count + slots[b], &counts[b], 4, hipMemcpyHostToDevice, s));
   int32_t *d_len = ctx->at<int32_t>(pl.off_prompt_len), *d_off = ctx->at<int32_t>(pl.off_prompt_off);
   int32_t *d_slots = ctx->at<int32_t>(pl.off_slot_list);
-  HIP_TRY(ctx, hipMemcpyAsync(d_len, prefix_len, (size_t)n_seq * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(ctx, hipMemcpyAsync(d_off, offs.data(), (size_t)n_seq * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(ctx, hipMemcpyAsync(d_slots, slots.data(), (size_t)n_seq * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(ctx, hipStreamSynchronize(s));     // host vectors go out of scope / are reused below
+  int32_t *d_up = ctx->at<int32_t>(pl.off_admit);
+  HIP_TRY(ctx, hipMemcpyAsync(d_up, up.data(), up.size() * 4, hipMemcpyHostToDevice, s));   // `up` lives until the synchronisation below
+  const bool prefill = prompt_tokens && total_prompt > 0;
+  fk::admit(s, n_seq, B, d_up, d_slots, d_len, d_off, st, !prefill, g.mask_token_id, keep_stats);
 
-  if (prompt_tokens && total_prompt > 0) {
+  if (prefill) {
     HIP_TRY(ctx, hipMemcpyAsync(ctx->at<int32_t>(pl.off_prompt), prompt_tokens, (size_t)total_prompt * 4, hipMemcpyHostToDevice, s));
     uint64_t *keep = ctx->at<uint64_t>(pl.off_keep);
     int32_t *cu = ctx->at<int32_t>(pl.off_cu), *row_map = ctx->at<int32_t>(pl.off_row_map), *total = ctx->at<int32_t>(pl.off_total);
@@ -654,8 +653,8 @@ int focus_prefill_kv(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int3
         layer_rest(ctx, s, l, rs, resid, ctx->at<char>(pl.off_qkv), qkv_w, keep);
       }
     }
+    fk::reset_block_state(s, n_seq, B, d_slots, st, d_len, g.mask_token_id, keep_stats);
   }
-  fk::reset_block_state(s, n_seq, B, d_slots, st, d_len, g.mask_token_id, keep_stats);
   HIP_TRY(ctx, hipStreamSynchronize(s));
   HIP_TRY(ctx, hipGetLastError());
   return FOCUS_OK;

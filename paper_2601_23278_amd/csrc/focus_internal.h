@@ -241,6 +241,10 @@ void commit(hipStream_t s, const CommitArgs &a);
 void prefill_chunk_setup(hipStream_t s, int n_seq, int B, int chunk, const int32_t *seq_slot, SlotState st,
                          const int32_t *prompt, const int32_t *prompt_offset, const int32_t *prompt_len,
                          uint64_t *keep_bits);
+// Spreads the upload of an admission ([n] slots, [n] prefix lengths, [n] prompt offsets, [n] page counts, [n, table_stride] page
+// tables) into the slots and into the three lists; reset: also starts the block of every sequence (reset_block_state()).
+void admit(hipStream_t s, int n_seq, int B, const int32_t *up, int32_t *slot_list, int32_t *prompt_len, int32_t *prompt_off, SlotState st,
+           bool reset, int mask_id, int keep_stats);
 void reset_block_state(hipStream_t s, int n_seq, int B, const int32_t *seq_slot, SlotState st,
                        const int32_t *prefix_len, int mask_id, int keep_stats);
 // Multi-block generation: picks the sequences whose block is complete (and that have room for another block),

@@ -346,13 +346,10 @@ void length_order(hipStream_t s, int n_seq, const int32_t *seq_slot, SlotState s
 }
 
 // New block: every position masked, nothing processed; statistics kept or cleared.
-__global__ void k_reset_block(int n_seq, int B, const int32_t *seq_slot, SlotState st, const int32_t *prefix_len,
-                              int mask_id, int keep_stats) {
-  int b = blockIdx.x;
-  int slot = slot_of(seq_slot, b, st);
-  if (threadIdx.x < B) st.tokens[slot * B + threadIdx.x] = mask_id;
+__device__ __forceinline__ void reset_block(int slot, int B, SlotState st, int prefix_len, int mask_id, int keep_stats) {
+  if ((int)threadIdx.x < B) st.tokens[slot * B + threadIdx.x] = mask_id;
   if (threadIdx.x == 0) {
-    st.prefix_len[slot] = prefix_len[b];
+    st.prefix_len[slot] = prefix_len;
     st.mask_bits[slot] = B >= 64 ? ~0ull : ((1ull << B) - 1);
     st.processed_bits[slot] = 0;
     st.cached_bits[slot] = 0;
@@ -362,9 +359,34 @@ __global__ void k_reset_block(int n_seq, int B, const int32_t *seq_slot, SlotSta
     }
   }
 }
+__global__ void k_reset_block(int n_seq, int B, const int32_t *seq_slot, SlotState st, const int32_t *prefix_len,
+                              int mask_id, int keep_stats) {
+  const int b = blockIdx.x;
+  reset_block(slot_of(seq_slot, b, st), B, st, prefix_len[b], mask_id, keep_stats);
+}
 void reset_block_state(hipStream_t s, int n_seq, int B, const int32_t *seq_slot, SlotState st,
                        const int32_t *prefix_len, int mask_id, int keep_stats) {
   if (n_seq > 0) k_reset_block<<<n_seq, 64, 0, s>>>(n_seq, B, seq_slot, st, prefix_len, mask_id, keep_stats);
+}
+
+// One workgroup per admitted sequence.  Bound by the round trip to the host: two copies per sequence from pageable memory, about 2.2 us
+// each, were 1.2 ms of a pass that admits 256 requests (16.6 instead of 17.8 ms); one copy and this launch are a few tens of us.
+__global__ __launch_bounds__(64) void k_admit(int n_seq, int B, const int32_t *up, int32_t *slot_list, int32_t *prompt_len, int32_t *prompt_off,
+                                              SlotState st, bool reset, int mask_id, int keep_stats) {
+  const int b = blockIdx.x, slot = up[b], len = up[n_seq + b];          // slots were checked on the host
+  const int32_t *table = up + (size_t)4 * n_seq + (size_t)b * st.table_stride;
+  for (int i = threadIdx.x; i < st.table_stride; i += 64) st.page_table[(size_t)slot * st.table_stride + i] = table[i];
+  if (threadIdx.x == 0) {
+    slot_list[b] = slot;
+    prompt_len[b] = len;
+    prompt_off[b] = up[2 * n_seq + b];
+    st.page_count[slot] = up[3 * n_seq + b];
+  }
+  if (reset) reset_block(slot, B, st, len, mask_id, keep_stats);
+}
+void admit(hipStream_t s, int n_seq, int B, const int32_t *up, int32_t *slot_list, int32_t *prompt_len, int32_t *prompt_off, SlotState st,
+           bool reset, int mask_id, int keep_stats) {
+  if (n_seq > 0) k_admit<<<n_seq, 64, 0, s>>>(n_seq, B, up, slot_list, prompt_len, prompt_off, st, reset, mask_id, keep_stats);
 }
 
 __global__ void k_finalize_pick(int n_seq, int B, int P, const int32_t *seq_slot, SlotState st, uint64_t *keep_bits, int32_t *finalized) {

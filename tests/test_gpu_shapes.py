@@ -26,3 +26,9 @@ def test_fp32_projections_and_attention(shape):
     exact and values within the fp32 bound of the parity tests."""
     budget = dict(budget_mode=1, keep_ratio=1.0) if shape.get("batch") == 33 else {}
     compare_steps(fi.workload("c1_tiny", **dict(shape, **budget)), 2, 1e-3, exact=True)
+
+
+@pytest.mark.parametrize("shape", [dict(page_size=1, prefix_lo=3, prefix_hi=5), dict(page_size=1, prefix_lo=61, prefix_hi=64), dict(prefix_lo=0, prefix_hi=1)])
+def test_admission_upload(shape):
+    """Page tables longer than the prompts (the upload has a region of its own then), shorter, and prompts without tokens."""
+    compare_steps(fi.workload("c1_tiny", **shape), 2, 1e-3, exact=True)
