@@ -40,7 +40,64 @@ struct Plan {
   int table_stride, max_rows, max_pos, moe_tile_slots;
 };
 
+// A prefill pass runs many blocks of the prompts at once, as virtual sequences with a slot state of their own (PrefillPass).
+struct PrefillPass {
+  Plan plan;           // the base plan with the layers' buffers replaced
+  size_t off_len, off_table, off_tokens, off_mask, off_keep;
+  int blocks;          // blocks it has room for
+};
+constexpr int kPrefillRows = 8192;   // rows of a pass: the projections gain nothing from more
+
 size_t esize(int dtype) { return dtype == FOCUS_F32 ? 4 : 2; }
+
+template <typename Take> void plan_moe(Plan &p, const focus_config &c, size_t rows, Take &&take) {
+  if (c.n_experts > 0) {
+    const size_t E = c.n_experts, ent = rows * c.experts_per_token;
+    p.moe_tile_slots = (int)(ent / fk::kMoeTileRows + E);
+    p.off_moe_logits = take(rows * E * 4);
+    p.off_moe_idx = take((ent + 1024) * 4);          // read in 1024-entry trips
+    p.off_moe_w = take(ent * 4);
+    p.off_moe_list = take(E * rows * 4);
+    p.off_moe_count = take(E * 4);
+    p.off_moe_offs = take((E + 1) * 4);
+    p.off_moe_tile_e = take((size_t)p.moe_tile_slots * 4);
+    p.off_moe_tile_m0 = take((size_t)p.moe_tile_slots * 4);
+    p.off_moe_ntiles = take(4);
+    p.off_moe_pos = take(ent * 4);
+    p.off_moe_arow = take(ent * 4);
+    p.off_moe_aexp = take(ent * 4);
+    p.off_moe_act = take(ent * c.expert_ffn * esize(c.dtype));
+    p.off_moe_y = take(ent * c.hidden * 4);
+  }
+}
+
+// Lays out a prefill pass of `blocks` blocks from p.off_resid on; returns its end.  gate_up: the unfused feed-forward needs its buffer.
+size_t lay_prefill(const focus_config &c, const Plan &base, size_t blocks, bool gate_up, PrefillPass *pp) {
+  size_t at = base.off_resid;
+  auto take = [&](size_t bytes) { size_t o = at; at += (bytes + 255) & ~(size_t)255; return o; };
+  const size_t B = c.block_size, rows = blocks * B, es = esize(c.dtype), q_w = (size_t)c.n_q_heads * c.head_dim;
+  const size_t ffn_w = c.n_experts > 0 ? (size_t)std::max(c.ffn, c.shared_ffn) : (size_t)c.ffn;
+  Plan &p = pp->plan;
+  p = base;
+  pp->blocks = (int)blocks;
+  pp->off_len = take(blocks * 4);
+  pp->off_table = take(blocks * base.table_stride * 4);
+  pp->off_tokens = take(rows * 4);
+  pp->off_mask = take(blocks * 8);
+  pp->off_keep = take(blocks * 8);
+  p.off_cu = take((blocks + 1) * 4);
+  p.off_row_map = take(rows * 4);
+  p.off_total = take(4);
+  p.off_order = take(blocks * 4);
+  p.off_resid_p = take(rows * c.hidden * 4);
+  p.off_normed = take(rows * c.hidden * es);
+  p.off_qkv = take(rows * (q_w + 2 * (size_t)c.n_kv_heads * c.head_dim) * es);
+  p.off_attn = take(rows * q_w * es);
+  p.off_gate_up = gate_up ? take(rows * 2 * ffn_w * es) : at;
+  p.off_act = take(rows * ffn_w * es);
+  plan_moe(p, c, rows, take);
+  return at;
+}
 
 Plan make_plan(const focus_config &c) {
   Plan p{};
@@ -71,6 +128,9 @@ Plan make_plan(const focus_config &c) {
   p.off_gate_up = take(rows * 2 * ffn_w * es);
   p.off_act = take(rows * ffn_w * es);
   p.off_logits = take(rows * (size_t)c.vocab * 4);
+  // a prefill pass uses everything from off_resid up to here, ten times the rows of a step for the usual vocabularies
+  PrefillPass one;
+  at = std::max(at, lay_prefill(c, p, 1, true, &one));
   p.off_partial = take(2 * nb * c.n_q_heads * B * 4);
   p.off_delta = take(rows * 4);
   p.off_K = take(nb * 4);
@@ -103,24 +163,7 @@ Plan make_plan(const focus_config &c) {
   p.off_n_dec = take(nb * 4);
   p.splitk_bytes = c.dtype == FOCUS_BF16 ? (size_t)64 << 20 : 0;
   p.off_splitk = take(p.splitk_bytes);
-  if (c.n_experts > 0) {
-    const size_t E = c.n_experts, ent = rows * c.experts_per_token;
-    p.moe_tile_slots = (int)(ent / fk::kMoeTileRows + E);
-    p.off_moe_logits = take(rows * E * 4);
-    p.off_moe_idx = take((ent + 1024) * 4);          // read in 1024-entry trips
-    p.off_moe_w = take(ent * 4);
-    p.off_moe_list = take(E * rows * 4);
-    p.off_moe_count = take(E * 4);
-    p.off_moe_offs = take((E + 1) * 4);
-    p.off_moe_tile_e = take((size_t)p.moe_tile_slots * 4);
-    p.off_moe_tile_m0 = take((size_t)p.moe_tile_slots * 4);
-    p.off_moe_ntiles = take(4);
-    p.off_moe_pos = take(ent * 4);
-    p.off_moe_arow = take(ent * 4);
-    p.off_moe_aexp = take(ent * 4);
-    p.off_moe_act = take(ent * c.expert_ffn * es);
-    p.off_moe_y = take(ent * c.hidden * 4);
-  }
+  plan_moe(p, c, rows, take);
   p.bytes = at;
   return p;
 }
@@ -268,6 +311,8 @@ struct RowSet {        // a set of rows the layers run on
   const int32_t *cu;   // rows of sequence b: cu[b] .. cu[b + 1]
   int max_rows_per_seq;
   const int32_t *order;   // attention launch order (longest sequence first) or null
+  const Plan *pl = nullptr;   // the buffers of the layers and the state of the sequences, where they are not the context's own (prefill)
+  fk::SlotState st = {};
 };
 
 // K/V split size for the attention launch: whole sequences when there are enough (sequence, kv head) groups
@@ -276,14 +321,19 @@ struct RowSet {        // a set of rows the layers run on
 void attention_split(const focus_ctx *c, int n_seq, int rows_cap, int rows_per_seq, int *chunk, int *splits);
 
 // rmsnorm -> QKV projection -> rotary + K/V write, for every row of the set (App. C ordering).
-void layer_qkv(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, const float *resid) {
+// kv_only: nothing of the layer but its keys and values is wanted; the query columns are then left as they are.
+void layer_qkv(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, const float *resid, bool kv_only = false) {
   const focus_config &g = c->cfg;
-  const int qkv_w = (g.n_q_heads + 2 * g.n_kv_heads) * g.head_dim;
-  void *normed = c->at<char>(c->plan.off_normed), *qkv = c->at<char>(c->plan.off_qkv);
+  const Plan &pl = rs.pl ? *rs.pl : c->plan;
+  const int qkv_w = (g.n_q_heads + 2 * g.n_kv_heads) * g.head_dim, skip = kv_only ? g.n_q_heads * g.head_dim : 0;
+  const size_t es = esize(g.dtype);
+  char *normed = c->at<char>(pl.off_normed), *qkv = c->at<char>(pl.off_qkv);
   { Timed t(c, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid, c->attn_norm[l], normed, g.hidden, g.rms_eps, rs.rows); }
-  { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, normed, c->w_qkv[l], qkv_w, g.hidden, rs.rows, fk::EPI_STORE, qkv, qkv_w, fk::Warm(), c->scratch()); }
+  { Timed t(c, s, FOCUS_KC_GEMM);
+    fk::gemm(s, g.dtype, normed, (const char *)c->w_qkv[l] + skip * es * g.hidden, qkv_w - skip, g.hidden, rs.rows, fk::EPI_STORE, qkv + skip * es, qkv_w,
+             fk::Warm(), c->scratch()); }
   { Timed t(c, s, FOCUS_KC_KV_WRITE);
-    fk::rope_kv_write(s, g.dtype, qkv, g.n_q_heads, rs.rows, rs.ri, c->slots(), c->kv_layer(l), c->at<float2>(c->plan.off_rope), rs.n_seq, rs.cu); }
+    fk::rope_kv_write(s, g.dtype, qkv, g.n_q_heads, rs.rows, rs.ri, rs.pl ? rs.st : c->slots(), c->kv_layer(l), c->at<float2>(pl.off_rope), rs.n_seq, rs.cu); }
 }
 
 void swiglu_ffn(focus_ctx *c, hipStream_t s, const RowSet &rs, const void *normed, const void *w_gate_up, const void *w_down, int ffn,
@@ -296,12 +346,13 @@ void moe_ffn(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid,
 void layer_rest(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid, const void *q, int q_stride,
                 const uint64_t *vis_by_b, float *imp_partial = nullptr) {
   const focus_config &g = c->cfg;
+  const Plan &pl = rs.pl ? *rs.pl : c->plan;
   const int q_w = g.n_q_heads * g.head_dim;
-  void *normed = c->at<char>(c->plan.off_normed), *attn = c->at<char>(c->plan.off_attn);
+  void *normed = c->at<char>(pl.off_normed), *attn = c->at<char>(pl.off_attn);
   { Timed t(c, s, FOCUS_KC_ATTENTION);
     fk::AttnArgs a{};
     a.dtype = g.dtype; a.q = q; a.q_stride = q_stride; a.n_q_heads = g.n_q_heads; a.n_seq = rs.n_seq; a.cu = rs.cu;
-    a.max_rows_per_seq = rs.max_rows_per_seq; a.rows = rs.rows; a.ri = rs.ri; a.st = c->slots(); a.vis_by_b = vis_by_b;
+    a.max_rows_per_seq = rs.max_rows_per_seq; a.rows = rs.rows; a.ri = rs.ri; a.st = rs.pl ? rs.st : c->slots(); a.vis_by_b = vis_by_b;
     a.kv = c->kv_layer(l); a.out = attn;
     a.part_o = c->plan.part_entries ? c->at<float>(c->plan.off_part_o) : nullptr;
     a.part_ml = c->plan.part_entries ? c->at<float>(c->plan.off_part_ml) : nullptr;
@@ -330,7 +381,8 @@ void layer_rest(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *res
 void swiglu_ffn(focus_ctx *c, hipStream_t s, const RowSet &rs, const void *normed, const void *w_gate_up, const void *w_down, int ffn,
                 float *resid, fk::Warm warm_after) {
   const focus_config &g = c->cfg;
-  void *gate_up = c->at<char>(c->plan.off_gate_up), *act = c->at<char>(c->plan.off_act);
+  const Plan &pl = rs.pl ? *rs.pl : c->plan;
+  void *gate_up = c->at<char>(pl.off_gate_up), *act = c->at<char>(pl.off_act);
   if (fk::gemm_fuses_silu_mul(g.dtype, normed, w_gate_up, 2 * ffn, g.hidden, rs.rows.cap)) {
     Timed t(c, s, FOCUS_KC_GEMM);
     fk::gemm(s, g.dtype, normed, w_gate_up, 2 * ffn, g.hidden, rs.rows, fk::EPI_SILU_MUL, act, ffn,
@@ -346,7 +398,7 @@ void swiglu_ffn(focus_ctx *c, hipStream_t s, const RowSet &rs, const void *norme
 // entries sorted by expert -> grouped gate/up and down projections -> weighted sum; plus the shared expert, if any.
 void moe_ffn(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid, const void *normed) {
   const focus_config &g = c->cfg;
-  const Plan &pl = c->plan;
+  const Plan &pl = rs.pl ? *rs.pl : c->plan;
   const size_t plane = (size_t)g.max_batch * g.block_size * g.experts_per_token;
   fk::MoeArgs a{};
   a.dtype = g.dtype; a.n_experts = g.n_experts; a.k = g.experts_per_token; a.expert_ffn = g.expert_ffn; a.hidden = g.hidden;
@@ -392,7 +444,7 @@ void attention_split(const focus_ctx *c, int n_seq, int rows_cap, int rows_per_s
   long ch = ((max_total + want - 1) / want + 63) / 64 * 64;
   if (ch < 128) ch = 128;
   // partial buffer: rows * H_q * splits entries
-  while (c->plan.part_entries && (long)rows_cap * g.n_q_heads * ((max_total + ch - 1) / ch) > (long)c->plan.part_entries) ch *= 2;
+  while (c->plan.part_entries && ch < max_total && (long)rows_cap * g.n_q_heads * ((max_total + ch - 1) / ch) > (long)c->plan.part_entries) ch *= 2;
   *chunk = (int)ch;
   *splits = (int)((max_total + ch - 1) / ch);
 }
@@ -639,18 +691,49 @@ int focus_prefill_kv(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int3
 
   if (prefill) {
     HIP_TRY(ctx, hipMemcpyAsync(ctx->at<int32_t>(pl.off_prompt), prompt_tokens, (size_t)total_prompt * 4, hipMemcpyHostToDevice, s));
-    uint64_t *keep = ctx->at<uint64_t>(pl.off_keep);
-    int32_t *cu = ctx->at<int32_t>(pl.off_cu), *row_map = ctx->at<int32_t>(pl.off_row_map), *total = ctx->at<int32_t>(pl.off_total);
-    float *resid = ctx->at<float>(pl.off_resid_p);
-    RowSet rs{{n_seq * B, total}, {row_map, d_slots, B}, n_seq, cu, B, nullptr};
-    const int qkv_w = (g.n_q_heads + 2 * g.n_kv_heads) * g.head_dim;
-    for (int c0 = 0; c0 * B < max_len; ++c0) {
-      fk::prefill_chunk_setup(s, n_seq, B, c0, d_slots, st, ctx->at<int32_t>(pl.off_prompt), d_off, d_len, keep);
-      fk::scan_compact(s, n_seq, B, keep, cu, row_map, total);
-      fk::embed(s, g.dtype, ctx->embed, g.hidden, rs.rows, rs.ri, st, g.mask_token_id, resid);
+    // Passes of as many blocks as the workspace has room for, in the order of the prompts: the K/V that a block attends to is written by
+    // earlier passes or by its own pass, which computes the K/V of all its blocks in a layer before it runs the layer's attention.
+    int n_blocks = 0;
+    for (int b = 0; b < n_seq; ++b) n_blocks += (lens[b] + B - 1) / B;
+    const int most_rows = std::min((long)kPrefillRows, (long)n_blocks * B);
+    bool gate_up = false;
+    for (int l = 0; l < g.n_layers - 1; ++l)
+      gate_up |= !ctx->moe_layer(l) ? !fk::gemm_fuses_silu_mul(g.dtype, ctx->ws, ctx->w_gate_up[l], 2 * g.ffn, g.hidden, most_rows)
+                                    : g.shared_ffn > 0 && !fk::gemm_fuses_silu_mul(g.dtype, ctx->ws, ctx->w_shared_gate_up[l], 2 * g.shared_ffn, g.hidden, most_rows);
+    PrefillPass pp;
+    int room = 1, over = std::min(n_blocks, std::max(1, kPrefillRows / B)) + 1;      // `room` blocks fit, `over` blocks need not be tried
+    while (over - room > 1) {
+      const int mid = (room + over) / 2;
+      (lay_prefill(g, pl, mid, gate_up, &pp) <= pl.off_partial ? room : over) = mid;
+    }
+    const int n_passes = (n_blocks + room - 1) / room, per_pass = (n_blocks + n_passes - 1) / n_passes;
+    lay_prefill(g, pl, per_pass, gate_up, &pp);
+    const Plan &lp = pp.plan;
+    fk::SlotState vst{};
+    vst.prefix_len = ctx->at<int32_t>(pp.off_len); vst.page_table = ctx->at<int32_t>(pp.off_table); vst.table_stride = pl.table_stride;
+    vst.tokens = ctx->at<int32_t>(pp.off_tokens); vst.mask_bits = ctx->at<uint64_t>(pp.off_mask); vst.max_batch = per_pass;
+    uint64_t *keep = ctx->at<uint64_t>(pp.off_keep);
+    int32_t *cu = ctx->at<int32_t>(lp.off_cu), *row_map = ctx->at<int32_t>(lp.off_row_map), *total = ctx->at<int32_t>(lp.off_total);
+    int32_t *order = ctx->at<int32_t>(lp.off_order);
+    float *resid = ctx->at<float>(lp.off_resid_p);
+    int b = 0, start = 0;                                          // next block: sequence and first token
+    for (int v0 = 0; v0 < n_blocks; v0 += per_pass) {
+      const int nv = std::min(per_pass, n_blocks - v0);
+      int rows = 0;
+      for (int v = 0; v < nv; ++v) {
+        while (start >= lens[b]) { ++b; start = 0; }
+        rows += std::min(B, lens[b] - start);
+        start += B;
+      }
+      RowSet rs{{rows, total}, {row_map, nullptr, B}, nv, cu, B, order, &lp, vst};
+      fk::prefill_blocks(s, v0, nv, n_seq, B, g.page_size, d_slots, ctx->slots(), ctx->at<int32_t>(pl.off_prompt), d_off, d_len, vst, keep);
+      fk::scan_compact(s, nv, B, keep, cu, row_map, total);
+      fk::length_order(s, nv, nullptr, vst, order);
+      fk::embed(s, g.dtype, ctx->embed, g.hidden, rs.rows, rs.ri, vst, g.mask_token_id, resid);
       for (int l = 0; l < g.n_layers; ++l) {
-        layer_qkv(ctx, s, l, rs, resid);
-        layer_rest(ctx, s, l, rs, resid, ctx->at<char>(pl.off_qkv), qkv_w, keep);
+        const bool last = l == g.n_layers - 1;                     // nothing reads more of the last layer than its keys and values
+        layer_qkv(ctx, s, l, rs, resid, last);
+        if (!last) layer_rest(ctx, s, l, rs, resid, ctx->at<char>(lp.off_qkv), (g.n_q_heads + 2 * g.n_kv_heads) * g.head_dim, keep);
       }
     }
     fk::reset_block_state(s, n_seq, B, d_slots, st, d_len, g.mask_token_id, keep_stats);
@@ -891,8 +974,9 @@ int focus_finalize_blocks(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const
   RowSet rs{{n_seq * B, total}, {row_map, seq_slot, B}, n_seq, cu, B, nullptr};
   fk::embed(s, g.dtype, ctx->embed, g.hidden, rs.rows, rs.ri, st, g.mask_token_id, resid);
   for (int l = 0; l < g.n_layers; ++l) {
-    layer_qkv(ctx, s, l, rs, resid);
-    layer_rest(ctx, s, l, rs, resid, ctx->at<char>(pl.off_qkv), qkv_w, nullptr);   // a finished block sees all of itself
+    const bool last = l == g.n_layers - 1;                                         // of the last layer only the keys and values are wanted
+    layer_qkv(ctx, s, l, rs, resid, last);
+    if (!last) layer_rest(ctx, s, l, rs, resid, ctx->at<char>(pl.off_qkv), qkv_w, nullptr);   // a finished block sees all of itself
   }
   fk::finalize_advance(s, n_seq, B, seq_slot, st, done, g.mask_token_id);
   HIP_TRY(ctx, hipGetLastError());

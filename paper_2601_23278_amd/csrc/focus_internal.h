@@ -237,10 +237,10 @@ struct CommitArgs {
   int32_t *n_decoded_out;
 };
 void commit(hipStream_t s, const CommitArgs &a);
-// Prefill helper: installs chunk c of every prompt as the block (unmasked tokens, prefix_len = c * B).
-void prefill_chunk_setup(hipStream_t s, int n_seq, int B, int chunk, const int32_t *seq_slot, SlotState st,
-                         const int32_t *prompt, const int32_t *prompt_offset, const int32_t *prompt_len,
-                         uint64_t *keep_bits);
+// Prefill helper: blocks v0 .. v0 + nv - 1 of the prompts (cut into blocks of B tokens and counted through, prompt after prompt) as nv
+// virtual sequences: prefix_len = the block's first token, its tokens unmasked, the page table of its prompt's slot.
+void prefill_blocks(hipStream_t s, int v0, int nv, int n_seq, int B, int page_size, const int32_t *seq_slot, SlotState st, const int32_t *prompt,
+                    const int32_t *prompt_offset, const int32_t *prompt_len, SlotState vst, uint64_t *keep_bits);
 // Spreads the upload of an admission ([n] slots, [n] prefix lengths, [n] prompt offsets, [n] page counts, [n, table_stride] page
 // tables) into the slots and into the three lists; reset: also starts the block of every sequence (reset_block_state()).
 void admit(hipStream_t s, int n_seq, int B, const int32_t *up, int32_t *slot_list, int32_t *prompt_len, int32_t *prompt_off, SlotState st,

@@ -420,27 +420,41 @@ void finalize_advance(hipStream_t s, int n_seq, int B, const int32_t *seq_slot, 
   if (n_seq > 0) k_finalize_advance<<<n_seq, 64, 0, s>>>(n_seq, B, seq_slot, st, finalized, mask_id);
 }
 
-// Prefill: chunk c of each prompt becomes the (fully unmasked) block at prefix_len = c * B; sequences whose
-// prompt has ended contribute no rows.
-__global__ void k_prefill_chunk(int n_seq, int B, int chunk, const int32_t *seq_slot, SlotState st, const int32_t *prompt,
-                                const int32_t *prompt_offset, const int32_t *prompt_len, uint64_t *keep_bits) {
-  int b = blockIdx.x;
-  int slot = slot_of(seq_slot, b, st);
-  int start = chunk * B;
-  int nr = min(max(prompt_len[b] - start, 0), B);
-  if ((int)threadIdx.x < nr) st.tokens[slot * B + threadIdx.x] = prompt[prompt_offset[b] + start + threadIdx.x];
-  if (threadIdx.x == 0) {
-    st.prefix_len[slot] = start;
-    st.mask_bits[slot] = 0;
-    st.cached_bits[slot] = 0;
-    keep_bits[b] = nr >= 64 ? ~0ull : ((1ull << nr) - 1);
+// Prefill: one wavefront per block finds its prompt by a prefix sum over the prompts' block counts.
+__global__ __launch_bounds__(64) void k_prefill_blocks(int v0, int n_seq, int B, int P, const int32_t *seq_slot, SlotState st, const int32_t *prompt,
+                                                       const int32_t *prompt_offset, const int32_t *prompt_len, SlotState vst, uint64_t *keep_bits) {
+  const int v = v0 + blockIdx.x, lane = threadIdx.x;
+  int b = -1, c = 0, before = 0;
+  for (int i = 0; i < n_seq && b < 0; i += 64) {
+    const int n = i + lane < n_seq ? (prompt_len[i + lane] + B - 1) / B : 0;
+    int upto = n;
+    for (int o = 1; o < 64; o <<= 1) { const int x = __shfl_up(upto, o); upto += lane >= o ? x : 0; }
+    const uint64_t hit = __ballot(before + upto > v);
+    if (hit) {
+      const int f = __ffsll((long long)hit) - 1;
+      b = i + f;
+      c = v - before - __shfl(upto - n, f);
+    }
+    before += __shfl(upto, 63);
+  }
+  if (b < 0) {                            // more blocks than the prompts have
+    if (lane == 0) { keep_bits[blockIdx.x] = 0; vst.prefix_len[blockIdx.x] = 0; }
+    return;
+  }
+  const int slot = slot_of(seq_slot, b, st), start = c * B, nr = min(prompt_len[b] - start, B);
+  if (lane < nr) vst.tokens[blockIdx.x * B + lane] = prompt[prompt_offset[b] + start + lane];
+  for (int i = lane; i < min((start + B + P - 1) / P, st.table_stride); i += 64)
+    vst.page_table[(size_t)blockIdx.x * vst.table_stride + i] = st.page_table[(size_t)slot * st.table_stride + i];
+  if (lane == 0) {
+    vst.prefix_len[blockIdx.x] = start;
+    vst.mask_bits[blockIdx.x] = 0;
+    keep_bits[blockIdx.x] = nr >= 64 ? ~0ull : ((1ull << nr) - 1);
   }
 }
-void prefill_chunk_setup(hipStream_t s, int n_seq, int B, int chunk, const int32_t *seq_slot, SlotState st,
-                         const int32_t *prompt, const int32_t *prompt_offset, const int32_t *prompt_len,
-                         uint64_t *keep_bits) {
-  if (n_seq > 0)
-    k_prefill_chunk<<<n_seq, 64, 0, s>>>(n_seq, B, chunk, seq_slot, st, prompt, prompt_offset, prompt_len, keep_bits);
+void prefill_blocks(hipStream_t s, int v0, int nv, int n_seq, int B, int page_size, const int32_t *seq_slot, SlotState st, const int32_t *prompt,
+                    const int32_t *prompt_offset, const int32_t *prompt_len, SlotState vst, uint64_t *keep_bits) {
+  if (nv > 0)
+    k_prefill_blocks<<<nv, 64, 0, s>>>(v0, n_seq, B, page_size, seq_slot, st, prompt, prompt_offset, prompt_len, vst, keep_bits);
 }
 
 }  // namespace fk

@@ -32,3 +32,17 @@ def test_fp32_projections_and_attention(shape):
 def test_admission_upload(shape):
     """Page tables longer than the prompts (the upload has a region of its own then), shorter, and prompts without tokens."""
     compare_steps(fi.workload("c1_tiny", **shape), 2, 1e-3, exact=True)
+
+
+@pytest.mark.parametrize("shape", [dict(batch=3, prefix_lo=1, prefix_hi=300, vocab=512, mask_token_id=511),      # several passes, ragged last blocks
+                                   dict(batch=1, prefix_lo=257, prefix_hi=257, vocab=8192, mask_token_id=8191),  # one pass, one token in its last block
+                                   dict(batch=70, prefix_lo=0, prefix_hi=40, block_size=4, n_layers=2)])         # more prompts than a wavefront has lanes, some empty
+def test_prefill_of_several_blocks_per_pass(shape):
+    """Prompts whose blocks share a pass, and passes that end inside a prompt; keys and values of every layer show in the steps."""
+    compare_steps(small_bf16(**dict(dict(prefill="prompt", steps=1), **shape)), 1, 2e-2, exact=False)
+
+
+@pytest.mark.parametrize("shape", [dict(batch=5, prefix_lo=1, prefix_hi=150, block_size=13), dict(batch=1, prefix_lo=640, prefix_hi=640, page_size=1),
+                                   dict(n_experts=4, experts_per_token=2, expert_ffn=64, shared_ffn=64, first_moe_layer=0, prefix_hi=200)])
+def test_prefill_of_several_blocks_per_pass_fp32(shape):
+    compare_steps(fi.workload("c1_tiny", **shape), 2, 1e-3, exact=True)
