@@ -302,7 +302,7 @@ static void launch_mfma(hipStream_t s, const void *A, const void *W, int N, int 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Large problems: BM x 256 x 64 tiles (BM = 256 or 128), 8 wavefronts (2 x 4), K-slabs loaded straight into LDS
+// BM x 256 x 64 tiles, four wavefronts, one workgroup per CU (two at BM = 64), K-slabs loaded straight into LDS
 // (buffer_load_dwordx4 ... lds: lane l of an instruction fills the 16-byte slot l of a 1 KB block = 8 tile rows, so
 // the bank swizzle is applied by choosing which chunk a lane fetches; rows beyond the matrix fall outside the buffer
 // descriptor and read as zero), two LDS stages, software-pipelined by hand:
@@ -338,24 +338,27 @@ template <int CTRL> __device__ __forceinline__ void lane_max_step(float &m, int 
   if (om > m || (om == m && oi < mi)) { m = om; mi = oi; }     // equal maxima: the lower column
 }
 
-template <int BM, int NW, int EPI, int BN = 256>
-__global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void k_gemm_pipe(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W, int N, int K,
+template <int BM, int EPI, int BN = 256>
+__global__ __launch_bounds__(256, BM <= 64 ? 2 : 1) void k_gemm_pipe(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W, int N, int K,
                                                       Rows rows, void *out, int ldo, int tiles_m, int tiles_n, const void *warm,
                                                       unsigned warm_bytes, int splits, size_t split_stride) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer-resource builtins exist in the device pass only
   // splits > 1: the K range is cut into `splits` parts, one workgroup each; part s writes its fp32 sums to
   // out + s * split_stride and a second kernel adds the parts in order (EPI is then EPI_STORE_F32 or EPI_PARTIAL_SILU)
   constexpr bool SILU_W = EPI == EPI_SILU_MUL || EPI == EPI_PARTIAL_SILU;
-  // NW = 8: wavefronts 2 x 4, each BM/2 x 64;  NW = 4: wavefronts 2 x 2, each BM/2 x 128 (a third fewer LDS reads per MFMA,
-  // accumulators in the 256 accumulation registers a lone wavefront per SIMD can have)
-  // BN = 192 (4 wavefronts of 128 x 96) exists for launches whose 256-wide tiles would leave a quarter of the CUs idle
-  constexpr int BK = 64, WCOLS = NW / 2, WM = BM / 2, WN = BN / WCOLS, TM = WM / 32, TN = WN / 32;
-  static_assert(WN % 32 == 0 && (BN / 8) % NW == 0 && (!SILU_W || TN % 2 == 0), "tile shape");
+  // BM = 256: wavefronts 2 x 2, each 128 x BN/2 (the fewest LDS reads per MFMA; accumulators in the 256 accumulation registers a lone
+  // wavefront per SIMD can have).  Otherwise the wavefronts lie side by side, each BM x 64, so that BM may be any multiple of 32: the
+  // height that fits the row count.  (Eight wavefronts, 2 x 4, were slower at every height: 2048 x 4096 x 12288, K cut in two, 185 us
+  // against 176; BM = 128 229 against 208.)
+  // BN = 192 exists for launches whose 256-wide tiles would leave a quarter of the CUs idle
+  constexpr int NW = 4, WROWS = BM == 256 ? 2 : 1;
+  constexpr int BK = 64, WCOLS = NW / WROWS, WM = BM / WROWS, WN = BN / WCOLS, TM = WM / 32, TN = WN / 32;
+  static_assert(WM % 32 == 0 && WN % 32 == 0 && (BM / 8) % NW == 0 && (BN / 8) % NW == 0 && (!SILU_W || TN % 2 == 0), "tile shape");
   constexpr int IA = BM / 8 / NW, IB = BN / 8 / NW, NI = IA + IB;
   constexpr int ASTAGE = BM * 128, WSTAGE = BN * 128, WBASE = 2 * ASTAGE, NMF = TM * TN;
-  // loads issued in the k-step right behind the barrier; the rest follow in the first k-step of the next slab
-  constexpr int L0 = NI / 2, L1 = NI - L0;
-  static_assert(L0 <= NMF && L1 <= NMF && TM + TN <= NMF, "one load and one fragment read per MFMA at most");
+  // loads issued in the k-step right behind the barrier; the rest follow in the first k-steps of the next slab
+  constexpr int L0 = NI / 2 < NMF ? NI / 2 : NMF, L1 = NI - L0 < NMF ? NI - L0 : NMF, L2 = NI - L0 - L1;
+  static_assert(L2 <= NMF && TM + TN <= NMF, "one load and one fragment read per MFMA at most");
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_pipe[];
   unsigned char *const lds = lds_pipe;
   const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
@@ -471,6 +474,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void k_gemm_pipe(const bf
   {                                                                                                     \
     const int so1 = min(((kt) + 1) * (BK * 2), last), so2 = min(((kt) + 2) * (BK * 2), last);           \
     FK_STEP(0, 1, buf, L1, L0, so1, (buf) ^ 1)                                                          \
+    FK_STEP(1, 2, buf, L2, L0 + L1, so1, (buf) ^ 1)                                                     \
     {                                                                                                   \
       const bool hit = (kt) == warm_next && warm_left > 0;                                              \
       const unsigned so = hit ? warm_off : 0x80000000u;                                                 \
@@ -478,7 +482,6 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void k_gemm_pipe(const bf
       warm_prev = __builtin_amdgcn_raw_buffer_load_b32(rs_p, warm_lane, so, 0);                         \
       warm_off += hit ? HIT : 0u; warm_left -= hit ? 1u : 0u; warm_next += hit ? warm_stride : 0;       \
     }                                                                                                   \
-    FK_STEP(1, 2, buf, 0, 0, so1, (buf) ^ 1)                                                            \
     FK_STEP(0, 3, buf, 0, 0, so1, (buf) ^ 1)                                                            \
     __builtin_amdgcn_s_waitcnt(0x0F71); /* vmcnt(1): all but the warm-up load: this wavefront's part of the next slab has landed */ \
     lds_barrier();                     /* ... and everyone's; everyone has read all of this slab */    \
@@ -643,19 +646,87 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float *__restrict__
   }
 }
 
-template <int BM, int NW, int EPI, int BN = 256>
-static bool launch_pipe_epi(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, int K, Rows rows, void *out, int ldo, int tiles_m, int tiles_n, Warm warm,
-                            int splits = 1, size_t split_stride = 0) {
+template <int BM, int EPI, int BN = 256>
+static bool launch_pipe(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, int K, Rows rows, void *out, int ldo, Warm warm, int splits = 1,
+                        size_t split_stride = 0) {
   constexpr int kLds = 2 * (BM + BN) * 128;
+  constexpr bool SILU_W = EPI == EPI_SILU_MUL || EPI == EPI_PARTIAL_SILU;
   static bool ready = false;             // the dynamic LDS size has to be allowed once per kernel
   if (!ready) {
-    if (hipFuncSetAttribute((const void *)k_gemm_pipe<BM, NW, EPI, BN>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess) return false;
+    if (hipFuncSetAttribute((const void *)k_gemm_pipe<BM, EPI, BN>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess) return false;
     ready = true;
   }
+  const int tiles_m = (rows.cap + BM - 1) / BM, tiles_n = SILU_W ? (N / 2 + BN / 2 - 1) / (BN / 2) : (N + BN - 1) / BN;
   const int grid = ((tiles_m * tiles_n * splits + 7) / 8) * 8;
-  k_gemm_pipe<BM, NW, EPI, BN><<<grid, NW * 64, kLds, s>>>(a, w, N, K, rows, out, ldo, tiles_m, tiles_n, warm.ptr, (unsigned)std::min<size_t>(warm.bytes, 0x7fffffffu),
-                                                      splits, split_stride);
+  k_gemm_pipe<BM, EPI, BN><<<grid, 256, kLds, s>>>(a, w, N, K, rows, out, ldo, tiles_m, tiles_n, warm.ptr, (unsigned)std::min<size_t>(warm.bytes, 0x7fffffffu),
+                                                   splits, split_stride);
   return true;
+}
+
+template <int BM>
+static bool launch_pipe_epi(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, int K, Rows rows, int epi, void *out, int ldo, Warm warm, int splits,
+                            size_t split_stride) {
+  switch (epi) {
+    case EPI_STORE: return launch_pipe<BM, EPI_STORE>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
+    case EPI_ADD_F32: return launch_pipe<BM, EPI_ADD_F32>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
+    case EPI_STORE_F32: return launch_pipe<BM, EPI_STORE_F32>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
+    case EPI_SILU_MUL: return launch_pipe<BM, EPI_SILU_MUL>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
+    case EPI_PARTIAL_SILU: return launch_pipe<BM, EPI_PARTIAL_SILU>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
+    case EPI_CONF: return launch_pipe<BM, EPI_CONF>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
+  }
+  return false;
+}
+
+// Shape of a pipelined launch: tile height, tile width and parts of K.
+struct PipeShape { int bm, bn, splits; };
+
+static bool launch_shape(hipStream_t s, PipeShape p, const void *A, const void *W, int N, int K, Rows rows, int epi, void *out, int ldo, Warm warm,
+                         size_t split_stride = 0) {
+  const bf16_t *a = (const bf16_t *)A, *w = (const bf16_t *)W;
+  if (p.bn == 192)
+    return epi == EPI_STORE     ? launch_pipe<256, EPI_STORE, 192>(s, a, w, N, K, rows, out, ldo, warm)
+           : epi == EPI_ADD_F32 ? launch_pipe<256, EPI_ADD_F32, 192>(s, a, w, N, K, rows, out, ldo, warm)
+                                : launch_pipe<256, EPI_STORE_F32, 192>(s, a, w, N, K, rows, out, ldo, warm);
+  switch (p.bm) {
+    case 64: return launch_pipe_epi<64>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
+    case 96: return launch_pipe_epi<96>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
+    case 128: return launch_pipe_epi<128>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
+    case 160: return launch_pipe_epi<160>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
+    case 192: return launch_pipe_epi<192>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
+    case 224: return launch_pipe_epi<224>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
+  }
+  return launch_pipe_epi<256>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
+}
+
+// The shape with the least estimated time.  A compute unit spends about 0.62 + 0.0031 BM us on a 64-wide slab of a BM x 256 tile, takes
+// one tile at a time (of height 64 two, each at half the pace), and a launch has about 10 us of its own; K cut into parts costs writing the fp32 partial sums,
+// reading them back and one more launch (about 4.5 TB/s).  Measured with weights that come from HBM: 2048 x 4096 x 12288 in two parts
+// of 256 rows 176 us (230 with one round of 128-row tiles), 1024 rows in four parts 103 (138), 1536 x 6144 x 4096 in tiles of 192 rows 84
+// (128), 768 x 24576 x 4096 in 160 rows 154 (194), 276 rows of it 84 (103).  The estimates are within 10 %.
+// (Shapes are chosen for the expected row count; the grids cover rows.cap.)
+static PipeShape pipe_shape(int N, int K, Rows rows, int epi, size_t scratch_bytes) {
+  static const int heights[] = {256, 224, 192, 160, 128, 96, 64};
+  const bool silu = epi == EPI_SILU_MUL;
+  const int nk = K / 64, est = rows.expected();
+  const double out_mb = (double)est * (silu ? N / 2 : N) * (epi == EPI_ADD_F32 ? 8 : epi == EPI_STORE_F32 ? 4 : 2) * 1e-6;
+  PipeShape best{256, 256, 1};
+  double best_us = 1e30;
+  auto consider = [&](PipeShape p, long tiles, double slab_us) {
+    const double us = 10 + (double)((tiles * p.splits + 255) / 256) * (nk / p.splits) * slab_us +
+                      (p.splits > 1 ? 3 + (p.splits * (double)est * N * 4e-6 + out_mb) / 4.5 : 0);
+    if (us < best_us) { best_us = us; best = p; }
+  };
+  for (int bm : heights) {
+    const long tiles = (long)((est + bm - 1) / bm) * (silu ? (N / 2 + 127) / 128 : (N + 255) / 256);
+    for (int splits = 1; splits <= 16; splits *= 2) {
+      // an even number of slabs per part, at least four; sums in 16-byte pieces
+      if (splits > 1 && (nk % (splits * 2) || nk / splits < 4 || N % 8 || (size_t)splits * rows.cap * N * 4 > scratch_bytes)) break;
+      consider(PipeShape{bm, 256, splits}, tiles, 0.62 + 0.0031 * bm);
+    }
+  }
+  if (N % 192 == 0 && (epi == EPI_STORE || epi == EPI_ADD_F32 || epi == EPI_STORE_F32))
+    consider(PipeShape{256, 192, 1}, (long)((est + 255) / 256) * (N / 192), 1.25);
+  return best;
 }
 
 // K-split launch for problems with too few tiles to occupy the chip (few rows: the projection is bound by streaming W,
@@ -671,53 +742,19 @@ static void launch_reduce(hipStream_t s, int N, Rows rows, int epi, void *out, i
   else k_splitk_reduce<EPI_STORE_F32><<<grid, 256, 0, s>>>(scratch, splits, stride, rows, N, out, ldo);
 }
 
-static bool launch_split(hipStream_t s, const void *A, const void *W, int N, int K, Rows rows, int epi, void *out, int ldo, Warm warm,
-                         int splits, float *scratch) {
-  const int tiles_m = (rows.cap + 127) / 128;
-  const int tiles_n = epi == EPI_SILU_MUL ? (N / 2 + 127) / 128 : (N + 255) / 256;
-  const bf16_t *a = (const bf16_t *)A, *w = (const bf16_t *)W;
-  const size_t stride = (size_t)rows.cap * N;
-  const bool ok = epi == EPI_SILU_MUL ? launch_pipe_epi<128, 8, EPI_PARTIAL_SILU>(s, a, w, N, K, rows, scratch, N, tiles_m, tiles_n, warm, splits, stride)
-                                      : launch_pipe_epi<128, 8, EPI_STORE_F32>(s, a, w, N, K, rows, scratch, N, tiles_m, tiles_n, warm, splits, stride);
-  if (!ok) return false;
-  launch_reduce(s, N, rows, epi, out, ldo, splits, scratch);
-  return true;
-}
-
-template <int BM, int NW>
-static bool launch_pipe(hipStream_t s, const void *A, const void *W, int N, int K, Rows rows, int epi, void *out, int ldo, Warm warm) {
-  const int tiles_m = (rows.cap + BM - 1) / BM;
-  const int tiles_n = epi == EPI_SILU_MUL ? (N / 2 + 127) / 128 : (N + 255) / 256;
-  const bf16_t *a = (const bf16_t *)A, *w = (const bf16_t *)W;
-  if (epi == EPI_SILU_MUL) return launch_pipe_epi<BM, NW, EPI_SILU_MUL>(s, a, w, N, K, rows, out, ldo, tiles_m, tiles_n, warm);
-  if (epi == EPI_STORE) return launch_pipe_epi<BM, NW, EPI_STORE>(s, a, w, N, K, rows, out, ldo, tiles_m, tiles_n, warm);
-  if (epi == EPI_ADD_F32) return launch_pipe_epi<BM, NW, EPI_ADD_F32>(s, a, w, N, K, rows, out, ldo, tiles_m, tiles_n, warm);
-  return launch_pipe_epi<BM, NW, EPI_STORE_F32>(s, a, w, N, K, rows, out, ldo, tiles_m, tiles_n, warm);
+static bool takes_pipe(int N, int K, int rows_cap) {   // byte offsets of rows within 32 bits, an even number of slabs
+  return (double)std::max(rows_cap + 256, N + 256) * K * 2 < 4.0e9 && K % 128 == 0;
 }
 
 bool gemm_conf_partials(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, Rows rows, float *part, size_t part_bytes,
                         int *n_slots) {
-  if (rows.cap <= 0 || dtype != FOCUS_BF16 || K % 64 || (((uintptr_t)A | (uintptr_t)W) & 15)) return false;
-  if (!((double)std::max(rows.cap + 256, N + 256) * K * 2 < 4.0e9 && (K / 64) % 2 == 0)) return false;
-  const int est = rows.expected(), tn = (N + 255) / 256;
-  const long t256 = (long)((est + 255) / 256) * tn, t128 = (long)((est + 127) / 128) * tn;
-  const bf16_t *a = (const bf16_t *)A, *w = (const bf16_t *)W;
-  // same tile choice as gemm(): the largest tile that gives every compute unit work; four wavefronts where a unit takes several tiles
-  if (t256 >= 160) {
-    const bool four = t256 > 256;
-    const int slots = tn * (four ? 2 : 4), tm = (rows.cap + 255) / 256;
-    if ((size_t)rows.cap * slots * 12 > part_bytes) return false;
-    *n_slots = slots;
-    return four ? launch_pipe_epi<256, 4, EPI_CONF>(s, a, w, N, K, rows, part, slots, tm, tn, Warm())
-                : launch_pipe_epi<256, 8, EPI_CONF>(s, a, w, N, K, rows, part, slots, tm, tn, Warm());
-  }
-  if (t128 >= 160) {
-    const int slots = tn * 4, tm = (rows.cap + 127) / 128;
-    if ((size_t)rows.cap * slots * 12 > part_bytes) return false;
-    *n_slots = slots;
-    return launch_pipe_epi<128, 8, EPI_CONF>(s, a, w, N, K, rows, part, slots, tm, tn, Warm());
-  }
-  return false;
+  if (rows.cap <= 0 || dtype != FOCUS_BF16 || K % 64 || (((uintptr_t)A | (uintptr_t)W) & 15) || !takes_pipe(N, K, rows.cap)) return false;
+  if ((long)((rows.expected() + 127) / 128) * ((N + 255) / 256) < 160) return false;   // a small vocabulary: K-split and materialised logits
+  const PipeShape p = pipe_shape(N, K, rows, EPI_CONF, 0);
+  const int slots = (N + 255) / 256 * (p.bm == 256 ? 2 : 4);       // one per wavefront column
+  if ((size_t)rows.cap * slots * 12 > part_bytes) return false;
+  *n_slots = slots;
+  return launch_shape(s, p, A, W, N, K, rows, EPI_CONF, part, slots, Warm());
 }
 
 bool gemm_fuses_silu_mul(int dtype, const void *A, const void *W, int N, int K, int rows_cap) {
@@ -736,35 +773,14 @@ void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, 
   }
   const bool aligned = K % 64 == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)W & 15) == 0;
   if (!aligned) { launch_valu<bf16_t>(s, A, W, N, K, rows, epilogue, out, ldo); return; }
-  // tile choice: the pipelined kernels run one workgroup per CU; take the largest tile that still gives every CU work
-  // (byte offsets of rows must fit 32 bits there, and the slab count must be even), else the register-staged kernel with smaller tiles
-  const long n_tiles = epilogue == EPI_SILU_MUL ? (N / 2 + 127) / 128 : (N + 255) / 256;
-  const bool fits32 = (double)std::max(rows.cap + 256, N + 256) * K * 2 < 4.0e9 && (K / 64) % 2 == 0;
-  // (tile shapes are chosen for the expected row count; the grids below cover rows.cap)
+  // one tile of rows and fewer column tiles than CUs: pure weight streaming.  The expert-projection kernel (two workgroups per CU, two
+  // weight slabs in flight each) with K cut so that about one workgroup per CU exists (64 rows x 4096 x 4096 16.4 us, 21 with two)
   const int est = rows.expected();
-  const long t256 = (long)((est + 255) / 256) * n_tiles, t128 = (long)((est + 127) / 128) * n_tiles;
-  const int choice = t256 >= 160 ? 256 : (t128 >= 160 ? 128 : 0);
-  // four wavefronts of 128 x 128 read a third less from LDS per MFMA: measured 2-5 % faster where the launch takes more
-  // than one round of workgroups (gate/up, vocabulary projection, full-block layers), no gain on single-round launches
-  const bool four = t256 > 256;
-  // one round of 256-wide tiles that leaves CUs idle (the QKV projection of 2048 rows: 192 tiles): 192-wide tiles fill them
-  const long t192 = N % 192 == 0 ? (long)((est + 255) / 256) * (N / 192) : 0;
-  if (fits32 && choice == 256 && !four && t256 < 240 && t192 > t256 && t192 <= 256 && epilogue != EPI_SILU_MUL) {
-    const int tm = (rows.cap + 255) / 256, tn = N / 192;
-    const bf16_t *a = (const bf16_t *)A, *w = (const bf16_t *)W;
-    const bool ok = epilogue == EPI_STORE ? launch_pipe_epi<256, 4, EPI_STORE, 192>(s, a, w, N, K, rows, out, ldo, tm, tn, warm)
-                  : epilogue == EPI_ADD_F32 ? launch_pipe_epi<256, 4, EPI_ADD_F32, 192>(s, a, w, N, K, rows, out, ldo, tm, tn, warm)
-                                            : launch_pipe_epi<256, 4, EPI_STORE_F32, 192>(s, a, w, N, K, rows, out, ldo, tm, tn, warm);
-    if (ok) return;
-  }
-  if (fits32 && choice == 256 && (four ? launch_pipe<256, 4>(s, A, W, N, K, rows, epilogue, out, ldo, warm) : launch_pipe<256, 8>(s, A, W, N, K, rows, epilogue, out, ldo, warm))) return;
-  if (fits32 && choice == 128 && launch_pipe<128, 8>(s, A, W, N, K, rows, epilogue, out, ldo, warm)) return;
-  if (fits32 && choice == 0 && scratch.ptr && N % 8 == 0 && rows.cap <= 128) {
-    // one tile of rows: pure weight streaming.  The expert-projection kernel (two workgroups per CU, two weight slabs in
-    // flight each) with K cut so that about two workgroups per CU exist
+  const bool pipe = takes_pipe(N, K, rows.cap);
+  if (pipe && scratch.ptr && N % 8 == 0 && rows.cap <= 128 && (epilogue == EPI_SILU_MUL ? (N / 2 + 127) / 128 : (N + 255) / 256) < 160) {
     const int nk = K / 64, tn = epilogue == EPI_SILU_MUL ? (N / 2 + 63) / 64 : (N + 127) / 128;
     int splits = 1;
-    while (splits < 16 && (long)tn * (splits * 2) <= 512 && nk % (splits * 2) == 0 && nk / (splits * 2) >= 4 &&
+    while (splits < 16 && (long)tn * (splits * 2) <= 256 && nk % (splits * 2) == 0 && nk / (splits * 2) >= 4 &&
            (size_t)(splits * 2) * rows.cap * N * 4 <= scratch.bytes)
       splits *= 2;
     if ((size_t)splits * rows.cap * N * 4 <= scratch.bytes &&
@@ -773,15 +789,14 @@ void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, 
       return;
     }
   }
-  if (fits32 && choice == 0 && scratch.ptr && N % 8 == 0) {
-    // too few tiles for the chip: cut K so that about one workgroup per CU exists (each part an even number of slabs, at least 4)
-    const int nk = K / 64;
-    int splits = 1;
-    while (splits < 16 && t128 * (splits * 2) <= 256 && nk % (splits * 4) == 0 && nk / (splits * 2) >= 4 &&
-           (size_t)(splits * 2) * rows.cap * N * 4 <= scratch.bytes)
-      splits *= 2;
-    if (splits > 1 && launch_split(s, A, W, N, K, rows, epilogue, out, ldo, warm, splits, (float *)scratch.ptr)) return;
-    if (launch_pipe<128, 8>(s, A, W, N, K, rows, epilogue, out, ldo, warm)) return;
+  if (pipe) {
+    const PipeShape p = pipe_shape(N, K, rows, epilogue, scratch.ptr ? scratch.bytes : 0);
+    if (p.splits == 1) {
+      if (launch_shape(s, p, A, W, N, K, rows, epilogue, out, ldo, warm)) return;
+    } else if (launch_shape(s, p, A, W, N, K, rows, epilogue == EPI_SILU_MUL ? EPI_PARTIAL_SILU : EPI_STORE_F32, scratch.ptr, N, warm, (size_t)rows.cap * N)) {
+      launch_reduce(s, N, rows, epilogue, out, ldo, p.splits, (const float *)scratch.ptr);
+      return;
+    }
   }
   const long tiles_big = (long)((est + 255) / 256) * ((N + 127) / 128);
   if (tiles_big >= 512) launch_mfma<256, 128>(s, A, W, N, K, rows, epilogue, out, ldo);

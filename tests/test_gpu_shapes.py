@@ -46,3 +46,10 @@ def test_prefill_of_several_blocks_per_pass(shape):
                                    dict(n_experts=4, experts_per_token=2, expert_ffn=64, shared_ffn=64, first_moe_layer=0, prefix_hi=200)])
 def test_prefill_of_several_blocks_per_pass_fp32(shape):
     compare_steps(fi.workload("c1_tiny", **shape), 2, 1e-3, exact=True)
+
+
+@pytest.mark.parametrize("batch,block", [(3, 19), (5, 18), (8, 16), (15, 10), (27, 7), (31, 7), (10, 25), (11, 25), (64, 8)])
+def test_projection_tile_heights(batch, block):
+    """57 to 512 rows against a vocabulary of 200 column tiles: every tile height of the pipelined projection (64 to 256 rows, by the
+    vocabulary's launch) with a remainder in both directions, and K cut in parts (the layers' launches)."""
+    compare_steps(small_bf16(batch=batch, block_size=block, keep_ratio=1.0, vocab=51176, mask_token_id=51175, n_layers=2, steps=1), 1, 2e-2, exact=False)
