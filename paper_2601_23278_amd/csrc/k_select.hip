@@ -11,7 +11,34 @@ namespace fk {
 
 __device__ __forceinline__ uint64_t low_bits(int n) { return n >= 64 ? ~0ull : ((1ull << n) - 1); }
 
+// Value that lane i holds, i the same for all lanes: a scalar read, not a trip through the LDS as __shfl is.
+__device__ __forceinline__ float lane_value(float v, int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i)); }
+
+// Column j of [n_heads, B] added up in head order, PREV: of a second array too.  Sixteen loads per array are in flight at a time: the
+// additions have to keep their order, the loads need not wait for them.
+template <bool PREV>
+__device__ __forceinline__ void head_sums(const float *e, const float *p, int n_heads, int B, float &se, float &sp) {
+  constexpr int U = 16;
+  for (int h0 = 0; h0 < n_heads; h0 += U) {
+    float ve[U], vp[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const size_t at = (size_t)min(h0 + i, n_heads - 1) * B;
+      ve[i] = e[at];
+      if (PREV) vp[i] = p[at];
+    }
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+      if (h0 + i < n_heads) {
+        se += ve[i];
+        if (PREV) sp += vp[i];
+      }
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
+// Bound by latency (one wavefront per sequence, whatever the batch): the loads are batched and lane-to-lane reads are scalar
+// (27 us with one load after the other, 32 heads; the pass of one request, with k_confidence_slots below, 937 -> 884 us).
 __global__ __launch_bounds__(64) void k_select(SelectArgs a) {
   __shared__ float dsh[64];
   const int b = blockIdx.x, j = threadIdx.x, B = a.B;
@@ -25,9 +52,9 @@ __global__ __launch_bounds__(64) void k_select(SelectArgs a) {
   } else {
     float ie = 0.f, ip = 0.f;
     if (in) {
-      for (int h = 0; h < a.n_q_heads; ++h) ie += a.partial_evict[((size_t)b * a.n_q_heads + h) * B + j];
-      if (a.importance_mode == 0)
-        for (int h = 0; h < a.n_q_heads; ++h) ip += a.partial_prev[((size_t)b * a.n_q_heads + h) * B + j];
+      const size_t first = (size_t)b * a.n_q_heads * B + j;
+      if (a.importance_mode == 0) head_sums<true>(a.partial_evict + first, a.partial_prev + first, a.n_q_heads, B, ie, ip);
+      else head_sums<false>(a.partial_evict + first, nullptr, a.n_q_heads, B, ie, ip);
       if (a.imp_out) a.imp_out[(size_t)b * B + j] = ie;
       if (a.imp_prev_out) a.imp_prev_out[(size_t)b * B + j] = ip;
     }
@@ -95,7 +122,7 @@ __global__ __launch_bounds__(64) void k_select(SelectArgs a) {
         z ^= z >> 31;
         const unsigned lo = (unsigned)z, hi = (unsigned)(z >> 32);
         for (int i = 0; i < B; ++i) {
-          const uint64_t zi = ((uint64_t)__shfl(hi, i) << 32) | __shfl(lo, i);
+          const uint64_t zi = ((uint64_t)(unsigned)__builtin_amdgcn_readlane((int)hi, i) << 32) | (unsigned)__builtin_amdgcn_readlane((int)lo, i);
           const bool mi = (masked >> i) & 1ull;
           rank += (mi && (zi > z || (zi == z && i < j))) ? 1 : 0;
         }
@@ -103,7 +130,7 @@ __global__ __launch_bounds__(64) void k_select(SelectArgs a) {
         float v = (a.selection == FOCUS_SELECT_BOTTOM) ? -d : d;   // BOTTOM: smallest delta first
         v = (v != v) ? -INFINITY : v;                              // NaN ranks last
         for (int i = 0; i < B; ++i) {
-          float vi = __shfl(v, i);
+          float vi = lane_value(v, i);
           bool mi = (masked >> i) & 1ull;
           rank += (mi && (vi > v || (vi == v && i < j))) ? 1 : 0;
         }
@@ -141,22 +168,25 @@ void select(hipStream_t s, const SelectArgs &a) {
 // scans a contiguous chunk of sequences), then row_map[cu[b] + i] = b * B + (i-th set bit of keep[b]).
 __global__ __launch_bounds__(256) void k_scan_compact(int n_seq, int B, const uint64_t *keep_bits, int32_t *cu,
                                                       int32_t *row_map, int32_t *total) {
-  __shared__ int part[256];
-  const int t = threadIdx.x;
+  __shared__ int wave_sum[4];
+  const int t = threadIdx.x, lane = t & 63;
   const int chunk = (n_seq + 255) / 256;
   const int b0 = t * chunk, b1 = min(b0 + chunk, n_seq);
   int sum = 0;
   for (int b = b0; b < b1; ++b) sum += __popcll(keep_bits[b]);
-  part[t] = sum;
-  __syncthreads();
-  if (t == 0) {
-    int run = 0;
-    for (int i = 0; i < 256; ++i) { int v = part[i]; part[i] = run; run += v; }
-    cu[n_seq] = run;
-    *total = run;
+  int upto = sum;                                      // inclusive prefix sum inside the wavefront, then over the wavefronts
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(upto, o);
+    if (lane >= o) upto += v;
   }
+  if (lane == 63) wave_sum[t >> 6] = upto;
   __syncthreads();
-  int at = part[t];
+  int at = upto - sum;
+  for (int w = 0; w < (t >> 6); ++w) at += wave_sum[w];
+  if (t == 255) {
+    cu[n_seq] = at + sum;
+    *total = at + sum;
+  }
   for (int b = b0; b < b1; ++b) {
     cu[b] = at;
     uint64_t k = keep_bits[b];
@@ -299,29 +329,48 @@ __global__ __launch_bounds__(256) void k_confidence_merge(const float *__restric
   argmax[r] = mi;
 }
 
-// Merge of the per-wavefront triples that the fused vocabulary projection leaves (gemm_conf_partials): one wavefront per row,
-// lane l folds slots l, l + 64, ... in ascending order, then the lanes are merged; equal maxima keep the lower column.
+// Merge of the per-wavefront triples that the fused vocabulary projection leaves (gemm_conf_partials): one workgroup per row, thread t
+// folds slots t, t + 256, ... in ascending order, then lanes and wavefronts are merged; equal maxima keep the lower column.  Bound by
+// the chain load - exponent - add of a thread: with one wavefront per row it was 37 slots of a vocabulary of 151936 long, each with a
+// load of its own; now it is ten, and the loads of four slots go out together.
 __global__ __launch_bounds__(256) void k_confidence_slots(const float *__restrict__ part, int n_slots, Rows rows, float *conf, int32_t *argmax) {
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  constexpr int U = 4;
+  __shared__ float sm[4], ss[4];
+  __shared__ int si[4];
+  const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
   if (r >= M) return;
   const float *p = part + (size_t)r * n_slots * 3;
   float m = -INFINITY, sum = 0.f;
   int mi = 0x7fffffff;
-  for (int i = lane; i < n_slots; i += 64) conf_merge(p[3 * i], __float_as_int(p[3 * i + 2]), p[3 * i + 1], m, mi, sum);
+  for (int i = tid; i < n_slots; i += 256 * U) {
+    float om[U], os[U];
+    int oi[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float *q = p + (size_t)3 * min(i + 256 * u, n_slots - 1);
+      om[u] = q[0]; os[u] = q[1]; oi[u] = __float_as_int(q[2]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i + 256 * u < n_slots) conf_merge(om[u], oi[u], os[u], m, mi, sum);
+  }
   for (int o = 32; o > 0; o >>= 1) {
     const float om = __shfl_xor(m, o), os = __shfl_xor(sum, o);
     const int oi = __shfl_xor(mi, o);
     conf_merge(om, oi, os, m, mi, sum);
   }
-  if (lane == 0) {
+  if (lane == 0) { sm[wave] = m; ss[wave] = sum; si[wave] = mi; }
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < 4; ++w) conf_merge(sm[w], si[w], ss[w], m, mi, sum);
     conf[r] = 1.0f / sum;
     argmax[r] = mi;
   }
 }
 
 void confidence_from_partials(hipStream_t s, const float *part, int n_slots, Rows rows, float *conf, int32_t *argmax) {
-  if (rows.cap > 0) k_confidence_slots<<<(rows.cap + 3) / 4, 256, 0, s>>>(part, n_slots, rows, conf, argmax);
+  if (rows.cap > 0) k_confidence_slots<<<rows.cap, 256, 0, s>>>(part, n_slots, rows, conf, argmax);
 }
 
 void confidence(hipStream_t s, const float *logits, int vocab, Rows rows, float *conf, int32_t *argmax, Scratch scratch) {
@@ -365,7 +414,7 @@ __global__ __launch_bounds__(64) void k_commit(CommitArgs a) {
       float best = -INFINITY;
       int bi = -1;
       for (int l = 0; l < nk; ++l) {
-        float cl = __shfl(c, l);
+        float cl = lane_value(c, l);
         if (((cands >> l) & 1ull) && (bi < 0 || cl > best)) { best = cl; bi = l; }
       }
       pass = 1ull << bi;
@@ -374,7 +423,7 @@ __global__ __launch_bounds__(64) void k_commit(CommitArgs a) {
     if (mine) a.st.tokens[slot * B + p] = tok;
     uint64_t cleared = 0;
     for (int l = 0; l < nk; ++l) {
-      int pl = __shfl(p, l);
+      int pl = __builtin_amdgcn_readlane(p, l);
       if ((pass >> l) & 1ull) cleared |= 1ull << pl;
     }
     masked &= ~cleared;

@@ -53,3 +53,16 @@ def test_projection_tile_heights(batch, block):
     """57 to 512 rows against a vocabulary of 200 column tiles: every tile height of the pipelined projection (64 to 256 rows, by the
     vocabulary's launch) with a remainder in both directions, and K cut in parts (the layers' launches)."""
     compare_steps(small_bf16(batch=batch, block_size=block, keep_ratio=1.0, vocab=51176, mask_token_id=51175, n_layers=2, steps=1), 1, 2e-2, exact=False)
+
+
+@pytest.mark.parametrize("shape", [dict(n_q_heads=17, n_kv_heads=17, batch=3), dict(n_q_heads=40, n_kv_heads=4, batch=2, block_size=64, prefix_hi=70),
+                                   dict(n_q_heads=1, n_kv_heads=1, batch=300, block_size=2, hidden=64, ffn=64, vocab=64, prefill="synthetic")])
+def test_head_sums_and_packing(shape):
+    """Importance summed over more heads than are loaded at a time, and over one; more sequences than the packing kernel has threads."""
+    compare_steps(fi.workload("c1_tiny", **shape), 1, 1e-3, exact=True)
+
+
+@pytest.mark.parametrize("vocab", [40968, 66000, 140001])
+def test_confidence_merge_of_many_slots(vocab):
+    """Fewer than one, more than one and more than two trips of the merge's threads over the projection's column slots."""
+    compare_steps(small_bf16(vocab=vocab, mask_token_id=vocab - 1, batch=5, n_layers=2, steps=1), 1, 2e-2, exact=False)
