@@ -38,7 +38,7 @@ __device__ __forceinline__ void head_sums(const float *e, const float *p, int n_
 
 // ---------------------------------------------------------------------------------------------
 // Bound by latency (one wavefront per sequence, whatever the batch): the loads are batched and lane-to-lane reads are scalar
-// (27 us with one load after the other, 32 heads; the pass of one request, with k_confidence_slots below, 937 -> 884 us).
+// (32 heads: 27 us with one load after the other, now 7.7; the pass of one request, with k_confidence_slots below, 937 -> 884 us).
 __global__ __launch_bounds__(64) void k_select(SelectArgs a) {
   __shared__ float dsh[64];
   const int b = blockIdx.x, j = threadIdx.x, B = a.B;
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(256) void k_confidence_merge(const float *__restric
 // Merge of the per-wavefront triples that the fused vocabulary projection leaves (gemm_conf_partials): one workgroup per row, thread t
 // folds slots t, t + 256, ... in ascending order, then lanes and wavefronts are merged; equal maxima keep the lower column.  Bound by
 // the chain load - exponent - add of a thread: with one wavefront per row it was 37 slots of a vocabulary of 151936 long, each with a
-// load of its own; now it is ten, and the loads of four slots go out together.
+// load of its own (18 us; 14 for 1024 rows of half the slots); now it is ten, and the loads of four slots go out together (5.3 and 7.2).
 __global__ __launch_bounds__(256) void k_confidence_slots(const float *__restrict__ part, int n_slots, Rows rows, float *conf, int32_t *argmax) {
   constexpr int U = 4;
   __shared__ float sm[4], ss[4];
