@@ -1,8 +1,10 @@
 """Sizes at which a launch changes its shape (splits, tiles, variants of a kernel), each against the CPU oracle on the same inputs."""
+import numpy as np
 import pytest
+import torch
 
 import focus_inputs as fi
-from test_gpu_parity import compare_steps, small_bf16
+from test_gpu_parity import DEV, Outs, _pk, compare_steps, relerr, small_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -48,10 +50,60 @@ def test_prefill_of_several_blocks_per_pass_fp32(shape):
     compare_steps(fi.workload("c1_tiny", **shape), 2, 1e-3, exact=True)
 
 
-@pytest.mark.parametrize("batch,block", [(3, 19), (5, 18), (8, 16), (15, 10), (27, 7), (31, 7), (10, 25), (11, 25), (64, 8)])
+def compare_without_logits(wl):
+    """Without a logits output the vocabulary projection reduces its tiles in the epilogue and the triples are merged per row: against the
+    same step with the logits, which compare_steps() holds against the oracle.  Arg-max tokens and commits are the same, confidences
+    differ by the order of the sums of exponentials."""
+    pk, runner = _pk()
+    sess = runner.open_session(wl, DEV)
+    n = wl.batch
+    full = Outs(pk, wl, n)
+    sess.focus.focus_step(n, out=full.struct)
+    with_logits = full.host()
+    sess.focus.focus_prefill_kv(sess.prefix_lens, sess.page_tables, None)          # the same block again
+    lean = {k: torch.zeros_like(full.t[k]) for k in ("tokens", "mask_bits", "keep_bits", "cu_seqlens", "conf", "argmax")}
+    sess.focus.focus_step(n, out=pk.make_step_out(**lean))
+    torch.cuda.synchronize()
+    rows = int(with_logits["cu_seqlens"][n])
+    assert rows > 0
+    for k in ("tokens", "mask_bits", "keep_bits", "cu_seqlens"):
+        assert np.array_equal(lean[k].cpu().numpy(), with_logits[k]), k
+    assert np.array_equal(lean["argmax"].cpu().numpy()[:rows], with_logits["argmax"][:rows])
+    assert relerr(lean["conf"].cpu().numpy()[:rows], with_logits["conf"][:rows]) < 1e-5
+    sess.focus.focus_free()
+
+
+# rows that take tiles of 64, 96, 128, 160, 192, 224 and 256 rows where a launch has 63 column tiles (four tile rows fill the chip and the
+# next lower height would need a fifth), the last tile with rows missing
+TILE_ROWS = [(10, 25), (13, 29), (17, 29), (22, 29), (26, 29), (19, 47), (35, 29)]
+# K = 128 is not cut in parts; neither 16000, 2 x 8128 nor 16100 columns fill their last column tile
+WIDE = dict(n_layers=2, keep_ratio=1.0, prefix_lo=3, prefix_hi=20, hidden=128, n_q_heads=75, n_kv_heads=25, ffn=8128, vocab=16100, mask_token_id=16099, steps=1)
+
+
+@pytest.mark.parametrize("batch,block", TILE_ROWS)
 def test_projection_tile_heights(batch, block):
-    """57 to 512 rows against a vocabulary of 200 column tiles: every tile height of the pipelined projection (64 to 256 rows, by the
-    vocabulary's launch) with a remainder in both directions, and K cut in parts (the layers' launches)."""
+    """Every tile height with a remainder in rows and columns: bf16 store (QKV), SiLU*up (gate/up), fp32 store and confidences (vocabulary)."""
+    wl = small_bf16(batch=batch, block_size=block, **WIDE)
+    compare_steps(wl, 1, 2e-2, exact=False)
+    compare_without_logits(wl)
+
+
+@pytest.mark.parametrize("batch,block", [(17, 59), (25, 61), (33, 61), (41, 61), (50, 61), (58, 61), (66, 61)])
+def test_projection_tile_heights_adding_to_the_residual_stream(batch, block):
+    """The same for the projections that add to the residual stream (O and down): 16 column tiles, the last with columns missing, and 16 tile
+    rows of 64 to 256 rows, the last with rows missing."""
+    wl = small_bf16(batch=batch, block_size=block, **dict(WIDE, hidden=4032, n_q_heads=1, n_kv_heads=1, ffn=128, vocab=300, mask_token_id=299))
+    compare_steps(wl, 1, 2e-2, exact=False)
+
+
+def test_confidence_of_the_lowest_tiles():
+    """185 rows x 20300 tokens: confidences from tiles of 64 rows."""
+    compare_without_logits(small_bf16(batch=5, block_size=37, **dict(WIDE, vocab=20300, mask_token_id=20299)))
+
+
+@pytest.mark.parametrize("batch,block", [(3, 19), (5, 18), (8, 16), (15, 10), (27, 7), (31, 7), (10, 25), (11, 25), (64, 8)])
+def test_projections_of_57_to_512_rows(batch, block):
+    """Few column tiles, so that K is cut in parts (the layers), and 200 of them (the vocabulary)."""
     compare_steps(small_bf16(batch=batch, block_size=block, keep_ratio=1.0, vocab=51176, mask_token_id=51175, n_layers=2, steps=1), 1, 2e-2, exact=False)
 
 
@@ -64,5 +116,7 @@ def test_head_sums_and_packing(shape):
 
 @pytest.mark.parametrize("vocab", [40968, 66000, 140001])
 def test_confidence_merge_of_many_slots(vocab):
-    """Fewer than one, more than one and more than two trips of the merge's threads over the projection's column slots."""
-    compare_steps(small_bf16(vocab=vocab, mask_token_id=vocab - 1, batch=5, n_layers=2, steps=1), 1, 2e-2, exact=False)
+    """644, 1032 and 2188 slots a row: one, two and three trips of 256 threads with four slots each, 40 rows."""
+    wl = small_bf16(vocab=vocab, mask_token_id=vocab - 1, batch=5, n_layers=2, steps=1)
+    compare_steps(wl, 1, 2e-2, exact=False)
+    compare_without_logits(wl)
