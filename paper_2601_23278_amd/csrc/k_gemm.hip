@@ -710,11 +710,16 @@ static bool launch_shape(hipStream_t s, PipeShape p, const void *A, const void *
   return launch_pipe_epi<256>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
 }
 
-// The shape with the least estimated time.  A compute unit spends about 0.62 + 0.0031 BM us on a 64-wide slab of a BM x 256 tile, takes
-// one tile at a time (of height 64 two, each at half the pace), and a launch has about 10 us of its own; K cut into parts costs writing the fp32 partial sums,
-// reading them back and one more launch (about 4.5 TB/s).  Measured with weights that come from HBM: 2048 x 4096 x 12288 in two parts
-// of 256 rows 176 us (230 with one round of 128-row tiles), 1024 rows in four parts 103 (138), 1536 x 6144 x 4096 in tiles of 192 rows 84
-// (128), 768 x 24576 x 4096 in 160 rows 154 (194), 276 rows of it 84 (103).  The estimates are within 10 %.
+// The shape with the least estimated time.  A compute unit spends about 0.62 + 0.0031 BM us (0.9 at height 64) on a 64-wide slab of a
+// BM x 256 tile, takes one tile at a time (of height 64 two, each at half the pace), and a launch has about 10 us of its own; K cut into
+// parts costs writing the fp32 partial sums and reading them back (about 4.5 TB/s), one more launch, and half a microsecond per part.
+// Measured with weights that come from HBM: 2048 x 4096 x 12288 in two parts of 256 rows 184 us (227 in 128-row tiles of eight
+// wavefronts), 1024 rows in four parts 103 (136), 1536 x 6144 x 4096 in tiles of 160 rows 76 (123), 777 x 24576 x 4096 in 160 rows 162
+// (182), 276 rows of it 80 (95).  Over 352 launches of 129 to 8192 rows the shape taken is on average 0.7 % slower than the best one (at
+// most 18 %); of those above 30 us nine in ten are estimated at 0.87 to 1.18 of their time.  The cost per part and height 64 were fitted
+// to whole layers, where the previous launch has read most of the weights ahead: without them launches of 161 to 230 rows of the
+// 4096-wide layers were 2 to 5 % slower than 128-row tiles of eight wavefronts (200 rows 211 us a layer, 201 with those, now 201), with a
+// full microsecond per part those of 129 to 1100 rows of 1024-wide layers up to 7 %.
 // (Shapes are chosen for the expected row count; the grids cover rows.cap.)
 static PipeShape pipe_shape(int N, int K, Rows rows, int epi, size_t scratch_bytes) {
   static const int heights[] = {256, 224, 192, 160, 128, 96, 64};
@@ -725,7 +730,7 @@ static PipeShape pipe_shape(int N, int K, Rows rows, int epi, size_t scratch_byt
   double best_us = 1e30;
   auto consider = [&](PipeShape p, long tiles, double slab_us) {
     const double us = 10 + (double)((tiles * p.splits + 255) / 256) * (nk / p.splits) * slab_us +
-                      (p.splits > 1 ? 3 + (p.splits * (double)est * N * 4e-6 + out_mb) / 4.5 : 0);
+                      (p.splits > 1 ? 3 + 0.5 * p.splits + (p.splits * (double)est * N * 4e-6 + out_mb) / 4.5 : 0);
     if (us < best_us) { best_us = us; best = p; }
   };
   for (int bm : heights) {
@@ -733,7 +738,7 @@ static PipeShape pipe_shape(int N, int K, Rows rows, int epi, size_t scratch_byt
     for (int splits = 1; splits <= 16; splits *= 2) {
       // an even number of slabs per part, at least four; sums in 16-byte pieces
       if (splits > 1 && (nk % (splits * 2) || nk / splits < 4 || N % 8 || (size_t)splits * rows.cap * N * 4 > scratch_bytes)) break;
-      consider(PipeShape{bm, 256, splits}, tiles, 0.62 + 0.0031 * bm);
+      consider(PipeShape{bm, 256, splits}, tiles, 0.62 + 0.0031 * bm + (bm == 64 ? 0.08 : 0));
     }
   }
   if (N % 192 == 0 && (epi == EPI_STORE || epi == EPI_ADD_F32 || epi == EPI_STORE_F32))
