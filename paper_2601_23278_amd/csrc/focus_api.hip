@@ -43,8 +43,7 @@ struct Plan {
 // A prefill pass runs many blocks of the prompts at once, as virtual sequences with a slot state of their own (PrefillPass).
 struct PrefillPass {
   Plan plan;           // the base plan with the layers' buffers replaced
-  size_t off_len, off_table, off_tokens, off_mask, off_keep;
-  int blocks;          // blocks it has room for
+  size_t off_len, off_table_row, off_tokens, off_mask;
 };
 constexpr int kPrefillRows = 8192;   // rows of a pass: the projections gain nothing from more
 
@@ -71,20 +70,25 @@ template <typename Take> void plan_moe(Plan &p, const focus_config &c, size_t ro
   }
 }
 
-// Lays out a prefill pass of `blocks` blocks from p.off_resid on; returns its end.  gate_up: the unfused feed-forward needs its buffer.
-size_t lay_prefill(const focus_config &c, const Plan &base, size_t blocks, bool gate_up, PrefillPass *pp) {
+// Lays out a prefill pass of `blocks` blocks; false: they do not fit.  As many blocks as there are slots have the rows of a step and take
+// its buffers (their own state goes where a step keeps its selection), so a pass never has to be smaller than one block of every
+// sequence.  More are laid out anew over everything from the residual stream to the logits.  gate_up: the unfused feed-forward needs its buffer.
+bool lay_prefill(const focus_config &c, const Plan &base, size_t blocks, bool gate_up, PrefillPass *pp) {
+  if (blocks <= (size_t)c.max_batch) {
+    *pp = PrefillPass{base, base.off_K, base.off_n_keep, base.off_argmax, base.off_vis};
+    return true;
+  }
   size_t at = base.off_resid;
   auto take = [&](size_t bytes) { size_t o = at; at += (bytes + 255) & ~(size_t)255; return o; };
   const size_t B = c.block_size, rows = blocks * B, es = esize(c.dtype), q_w = (size_t)c.n_q_heads * c.head_dim;
   const size_t ffn_w = c.n_experts > 0 ? (size_t)std::max(c.ffn, c.shared_ffn) : (size_t)c.ffn;
   Plan &p = pp->plan;
   p = base;
-  pp->blocks = (int)blocks;
   pp->off_len = take(blocks * 4);
-  pp->off_table = take(blocks * base.table_stride * 4);
+  pp->off_table_row = take(blocks * 4);
   pp->off_tokens = take(rows * 4);
   pp->off_mask = take(blocks * 8);
-  pp->off_keep = take(blocks * 8);
+  p.off_keep = take(blocks * 8);
   p.off_cu = take((blocks + 1) * 4);
   p.off_row_map = take(rows * 4);
   p.off_total = take(4);
@@ -96,7 +100,7 @@ size_t lay_prefill(const focus_config &c, const Plan &base, size_t blocks, bool 
   p.off_gate_up = gate_up ? take(rows * 2 * ffn_w * es) : at;
   p.off_act = take(rows * ffn_w * es);
   plan_moe(p, c, rows, take);
-  return at;
+  return at <= base.off_partial;
 }
 
 Plan make_plan(const focus_config &c) {
@@ -129,8 +133,6 @@ Plan make_plan(const focus_config &c) {
   p.off_act = take(rows * ffn_w * es);
   p.off_logits = take(rows * (size_t)c.vocab * 4);
   // a prefill pass uses everything from off_resid up to here, ten times the rows of a step for the usual vocabularies
-  PrefillPass one;
-  at = std::max(at, lay_prefill(c, p, 1, true, &one));
   p.off_partial = take(2 * nb * c.n_q_heads * B * 4);
   p.off_delta = take(rows * 4);
   p.off_K = take(nb * 4);
@@ -146,9 +148,9 @@ Plan make_plan(const focus_config &c) {
   p.off_conf = take(rows * 4);
   p.off_argmax = take(rows * 4);
   p.off_prompt = take(nb * (size_t)c.max_prefix_len * 4);
-  // upload of an admission (page tables and four numbers per sequence): where the prompts go afterwards, if it fits
-  const size_t admit_bytes = nb * ((size_t)p.table_stride + 4) * 4;
-  p.off_admit = admit_bytes <= nb * (size_t)c.max_prefix_len * 4 ? p.off_prompt : take(admit_bytes);
+  // upload of an admission (page tables and four numbers per sequence): over the buffers of the layers and the prompts, which come after
+  // it.  It fits: table_stride + 4 <= max_prefix_len + B + 4, and a sequence has 8 B numbers of the residual stream at least
+  p.off_admit = p.off_resid;
   p.off_prompt_off = take(nb * 4);
   p.off_prompt_len = take(nb * 4);
   p.off_slot_list = take(nb * 4);
@@ -704,15 +706,16 @@ int focus_prefill_kv(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int3
     int room = 1, over = std::min(n_blocks, std::max(1, kPrefillRows / B)) + 1;      // `room` blocks fit, `over` blocks need not be tried
     while (over - room > 1) {
       const int mid = (room + over) / 2;
-      (lay_prefill(g, pl, mid, gate_up, &pp) <= pl.off_partial ? room : over) = mid;
+      (lay_prefill(g, pl, mid, gate_up, &pp) ? room : over) = mid;
     }
     const int n_passes = (n_blocks + room - 1) / room, per_pass = (n_blocks + n_passes - 1) / n_passes;
     lay_prefill(g, pl, per_pass, gate_up, &pp);
     const Plan &lp = pp.plan;
     fk::SlotState vst{};
-    vst.prefix_len = ctx->at<int32_t>(pp.off_len); vst.page_table = ctx->at<int32_t>(pp.off_table); vst.table_stride = pl.table_stride;
+    int32_t *table_row = ctx->at<int32_t>(pp.off_table_row);
+    vst.prefix_len = ctx->at<int32_t>(pp.off_len); vst.page_table = st.page_table; vst.table_stride = pl.table_stride; vst.table_row = table_row;
     vst.tokens = ctx->at<int32_t>(pp.off_tokens); vst.mask_bits = ctx->at<uint64_t>(pp.off_mask); vst.max_batch = per_pass;
-    uint64_t *keep = ctx->at<uint64_t>(pp.off_keep);
+    uint64_t *keep = ctx->at<uint64_t>(lp.off_keep);
     int32_t *cu = ctx->at<int32_t>(lp.off_cu), *row_map = ctx->at<int32_t>(lp.off_row_map), *total = ctx->at<int32_t>(lp.off_total);
     int32_t *order = ctx->at<int32_t>(lp.off_order);
     float *resid = ctx->at<float>(lp.off_resid_p);
@@ -726,7 +729,7 @@ int focus_prefill_kv(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int3
         start += B;
       }
       RowSet rs{{rows, total}, {row_map, nullptr, B}, nv, cu, B, order, &lp, vst};
-      fk::prefill_blocks(s, v0, nv, n_seq, B, g.page_size, d_slots, ctx->slots(), ctx->at<int32_t>(pl.off_prompt), d_off, d_len, vst, keep);
+      fk::prefill_blocks(s, v0, nv, n_seq, B, d_slots, st, ctx->at<int32_t>(pl.off_prompt), d_off, d_len, vst, table_row, keep);
       fk::scan_compact(s, nv, B, keep, cu, row_map, total);
       fk::length_order(s, nv, nullptr, vst, order);
       fk::embed(s, g.dtype, ctx->embed, g.hidden, rs.rows, rs.ri, vst, g.mask_token_id, resid);

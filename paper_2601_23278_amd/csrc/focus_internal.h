@@ -37,7 +37,11 @@ struct SlotState {
   int32_t *page_count;    // pages each slot's table really holds
   int32_t max_prefix_len;
   uint64_t *cached_bits;  // positions whose K/V is frozen in every layer (delayed intra-block cache, Sec. 4.3)
+  const int32_t *table_row = nullptr;   // row of page_table that a slot uses; null: its own (prefill: the blocks of a prompt share one)
 };
+__device__ __forceinline__ const int32_t *pages_of(const SlotState &st, int slot) {
+  return st.page_table + (size_t)(st.table_row ? st.table_row[slot] : slot) * st.table_stride;
+}
 
 // Slot of batch entry b.  A caller-supplied slot list lives in device memory and cannot be checked on the
 // host, so it is clamped into range here: a bad entry aliases another slot instead of leaving the workspace.
@@ -238,9 +242,9 @@ struct CommitArgs {
 };
 void commit(hipStream_t s, const CommitArgs &a);
 // Prefill helper: blocks v0 .. v0 + nv - 1 of the prompts (cut into blocks of B tokens and counted through, prompt after prompt) as nv
-// virtual sequences: prefix_len = the block's first token, its tokens unmasked, the page table of its prompt's slot.
-void prefill_blocks(hipStream_t s, int v0, int nv, int n_seq, int B, int page_size, const int32_t *seq_slot, SlotState st, const int32_t *prompt,
-                    const int32_t *prompt_offset, const int32_t *prompt_len, SlotState vst, uint64_t *keep_bits);
+// virtual sequences: prefix_len = the block's first token, its tokens unmasked, the page table of its prompt's slot (table_row, written here).
+void prefill_blocks(hipStream_t s, int v0, int nv, int n_seq, int B, const int32_t *seq_slot, SlotState st, const int32_t *prompt,
+                    const int32_t *prompt_offset, const int32_t *prompt_len, SlotState vst, int32_t *table_row, uint64_t *keep_bits);
 // Spreads the upload of an admission ([n] slots, [n] prefix lengths, [n] prompt offsets, [n] page counts, [n, table_stride] page
 // tables) into the slots and into the three lists; reset: also starts the block of every sequence (reset_block_state()).
 void admit(hipStream_t s, int n_seq, int B, const int32_t *up, int32_t *slot_list, int32_t *prompt_len, int32_t *prompt_off, SlotState st,

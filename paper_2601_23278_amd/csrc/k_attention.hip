@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256) void k_attn_row(const T *__restrict__ q, int q
   const int slot = slot_of(ri.seq_slot, b, st);
   const int L = st.prefix_len[slot], total = L + ri.B;
   const uint64_t vis = vis_by_b ? vis_by_b[b] : ~0ull;
-  const int32_t *pt = st.page_table + (size_t)slot * st.table_stride;
+  const int32_t *pt = pages_of(st, slot);
   const float scale = 1.0f / sqrtf((float)D);
   const int tl = lane & (TT - 1), d0 = (lane >> 4) * DQ;
 
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
   const int t0 = split * a.chunk;
   const int t1 = split == nsplit - 1 ? total : t0 + a.chunk;
   const uint64_t vis = a.vis_by_b ? a.vis_by_b[b] : ~0ull;
-  const int32_t *pt = a.st.page_table + (size_t)slot * a.st.table_stride;
+  const int32_t *pt = pages_of(a.st, slot);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, col = lane & 31;
   // fused importance: only the workgroup of the last K/V range of the sequence (it is the one that ends with the block's tokens)
   const bool do_imp = IMP && a.imp_partial != nullptr && split == nsplit - 1;
@@ -612,7 +612,7 @@ struct ImpArgs {
 template <typename T>
 __device__ __forceinline__ const T *block_key_row(const ImpArgs &a, int slot, int hk, int j) {
   const int P = a.kv.page_size, pos = a.st.prefix_len[slot] + j;
-  const int page = a.st.page_table[(size_t)slot * a.st.table_stride + pos / P];
+  const int page = pages_of(a.st, slot)[pos / P];
   return (const T *)a.kv.base + (size_t)page * 2 * a.Hkv * P * a.D + ((size_t)hk * P + pos % P) * a.D;
 }
 

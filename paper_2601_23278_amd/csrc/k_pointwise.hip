@@ -130,7 +130,7 @@ __global__ __launch_bounds__(256) void k_rope_kv_write(T *qkv, int Hq, Rows rows
   int rm = ri.row_map[r], b = rm / ri.B, p = rm % ri.B;
   int slot = slot_of(ri.seq_slot, b, st);
   int pos = st.prefix_len[slot] + p;
-  int page = st.page_table[(size_t)slot * st.table_stride + pos / P], off = pos % P;
+  int page = pages_of(st, slot)[pos / P], off = pos % P;
   T *row = qkv + (size_t)r * (Hq + 2 * Hkv) * D;
   T *cache = (T *)kv.base + (size_t)page * 2 * Hkv * P * D;
   const float2 *cs = rope + (size_t)pos * half;
@@ -164,7 +164,7 @@ __device__ __forceinline__ void rope_kv_write_row(int r, bf16_t *qkv, int Hq, Ro
   const int rm = ri.row_map[r], b = rm / ri.B, p = rm % ri.B;
   const int slot = slot_of(ri.seq_slot, b, st);
   const int pos = st.prefix_len[slot] + p;
-  const int page = st.page_table[(size_t)slot * st.table_stride + pos / P], off = pos % P;
+  const int page = pages_of(st, slot)[pos / P], off = pos % P;
   bf16_t *row = qkv + (size_t)r * (Hq + 2 * Hkv) * D;
   bf16_t *cache = (bf16_t *)kv.base + (size_t)page * 2 * Hkv * P * D;
   const float2 *cs = rope + (size_t)pos * half;
@@ -202,7 +202,7 @@ __device__ __forceinline__ void v_write_group(int b, int hk, const bf16_t *qkv, 
   const int D = kv.head_dim, Hkv = kv.n_kv_heads, P = kv.page_size, stride = (Hq + 2 * Hkv) * D;
   const int slot = slot_of(ri.seq_slot, b, st);
   const int L = st.prefix_len[slot];
-  const int32_t *pt = st.page_table + (size_t)slot * st.table_stride;
+  const int32_t *pt = pages_of(st, slot);
   for (int rb = 0; rb < nr; rb += 8) {
     const int r = rb + (threadIdx.x & 7);
     if (r >= nr) continue;
@@ -421,8 +421,9 @@ void finalize_advance(hipStream_t s, int n_seq, int B, const int32_t *seq_slot, 
 }
 
 // Prefill: one wavefront per block finds its prompt by a prefix sum over the prompts' block counts.
-__global__ __launch_bounds__(64) void k_prefill_blocks(int v0, int n_seq, int B, int P, const int32_t *seq_slot, SlotState st, const int32_t *prompt,
-                                                       const int32_t *prompt_offset, const int32_t *prompt_len, SlotState vst, uint64_t *keep_bits) {
+__global__ __launch_bounds__(64) void k_prefill_blocks(int v0, int n_seq, int B, const int32_t *seq_slot, SlotState st, const int32_t *prompt,
+                                                       const int32_t *prompt_offset, const int32_t *prompt_len, SlotState vst, int32_t *table_row,
+                                                       uint64_t *keep_bits) {
   const int v = v0 + blockIdx.x, lane = threadIdx.x;
   int b = -1, c = 0, before = 0;
   for (int i = 0; i < n_seq && b < 0; i += 64) {
@@ -438,23 +439,21 @@ __global__ __launch_bounds__(64) void k_prefill_blocks(int v0, int n_seq, int B,
     before += __shfl(upto, 63);
   }
   if (b < 0) {                            // more blocks than the prompts have
-    if (lane == 0) { keep_bits[blockIdx.x] = 0; vst.prefix_len[blockIdx.x] = 0; }
+    if (lane == 0) { keep_bits[blockIdx.x] = 0; vst.prefix_len[blockIdx.x] = 0; table_row[blockIdx.x] = 0; }
     return;
   }
   const int slot = slot_of(seq_slot, b, st), start = c * B, nr = min(prompt_len[b] - start, B);
   if (lane < nr) vst.tokens[blockIdx.x * B + lane] = prompt[prompt_offset[b] + start + lane];
-  for (int i = lane; i < min((start + B + P - 1) / P, st.table_stride); i += 64)
-    vst.page_table[(size_t)blockIdx.x * vst.table_stride + i] = st.page_table[(size_t)slot * st.table_stride + i];
   if (lane == 0) {
     vst.prefix_len[blockIdx.x] = start;
+    table_row[blockIdx.x] = slot;
     vst.mask_bits[blockIdx.x] = 0;
     keep_bits[blockIdx.x] = nr >= 64 ? ~0ull : ((1ull << nr) - 1);
   }
 }
-void prefill_blocks(hipStream_t s, int v0, int nv, int n_seq, int B, int page_size, const int32_t *seq_slot, SlotState st, const int32_t *prompt,
-                    const int32_t *prompt_offset, const int32_t *prompt_len, SlotState vst, uint64_t *keep_bits) {
-  if (nv > 0)
-    k_prefill_blocks<<<nv, 64, 0, s>>>(v0, n_seq, B, page_size, seq_slot, st, prompt, prompt_offset, prompt_len, vst, keep_bits);
+void prefill_blocks(hipStream_t s, int v0, int nv, int n_seq, int B, const int32_t *seq_slot, SlotState st, const int32_t *prompt,
+                    const int32_t *prompt_offset, const int32_t *prompt_len, SlotState vst, int32_t *table_row, uint64_t *keep_bits) {
+  if (nv > 0) k_prefill_blocks<<<nv, 64, 0, s>>>(v0, n_seq, B, seq_slot, st, prompt, prompt_offset, prompt_len, vst, table_row, keep_bits);
 }
 
 }  // namespace fk

@@ -74,6 +74,18 @@ def test_sizes_and_config_errors_without_gpu():
         assert e.value.code == binding.FOCUS_EINVAL, field
 
 
+@pytest.mark.parametrize("name,over,size", [
+    ("c1_tiny", dict(page_size=1, max_prefix_len=40000, block_size=1, vocab=2, mask_token_id=0), 11610112),
+    ("c1_tiny", dict(vocab=8, mask_token_id=0, max_batch=1, n_experts=64, experts_per_token=8, expert_ffn=512, shared_ffn=64, route_scale=1.0), 766976),
+    ("c3_llada36", dict(max_batch=1, max_prefix_len=0), 228023552)])
+def test_workspace_size_holds_the_buffers_of_a_step_and_no_more(name, over, size):
+    """A prefill and an admission work inside the buffers of a step: a workspace of the size that has always been enough is still enough."""
+    c = config_from_workload(fi.workload(name), 4, 64, 24)
+    for k, v in over.items():
+        setattr(c, k, v)
+    assert pk.focus_workspace_bytes(c) == size
+
+
 def test_selection_and_expert_config_errors_without_gpu():
     moe = dict(n_experts=8, experts_per_token=2, expert_ffn=64, shared_ffn=32, first_moe_layer=1, route_scale=1.0)
 

@@ -32,7 +32,7 @@ def test_fp32_projections_and_attention(shape):
 
 @pytest.mark.parametrize("shape", [dict(page_size=1, prefix_lo=3, prefix_hi=5), dict(page_size=1, prefix_lo=61, prefix_hi=64), dict(prefix_lo=0, prefix_hi=1)])
 def test_admission_upload(shape):
-    """Page tables longer than the prompts (the upload has a region of its own then), shorter, and prompts without tokens."""
+    """Page tables longer than the prompts, shorter, and prompts without tokens."""
     compare_steps(fi.workload("c1_tiny", **shape), 2, 1e-3, exact=True)
 
 
@@ -48,6 +48,28 @@ def test_prefill_of_several_blocks_per_pass(shape):
                                    dict(n_experts=4, experts_per_token=2, expert_ffn=64, shared_ffn=64, first_moe_layer=0, prefix_hi=200)])
 def test_prefill_of_several_blocks_per_pass_fp32(shape):
     compare_steps(fi.workload("c1_tiny", **shape), 2, 1e-3, exact=True)
+
+
+EXPERTS = dict(n_experts=64, experts_per_token=8, expert_ffn=64, shared_ffn=64, first_moe_layer=0)
+
+
+@pytest.mark.parametrize("shape", [dict(EXPERTS, batch=8, vocab=64, prefix_lo=60, prefix_hi=64),           # expert buffers outweigh the logits
+                                   dict(EXPERTS, batch=1, vocab=64, prefix_lo=100, prefix_hi=100),
+                                   dict(batch=5, vocab=64, hidden=64, ffn=64, n_q_heads=1, n_kv_heads=1, page_size=1, block_size=4, prefix_lo=20, prefix_hi=30,
+                                        extra_blocks=1000)])                                              # long page tables
+def test_prefill_passes_hold_a_block_of_every_sequence(shape):
+    """However little room the workspace leaves, the prompts need no more passes than the longest of them has blocks."""
+    from paper_2601_23278_amd.binding import KC_KV_WRITE
+    wl = fi.workload("c1_tiny", **shape)
+    compare_steps(wl, 1, 1e-3, exact=True)
+    pk, runner = _pk()
+    sess = runner.open_session(wl, DEV)
+    lens = wl.prefix_lens()
+    sess.focus.focus_set_timing(True)
+    sess.focus.focus_prefill_kv(lens, sess.page_tables, wl.prompt_tokens(lens))
+    _, launches = sess.focus.focus_get_kernel_time(KC_KV_WRITE)                    # one per layer and pass
+    assert launches <= wl.n_layers * max(-(-x // wl.block_size) for x in lens), launches
+    sess.focus.focus_free()
 
 
 def compare_without_logits(wl):
