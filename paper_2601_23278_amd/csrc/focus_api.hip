@@ -23,7 +23,6 @@ constexpr int kMaxDevices = 64;
 int32_t *g_scratch_ptr[kMaxDevices];
 
 constexpr int kMaxTimed = 4096;
-constexpr int kTargetAttnGroups = 2048;   // (sequence, kv head, split) workgroups the attention launch aims for
 
 struct Plan {
   size_t off_prefix_len, off_page_count, off_page_table, off_tokens, off_mask, off_processed, off_cached, off_token_sum, off_total_steps;
@@ -156,7 +155,7 @@ Plan make_plan(const focus_config &c) {
   p.off_slot_list = take(nb * 4);
   // split-K/V partials of the attention: (row, head, split) entries; the launch policy keeps
   // rows * H_q * splits within  B * group * kTargetAttnGroups + max_rows * H_q
-  p.part_entries = c.dtype == FOCUS_BF16 ? (size_t)B * (c.n_q_heads / c.n_kv_heads) * kTargetAttnGroups + rows * c.n_q_heads : 0;
+  p.part_entries = c.dtype == FOCUS_BF16 ? (size_t)B * (c.n_q_heads / c.n_kv_heads) * fk::kTargetAttnGroups + rows * c.n_q_heads : 0;
   p.off_part_o = take(p.part_entries * c.head_dim * 4);
   p.off_part_ml = take(p.part_entries * 2 * 4);
   p.off_order = take(nb * 4);
@@ -317,10 +316,9 @@ struct RowSet {        // a set of rows the layers run on
   fk::SlotState st = {};
 };
 
-// K/V split size for the attention launch: whole sequences when there are enough (sequence, kv head) groups
-// to fill the chip, otherwise cut into more workgroups (never more than kTargetAttnGroups); always a multiple of the
-// 64-token tile and never so small that the partial buffer would overflow.
-void attention_split(const focus_ctx *c, int n_seq, int rows_cap, int rows_per_seq, int *chunk, int *splits);
+// K/V split size for the attention launch (attention_parts()): always a multiple of the 64-token tile, at least two of them, and never so
+// small that the partial buffer would overflow.
+void attention_split(const focus_ctx *c, int n_seq, int rows_cap, int rows_per_seq, bool importance, int *chunk, int *splits);
 
 // rmsnorm -> QKV projection -> rotary + K/V write, for every row of the set (App. C ordering).
 // kv_only: nothing of the layer but its keys and values is wanted; the query columns are then left as they are.
@@ -360,7 +358,7 @@ void layer_rest(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *res
     a.part_ml = c->plan.part_entries ? c->at<float>(c->plan.off_part_ml) : nullptr;
     a.order = rs.order;
     a.warm = fk::Warm{c->w_o[l], (size_t)g.hidden * q_w * esize(g.dtype)};
-    attention_split(c, rs.n_seq, rs.rows.cap, rs.max_rows_per_seq, &a.chunk, &a.launch_splits);
+    attention_split(c, rs.n_seq, rs.rows.cap, rs.max_rows_per_seq, imp_partial != nullptr, &a.chunk, &a.launch_splits);
     a.max_splits = a.launch_splits;
     a.imp_partial = imp_partial; a.imp_pool_k = g.maxpool_k;
     if (fk::attention(s, a)) imp_partial = nullptr; }
@@ -425,24 +423,10 @@ void moe_ffn(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid,
   { Timed t(c, s, FOCUS_KC_ROUTE); fk::moe_combine(s, a); }
 }
 
-void attention_split(const focus_ctx *c, int n_seq, int rows_cap, int rows_per_seq, int *chunk, int *splits) {
+void attention_split(const focus_ctx *c, int n_seq, int rows_cap, int rows_per_seq, bool importance, int *chunk, int *splits) {
   const focus_config &g = c->cfg;
   const int max_total = c->max_total > 0 ? c->max_total : g.max_prefix_len + g.block_size;
-  const long groups = (long)n_seq * g.n_kv_heads;
-  long want;                                      // splits per sequence
-  if (groups >= 512) {
-    // with several hundred (sequence, kv head) groups a split of fewer than 4096 tokens costs more in start-up and in the merge
-    // than its extra workgroups gain (measured: batch 128 with prefixes up to 2048 runs 8 % faster unsplit, batch 64 with
-    // prefixes up to 32768 15 % slower with two splits than with four)
-    want = groups >= kTargetAttnGroups ? 1 : (kTargetAttnGroups + groups - 1) / groups;
-    want = std::min(want, (long)max_total / 4096);
-  } else {
-    // a handful of sequences needs every workgroup it can get, down to two K/V tiles each, but no more than are resident at once:
-    // a second round and its partial sums gain nothing (two contexts of 31 000 tokens, 32 rows each: 87 us with 864 workgroups of four
-    // wavefronts and 101 with 1888, of which 512 are resident)
-    want = std::min(256 * fk::attention_groups_per_cu(rows_per_seq * (g.n_q_heads / g.n_kv_heads)) / groups, (long)max_total / 128);
-  }
-  want = std::max(1L, want);
+  const long want = fk::attention_parts(max_total, n_seq * g.n_kv_heads, rows_per_seq * (g.n_q_heads / g.n_kv_heads), importance);
   long ch = ((max_total + want - 1) / want + 63) / 64 * 64;
   if (ch < 128) ch = 128;
   // partial buffer: rows * H_q * splits entries

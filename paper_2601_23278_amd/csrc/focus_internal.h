@@ -144,10 +144,40 @@ struct AttnArgs {
   float *imp_partial = nullptr;
   int imp_pool_k = 3;
 };
-// Wavefronts of a workgroup for `pairs` (row, group head) pairs per kv head, and the workgroups of that shape a compute unit holds:
-// five of one wavefront (LDS), else eight wavefronts (registers).
-inline int attention_wavefronts(int pairs) { return pairs <= 32 ? 1 : pairs <= 64 ? 2 : pairs <= 128 ? 4 : 8; }
-inline long attention_groups_per_cu(int pairs) { const int nw = attention_wavefronts(pairs); return nw == 1 ? 5 : 8 / nw; }
+// Wavefronts of a workgroup for `pairs` (row, group head) pairs per kv head, and the workgroups of that shape a compute unit runs at
+// full speed: four of one wavefront, one per SIMD (there is LDS for a fifth without the importance: 1248 workgroups of four sequences
+// took 60 us, 960 of longer splits 55), else eight wavefronts (registers), but with the importance three of two wavefronts (LDS, up to
+// 51 KB; 1248 workgroups of one wavefront with the importance, of which four fit, took 120 us, 960 took 80).
+__host__ __device__ inline int attention_wavefronts(int pairs) { return pairs <= 32 ? 1 : pairs <= 64 ? 2 : pairs <= 128 ? 4 : 8; }
+__host__ __device__ inline int attention_groups_per_cu(int pairs, bool importance) {
+  const int nw = attention_wavefronts(pairs);
+  return nw == 1 ? 4 : nw == 2 && importance ? 3 : 8 / nw;
+}
+// Parts that the longest sequence's K/V (max_total tokens) is cut into, for `groups` (sequence, kv head) pairs.
+constexpr int kTargetAttnGroups = 2048;   // most workgroups that a cut of large batches makes
+__host__ __device__ inline int attention_parts(int max_total, int groups, int pairs, bool importance) {
+  // With several hundred groups a part of fewer than 4096 tokens costs more in start-up and in the merge than its extra workgroups gain
+  // (batch 128 with prefixes up to 2048 runs 8 % faster uncut, batch 64 with prefixes up to 32768 15 % slower with two parts than with four).
+  const int most = groups >= kTargetAttnGroups ? 1 : (kTargetAttnGroups + groups - 1) / groups, longest = max_total / (groups >= 512 ? 4096 : 3072);
+  int want = most < longest ? most : longest;
+  if (groups < 512) {
+    // A handful of sequences needs as many workgroups as run at once, down to two or three tiles of 64 tokens each (the caller rounds
+    // a part up to whole tiles): more of them, and their partial sums, gain nothing (two contexts of 31 000 tokens, 32 rows each: 87 us
+    // with 864 workgroups of four wavefronts and 101 with 1888, of which 512 are resident).  From 96 groups on the chip is busy without
+    // parts, and they have to gain something: a part saves its share of the chain of tiles, 1.35 us each (1.7 and 2.7 with four and
+    // eight wavefronts), while writing, reading and merging the partial sums takes about 3 us and 1 us per 5300 pairs and parts.  Half
+    // as many are taken where that gains more (8 kv heads, blocks of 32 rows, 382 tokens: batch 16 22 us uncut, 30 in two parts; batch 32
+    // 30 and 43; 4 kv heads, 8 rows, up to 600 tokens, batch 24: 27 uncut, 19 in four).
+    const int nw = attention_wavefronts(pairs), tiles = (max_total + 63) / 64;
+    const float tile_us = nw <= 2 ? 1.35f : nw == 4 ? 1.7f : 2.7f, part_us = (float)groups * (float)pairs / 5300.f;
+    int parts = 256 * attention_groups_per_cu(pairs, importance) / groups;
+    if (parts > max_total / 128) parts = max_total / 128;
+    auto gain = [&](int p) { return p > 1 ? (float)(tiles - (tiles + p - 1) / p) * tile_us - 3.f - (float)p * part_us : 0.f; };
+    while (groups >= 96 && parts > 1 && gain(parts) <= gain(parts / 2)) parts /= 2;
+    if (want < parts) want = parts;
+  }
+  return want > 1 ? want : 1;
+}
 // Returns true when imp_partial was asked for and has been written by the attention launch itself.
 bool attention(hipStream_t s, const AttnArgs &a);
 // Eq. 2 per (sequence, query head): partial[b, h, j] = sum over the sequence's query rows (rows cu[b] .. cu[b + 1] of the
