@@ -29,7 +29,7 @@ struct Plan {
   size_t off_rope, off_resid, off_resid_p, off_normed, off_qkv, off_q_p, off_attn, off_gate_up, off_act, off_logits;
   size_t off_partial, off_delta, off_K, off_keep, off_n_keep, off_vis, off_cu, off_cu_full, off_row_map,
       off_row_map_full, off_total, off_total_full, off_conf, off_argmax, off_prompt, off_prompt_off, off_prompt_len,
-      off_slot_list, off_admit, off_part_o, off_part_ml, off_order, off_uncached, off_finalized;
+      off_slot_list, off_admit, off_part_o, off_part_ml, off_order, off_chunk, off_uncached, off_finalized;
   // mixture-of-experts work buffers (zero-sized for a dense model)
   size_t off_moe_logits, off_moe_idx, off_moe_w, off_moe_list, off_moe_count, off_moe_offs, off_moe_tile_e, off_moe_tile_m0,
       off_moe_ntiles, off_moe_pos, off_moe_arow, off_moe_aexp, off_moe_act, off_moe_y;
@@ -91,6 +91,7 @@ bool lay_prefill(const focus_config &c, const Plan &base, size_t blocks, bool ga
   p.off_cu = take((blocks + 1) * 4);
   p.off_row_map = take(rows * 4);
   p.off_total = take(4);
+  p.off_chunk = p.off_total + 64;
   p.off_order = take(blocks * 4);
   p.off_resid_p = take(rows * c.hidden * 4);
   p.off_normed = take(rows * c.hidden * es);
@@ -144,6 +145,7 @@ Plan make_plan(const focus_config &c) {
   p.off_row_map_full = take(rows * 4);
   p.off_total = take(4);
   p.off_total_full = take(4);
+  p.off_chunk = p.off_total + 64;    // two split lengths of the attention, in the 256 bytes of the total
   p.off_conf = take(rows * 4);
   p.off_argmax = take(rows * 4);
   p.off_prompt = take(nb * (size_t)c.max_prefix_len * 4);
@@ -221,7 +223,7 @@ struct focus_ctx {
   std::vector<int> ev_class;
   int n_timed = 0;
   hipStream_t last_stream = nullptr;
-  int max_total = 0;                   // host-side bound of prefix_len + B over the installed sequences
+  int max_total = 0;                   // host-side bound of prefix_len + B over all sequences that were ever installed
   int hint_rows = 0, hint_rows_per_seq = 0;   // focus_set_row_hint: expected packed rows of a step / per sequence (0: none)
 
   template <typename T> T *at(size_t off) const { return (T *)(ws + off); }
@@ -311,14 +313,21 @@ struct RowSet {        // a set of rows the layers run on
   int n_seq;
   const int32_t *cu;   // rows of sequence b: cu[b] .. cu[b + 1]
   int max_rows_per_seq;
-  const int32_t *order;   // attention launch order (longest sequence first) or null
+  const int32_t *order;   // bf16 models: attention launch order (longest sequence first),
+  fk::AttnCut cut;        // shape of the attention launches (attention_cut()) and the split length that length_order() wrote for it
+  const int32_t *chunk;
   const Plan *pl = nullptr;   // the buffers of the layers and the state of the sequences, where they are not the context's own (prefill)
   fk::SlotState st = {};
 };
 
-// K/V split size for the attention launch (attention_parts()): always a multiple of the 64-token tile, at least two of them, and never so
-// small that the partial buffer would overflow.
-void attention_split(const focus_ctx *c, int n_seq, int rows_cap, int rows_per_seq, bool importance, int *chunk, int *splits);
+// Shape of the attention launches for n_seq sequences of at most max_total tokens; the splits' partial sums fit the buffer.
+fk::AttnCut attention_cut(const focus_ctx *c, int max_total, int n_seq, int rows_cap, int rows_per_seq, bool importance = false) {
+  const focus_config &g = c->cfg;
+  fk::AttnCut cut{n_seq * g.n_kv_heads, rows_per_seq * (g.n_q_heads / g.n_kv_heads), importance, 1};
+  const size_t room = c->plan.part_entries / std::max<size_t>(1, (size_t)rows_cap * g.n_q_heads);      // entries: rows * H_q * splits
+  cut.splits = (int)std::max<size_t>(1, std::min<size_t>(room, fk::attention_parts(max_total, cut.groups, cut.pairs, importance)));
+  return cut;
+}
 
 // rmsnorm -> QKV projection -> rotary + K/V write, for every row of the set (App. C ordering).
 // kv_only: nothing of the layer but its keys and values is wanted; the query columns are then left as they are.
@@ -358,8 +367,7 @@ void layer_rest(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *res
     a.part_ml = c->plan.part_entries ? c->at<float>(c->plan.off_part_ml) : nullptr;
     a.order = rs.order;
     a.warm = fk::Warm{c->w_o[l], (size_t)g.hidden * q_w * esize(g.dtype)};
-    attention_split(c, rs.n_seq, rs.rows.cap, rs.max_rows_per_seq, imp_partial != nullptr, &a.chunk, &a.launch_splits);
-    a.max_splits = a.launch_splits;
+    a.launch_splits = rs.cut.splits; a.chunk = rs.chunk;
     a.imp_partial = imp_partial; a.imp_pool_k = g.maxpool_k;
     if (fk::attention(s, a)) imp_partial = nullptr; }
   if (imp_partial) {
@@ -423,16 +431,15 @@ void moe_ffn(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid,
   { Timed t(c, s, FOCUS_KC_ROUTE); fk::moe_combine(s, a); }
 }
 
-void attention_split(const focus_ctx *c, int n_seq, int rows_cap, int rows_per_seq, bool importance, int *chunk, int *splits) {
+// Launch order and splits of the attention over a row set of its own.
+void order_sequences(focus_ctx *c, hipStream_t s, RowSet &rs) {
   const focus_config &g = c->cfg;
-  const int max_total = c->max_total > 0 ? c->max_total : g.max_prefix_len + g.block_size;
-  const long want = fk::attention_parts(max_total, n_seq * g.n_kv_heads, rows_per_seq * (g.n_q_heads / g.n_kv_heads), importance);
-  long ch = ((max_total + want - 1) / want + 63) / 64 * 64;
-  if (ch < 128) ch = 128;
-  // partial buffer: rows * H_q * splits entries
-  while (c->plan.part_entries && ch < max_total && (long)rows_cap * g.n_q_heads * ((max_total + ch - 1) / ch) > (long)c->plan.part_entries) ch *= 2;
-  *chunk = (int)ch;
-  *splits = (int)((max_total + ch - 1) / ch);
+  if (g.dtype != FOCUS_BF16) return;                  // only the matrix-core kernel has either
+  int32_t *order = c->at<int32_t>(c->plan.off_order), *chunk = c->at<int32_t>(c->plan.off_chunk);
+  rs.cut = attention_cut(c, c->max_total > 0 ? c->max_total : g.max_prefix_len + g.block_size, rs.n_seq, rs.rows.cap, rs.max_rows_per_seq);
+  fk::length_order(s, rs.n_seq, g.block_size, rs.ri.seq_slot, c->slots(), order, rs.cut, rs.cut, chunk);
+  rs.order = order;
+  rs.chunk = chunk;
 }
 
 int check_batch(focus_ctx *ctx, int n_seq) {
@@ -701,21 +708,23 @@ int focus_prefill_kv(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int3
     vst.tokens = ctx->at<int32_t>(pp.off_tokens); vst.mask_bits = ctx->at<uint64_t>(pp.off_mask); vst.max_batch = per_pass;
     uint64_t *keep = ctx->at<uint64_t>(lp.off_keep);
     int32_t *cu = ctx->at<int32_t>(lp.off_cu), *row_map = ctx->at<int32_t>(lp.off_row_map), *total = ctx->at<int32_t>(lp.off_total);
-    int32_t *order = ctx->at<int32_t>(lp.off_order);
+    int32_t *order = ctx->at<int32_t>(lp.off_order), *chunk = ctx->at<int32_t>(lp.off_chunk);
     float *resid = ctx->at<float>(lp.off_resid_p);
     int b = 0, start = 0;                                          // next block: sequence and first token
     for (int v0 = 0; v0 < n_blocks; v0 += per_pass) {
       const int nv = std::min(per_pass, n_blocks - v0);
-      int rows = 0;
+      int rows = 0, last_start = 0;
       for (int v = 0; v < nv; ++v) {
         while (start >= lens[b]) { ++b; start = 0; }
         rows += std::min(B, lens[b] - start);
+        last_start = std::max(last_start, start);
         start += B;
       }
-      RowSet rs{{rows, total}, {row_map, nullptr, B}, nv, cu, B, order, &lp, vst};
+      const fk::AttnCut cut = attention_cut(ctx, last_start + B, nv, rows, B);
+      RowSet rs{{rows, total}, {row_map, nullptr, B}, nv, cu, B, order, cut, chunk, &lp, vst};
       fk::prefill_blocks(s, v0, nv, n_seq, B, d_slots, st, ctx->at<int32_t>(pl.off_prompt), d_off, d_len, vst, table_row, keep);
       fk::scan_compact(s, nv, B, keep, cu, row_map, total);
-      fk::length_order(s, nv, nullptr, vst, order);
+      if (g.dtype == FOCUS_BF16) fk::length_order(s, nv, B, nullptr, vst, order, cut, cut, chunk);
       fk::embed(s, g.dtype, ctx->embed, g.hidden, rs.rows, rs.ri, vst, g.mask_token_id, resid);
       for (int l = 0; l < g.n_layers; ++l) {
         const bool last = l == g.n_layers - 1;                     // nothing reads more of the last layer than its keys and values
@@ -765,7 +774,17 @@ int focus_step(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int32_t *s
   const bool dc = g.intra_block_cache != 0;
   uint64_t *uncached = ctx->at<uint64_t>(pl.off_uncached);
   int32_t *cu_full = ctx->at<int32_t>(pl.off_cu_full), *total_full = ctx->at<int32_t>(pl.off_total_full);
-  RowSet full{{T0, dc ? total_full : nullptr}, {ctx->at<int32_t>(pl.off_row_map_full), seq_slot, B}, n_seq, cu_full, B, ctx->at<int32_t>(pl.off_order)};
+  // the packed row count is read from device memory by every kernel; `cap` bounds it (grids, buffers), the caller's hint,
+  // when there is one, shapes tiles, K splits and the attention's wavefront count
+  const int cap = packed_cap(g, n_seq, keep_override != nullptr);
+  const int rows_per_seq_cap = n_seq > 0 ? (cap + n_seq - 1) / n_seq : 0;
+  const int rows_per_seq = ctx->hint_rows_per_seq > 0 ? std::min(ctx->hint_rows_per_seq, rows_per_seq_cap) : rows_per_seq_cap;
+  int32_t *order = ctx->at<int32_t>(pl.off_order), *chunk = ctx->at<int32_t>(pl.off_chunk);
+  const int max_total = ctx->max_total > 0 ? ctx->max_total : g.max_prefix_len + B;
+  RowSet full{{T0, dc ? total_full : nullptr}, {ctx->at<int32_t>(pl.off_row_map_full), seq_slot, B}, n_seq, cu_full, B, order,
+              attention_cut(ctx, max_total, n_seq, T0, B, g.importance_mode == 0), chunk};
+  RowSet packed{{cap, total, ctx->hint_rows}, {row_map, seq_slot, B}, n_seq, cu, rows_per_seq, order,
+                attention_cut(ctx, max_total, n_seq, cap, rows_per_seq), chunk + 1};
   { Timed t(ctx, s, FOCUS_KC_POINTWISE);
     if (dc) {
       fk::uncached_bits(s, n_seq, B, seq_slot, st, uncached);
@@ -773,7 +792,7 @@ int focus_step(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int32_t *s
     } else {
       fk::iota_rows(s, ctx->at<int32_t>(pl.off_row_map_full), cu_full, n_seq, B, total_full);
     }
-    fk::length_order(s, n_seq, seq_slot, st, ctx->at<int32_t>(pl.off_order));
+    if (g.dtype == FOCUS_BF16) fk::length_order(s, n_seq, B, seq_slot, st, order, full.cut, packed.cut, chunk);
     fk::embed(s, g.dtype, ctx->embed, g.hidden, full.rows, full.ri, st, g.mask_token_id, resid); }
   for (int l = 0; l < e; ++l) {
     layer_qkv(ctx, s, l, full, resid);
@@ -804,12 +823,6 @@ int focus_step(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int32_t *s
     fk::select(s, a);
     fk::scan_compact(s, n_seq, B, keep, cu, row_map, total);
   }
-  // the packed row count is read from device memory by every kernel; `cap` bounds it (grids, buffers), the caller's hint,
-  // when there is one, shapes tiles, K splits and the attention's wavefront count
-  const int cap = packed_cap(g, n_seq, keep_override != nullptr);
-  const int rows_per_seq_cap = n_seq > 0 ? (cap + n_seq - 1) / n_seq : 0;
-  const int rows_per_seq = ctx->hint_rows_per_seq > 0 ? std::min(ctx->hint_rows_per_seq, rows_per_seq_cap) : rows_per_seq_cap;
-  RowSet packed{{cap, total, ctx->hint_rows}, {row_map, seq_slot, B}, n_seq, cu, rows_per_seq, ctx->at<int32_t>(pl.off_order)};
   { Timed t(ctx, s, FOCUS_KC_GATHER);
     fk::gather_rows(s, g.dtype, packed.rows, row_map, B, cu_full, dc ? uncached : nullptr, resid, resid_p, g.hidden, qkv, qkv_w, q_p, q_w); }
 
@@ -930,7 +943,8 @@ int focus_run_layers(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int3
   RouteScope route_scope(ctx, nullptr, nullptr);
   fk::scan_compact(s, n_seq, B, keep_bits, cu, row_map, total);
   HIP_TRY(ctx, hipMemcpyAsync(resid_p, hidden, (size_t)cap * g.hidden * 4, hipMemcpyDeviceToDevice, s));
-  RowSet packed{{cap, total}, {row_map, seq_slot, B}, n_seq, cu, B, nullptr};
+  RowSet packed{{cap, total}, {row_map, seq_slot, B}, n_seq, cu, B, nullptr, {}, nullptr};
+  order_sequences(ctx, s, packed);
   for (int l = layer_begin; l < layer_end; ++l) {
     layer_qkv(ctx, s, l, packed, resid_p);
     layer_rest(ctx, s, l, packed, resid_p, ctx->at<char>(pl.off_qkv), qkv_w, vis_bits);
@@ -958,7 +972,8 @@ int focus_finalize_blocks(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const
   fk::finalize_pick(s, n_seq, B, g.page_size, seq_slot, st, keep, done);
   if (finalized) HIP_TRY(ctx, hipMemcpyAsync(finalized, done, (size_t)n_seq * 4, hipMemcpyDeviceToDevice, s));
   fk::scan_compact(s, n_seq, B, keep, cu, row_map, total);
-  RowSet rs{{n_seq * B, total}, {row_map, seq_slot, B}, n_seq, cu, B, nullptr};
+  RowSet rs{{n_seq * B, total}, {row_map, seq_slot, B}, n_seq, cu, B, nullptr, {}, nullptr};
+  order_sequences(ctx, s, rs);
   fk::embed(s, g.dtype, ctx->embed, g.hidden, rs.rows, rs.ri, st, g.mask_token_id, resid);
   for (int l = 0; l < g.n_layers; ++l) {
     const bool last = l == g.n_layers - 1;                                         // of the last layer only the keys and values are wanted

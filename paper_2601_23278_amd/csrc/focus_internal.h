@@ -134,8 +134,9 @@ struct AttnArgs {
   const uint64_t *vis_by_b;      // visible in-block positions per batch entry, null = all
   KvLayer kv;
   void *out;                     // [rows, H_q * D]
-  float *part_o, *part_ml;       // split-K/V partials: [rows, H_q, max_splits, D] and [.., 2]
-  int chunk, max_splits, launch_splits;
+  float *part_o, *part_ml;       // split-K/V partials: [rows, H_q, launch_splits, D] and [.., 2]
+  int launch_splits;             // splits the launch has workgroups (and the partials room) for
+  const int32_t *chunk;          // tokens of a split, written by length_order() from the lengths themselves
   const int32_t *order;          // batch entries sorted by descending prefix length (longest first), or null
   Warm warm;                     // weights of the projection that follows (bf16 kernel only)
   // Eq. 2 fused into this pass (the layer below the eviction layer, whose attention runs over the whole block anyway): when not
@@ -177,6 +178,17 @@ __host__ __device__ inline int attention_parts(int max_total, int groups, int pa
     if (want < parts) want = parts;
   }
   return want > 1 ? want : 1;
+}
+// Shape of the attention launches over one set of rows.  The host only knows a bound of the lengths (they grow on the device, and a slot
+// that this call leaves out may be longer), so it decides how many splits there can be; how long they are follows from the longest
+// sequence of the call, so that neither the time nor the rounding depends on what the context held before.
+struct AttnCut {
+  int groups, pairs, importance, splits;
+};
+__host__ __device__ inline int attention_chunk(int max_total, AttnCut c) {
+  const int parts = attention_parts(max_total, c.groups, c.pairs, c.importance != 0), n = parts < c.splits ? parts : c.splits;
+  const int chunk = ((max_total + n - 1) / n + 63) / 64 * 64;
+  return chunk < 128 ? 128 : chunk;
 }
 // Returns true when imp_partial was asked for and has been written by the attention launch itself.
 bool attention(hipStream_t s, const AttnArgs &a);
@@ -289,7 +301,7 @@ void finalize_advance(hipStream_t s, int n_seq, int B, const int32_t *seq_slot, 
 void fill_u64(hipStream_t s, uint64_t *p, int n, uint64_t v);
 void add_counts(hipStream_t s, int n, const int32_t *counts, int64_t *totals);   // totals[i] += counts[i]
 void iota_rows(hipStream_t s, int32_t *row_map, int32_t *cu, int n_seq, int B, int32_t *total);
-// order[rank] = batch entry, ranked by descending prefix length (ties: lower entry first)
-void length_order(hipStream_t s, int n_seq, const int32_t *seq_slot, SlotState st, int32_t *order);
+// order[rank] = batch entry, ranked by descending prefix length (ties: lower entry first); chunk[i] = attention_chunk() of the longest for cut i
+void length_order(hipStream_t s, int n_seq, int B, const int32_t *seq_slot, SlotState st, int32_t *order, AttnCut cut0, AttnCut cut1, int32_t *chunk);
 
 }  // namespace fk

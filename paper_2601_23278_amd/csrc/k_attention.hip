@@ -144,15 +144,23 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
   if (split >= a.launch_splits) {                        // a workgroup beyond the attention's own: it only warms the next weights
     const int n_warm = (int)gridDim.x - groups * a.launch_splits;
     const unsigned acc = warm_share(a.warm.ptr, a.warm.bytes, (int)blockIdx.x - groups * a.launch_splits, n_warm, NW * 64);
-    if (acc == 0x9e3779b9u && a.chunk < 0) ((unsigned *)a.out)[0] = acc;   // never true: keeps the loads
+    if (acc == 0x9e3779b9u && a.n_seq < 0) ((unsigned *)a.out)[0] = acc;   // never true: keeps the loads
     return;
   }
+  // Without such workgroups the last ones to start pull the next projection's weights into the memory-side cache: those without K/V
+  // of their own at once, the others (the shortest sequences) once through it; any earlier and the K/V stream would push them out again
+  auto warm_next = [&] {
+    const unsigned acc = (int)gridDim.x > groups * a.launch_splits ? 0u : warm_touch(a.warm.ptr, a.warm.bytes, NW * 64);
+    if (acc == 0x9e3779b9u && a.n_seq < 0) ((unsigned *)a.out)[0] = acc;   // never true: keeps the loads
+  };
+  const int chunk = *a.chunk;
   const int bo = group / Hkv, hk = group % Hkv;
   const int b = a.order ? a.order[bo] : bo;
   const int r0 = a.cu[b], nr = a.cu[b + 1] - r0;
   if (nr <= 0) {
     if (BJ > 0 && a.imp_partial && split == 0)           // a sequence without query rows: its importance sums are zero
       for (int i = threadIdx.x; i < g * a.ri.B; i += NW * 64) a.imp_partial[((size_t)b * Hq + hk * g) * a.ri.B + i] = 0.f;
+    warm_next();
     return;
   }
   const int slot = slot_of(a.ri.seq_slot, b, a.st);
@@ -160,10 +168,10 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
   // Splits that have tokens: the sequence's own length decides (it is read here, on the device), bounded by the number of
   // split workgroups this launch has; the last one takes everything that is left.  So a launch whose geometry was fixed when
   // the prefixes were shorter (a captured graph replayed after blocks became prefix) still attends to every token.
-  const int nsplit = min((total + a.chunk - 1) / a.chunk, a.launch_splits);
-  if (split >= nsplit) return;
-  const int t0 = split * a.chunk;
-  const int t1 = split == nsplit - 1 ? total : t0 + a.chunk;
+  const int nsplit = min((total + chunk - 1) / chunk, a.launch_splits);
+  if (split >= nsplit) { warm_next(); return; }
+  const int t0 = split * chunk;
+  const int t1 = split == nsplit - 1 ? total : t0 + chunk;
   const uint64_t vis = a.vis_by_b ? a.vis_by_b[b] : ~0ull;
   const int32_t *pt = pages_of(a.st, slot);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, col = lane & 31;
@@ -348,7 +356,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
         *(bf16x4 *)(orow + 32 * ds + 8 * q4 + 4 * half) = v;
       }
   } else {
-    const size_t pi = ((size_t)qrow * Hq + qhead) * a.max_splits + split;
+    const size_t pi = ((size_t)qrow * Hq + qhead) * a.launch_splits + split;
     float *po = a.part_o + pi * D;
 #pragma unroll
     for (int ds = 0; ds < 4; ++ds)
@@ -445,32 +453,26 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
       }
     }
   }
-  // the last workgroups to start (the shortest sequences), once through their own K/V, pull the next projection's
-  // weights into the memory-side cache: any earlier and the K/V stream would push them out again
-  const int n_attn = groups * a.launch_splits;
-  const unsigned warm_acc = (int)gridDim.x > n_attn ? 0u : warm_touch(a.warm.ptr, a.warm.bytes, NW * 64);
-  if (warm_acc == 0x9e3779b9u && a.chunk < 0) ((unsigned *)a.out)[0] = warm_acc;   // never true: keeps the loads
+  warm_next();
 }
 
 // Merge of the K/V splits of one (row, head): out = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M).  Latency-bound: one thread per
 // output value that walks the splits one after the other waits for memory that often (20 us for the 54 splits of a 31 000-token
 // context).  32 lanes read a split's 128 values as 16-byte pieces; the weights of all splits are computed side by side first.
-//   k_attn_combine_few   up to 16 splits: 32 lanes per (row, head), eight heads per workgroup
+//   k_attn_combine_few   launches of up to 16 splits: 32 lanes per (row, head), eight heads per workgroup
 //   k_attn_combine       more: a workgroup per (row, head), its eight groups of 32 lanes add every eighth split and the eight sums
-//                        are added in group order
+//                        are added in group order (rows of up to 16 splits as above)
 // Either order is fixed, so the result does not depend on timing.  9 us for 64 rows and 31 splits, 6.5 us for 16 rows and 70.
 __device__ __forceinline__ int combine_splits(const AttnArgs &a, int r) {     // as in k_attn_mfma; 0: no such row
   const int M = a.rows.count ? min(*a.rows.count, a.rows.cap) : a.rows.cap;
   if (r >= M) return 0;
   const int slot = slot_of(a.ri.seq_slot, a.ri.row_map[r] / a.ri.B, a.st);
-  return min((a.st.prefix_len[slot] + a.ri.B + a.chunk - 1) / a.chunk, a.max_splits);
+  const int chunk = *a.chunk;
+  return min((a.st.prefix_len[slot] + a.ri.B + chunk - 1) / chunk, a.launch_splits);
 }
 constexpr int kCombineFew = 16;
-__global__ __launch_bounds__(256) void k_attn_combine_few(AttnArgs a) {
-  const int r = blockIdx.x, hq = blockIdx.y * 8 + (threadIdx.x >> 5), col = threadIdx.x & 31;
-  const int nsplit = combine_splits(a, r);
-  if (nsplit <= 1 || hq >= a.n_q_heads) return;
-  const size_t pi = ((size_t)r * a.n_q_heads + hq) * a.max_splits;
+__device__ __forceinline__ void combine_few(const AttnArgs &a, int r, int hq, int nsplit, int col) {   // by 32 lanes
+  const size_t pi = ((size_t)r * a.n_q_heads + hq) * a.launch_splits;
   const float2 ml = col < nsplit ? *(const float2 *)(a.part_ml + (pi + col) * 2) : make_float2(-INFINITY, 0.f);
   float mm = ml.x;
   for (int o = 16; o > 0; o >>= 1) mm = fmaxf(mm, __shfl_xor(mm, o));
@@ -478,23 +480,35 @@ __global__ __launch_bounds__(256) void k_attn_combine_few(AttnArgs a) {
   float den = ml.y * w;
   for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o);
   float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 4
-  for (int s = 0; s < nsplit; ++s) {
-    const float4 v = *(const float4 *)(a.part_o + (pi + s) * 128 + col * 4);
-    const float ws = __shfl(w, s, 32);
-    num.x += v.x * ws; num.y += v.y * ws; num.z += v.z * ws; num.w += v.w * ws;
+  for (int s0 = 0; s0 < nsplit; s0 += 4) {
+    float4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = *(const float4 *)(a.part_o + (pi + min(s0 + i, nsplit - 1)) * 128 + col * 4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float ws = s0 + i < nsplit ? __shfl(w, s0 + i, 32) : 0.f;
+      if (s0 + i < nsplit) { num.x += v[i].x * ws; num.y += v[i].y * ws; num.z += v[i].z * ws; num.w += v[i].w * ws; }
+    }
   }
   const float inv = den > 0.f ? 1.0f / den : 0.f;
   bf16x4 o4;
   o4[0] = (bf16_t)(num.x * inv); o4[1] = (bf16_t)(num.y * inv); o4[2] = (bf16_t)(num.z * inv); o4[3] = (bf16_t)(num.w * inv);
   *(bf16x4 *)((bf16_t *)a.out + ((size_t)r * a.n_q_heads + hq) * 128 + col * 4) = o4;
 }
+__global__ __launch_bounds__(256) void k_attn_combine_few(AttnArgs a) {
+  const int r = blockIdx.x, hq = blockIdx.y * 8 + (threadIdx.x >> 5);
+  const int nsplit = combine_splits(a, r);
+  if (nsplit > 1 && hq < a.n_q_heads) combine_few(a, r, hq, nsplit, threadIdx.x & 31);
+}
 __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
   __shared__ float wsh[256], osh[8][128], red[8];
   const int r = blockIdx.x, hq = blockIdx.y, tid = threadIdx.x, grp = tid >> 5, col = tid & 31;
   const int nsplit = combine_splits(a, r);
-  if (nsplit <= 1) return;
-  const size_t pi = ((size_t)r * a.n_q_heads + hq) * a.max_splits;
+  if (nsplit <= kCombineFew) {       // the order of the sums is the sequence's, whichever of the two the launch has
+    if (nsplit > 1 && __builtin_amdgcn_readfirstlane(tid >> 6) == 0) combine_few(a, r, hq, nsplit, col);   // both halves alike
+    return;
+  }
+  const size_t pi = ((size_t)r * a.n_q_heads + hq) * a.launch_splits;
   float mm = -INFINITY;
   for (int s = tid; s < nsplit; s += 256) mm = fmaxf(mm, a.part_ml[(pi + s) * 2]);
   for (int o = 32; o > 0; o >>= 1) mm = fmaxf(mm, __shfl_xor(mm, o));

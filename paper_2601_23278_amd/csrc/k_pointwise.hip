@@ -330,19 +330,21 @@ void iota_rows(hipStream_t s, int32_t *row_map, int32_t *cu, int n_seq, int B, i
 
 // Longest-first launch order for the attention workgroups: with a handful of workgroups per CU and an 8x
 // spread of prefix lengths, starting the long sequences first keeps the tail of the launch short.
-__global__ __launch_bounds__(256) void k_length_order(int n_seq, const int32_t *seq_slot, SlotState st, int32_t *order) {
+__global__ __launch_bounds__(256) void k_length_order(int n_seq, int B, const int32_t *seq_slot, SlotState st, int32_t *order, AttnCut cut0, AttnCut cut1,
+                                                      int32_t *chunk) {
   const int b = blockIdx.x * 256 + threadIdx.x;
-  if (b >= n_seq) return;
-  const int len = st.prefix_len[slot_of(seq_slot, b, st)];
-  int rank = 0;
+  const int len = st.prefix_len[slot_of(seq_slot, min(b, n_seq - 1), st)];
+  int rank = 0, longest = 0;
   for (int o = 0; o < n_seq; ++o) {
     const int lo = st.prefix_len[slot_of(seq_slot, o, st)];
     rank += (lo > len || (lo == len && o < b)) ? 1 : 0;
+    longest = max(longest, lo);
   }
-  order[rank] = b;
+  if (b < n_seq) order[rank] = b;
+  if (b < 2) chunk[b] = attention_chunk(longest + B, b == 0 ? cut0 : cut1);
 }
-void length_order(hipStream_t s, int n_seq, const int32_t *seq_slot, SlotState st, int32_t *order) {
-  if (n_seq > 0) k_length_order<<<(n_seq + 255) / 256, 256, 0, s>>>(n_seq, seq_slot, st, order);
+void length_order(hipStream_t s, int n_seq, int B, const int32_t *seq_slot, SlotState st, int32_t *order, AttnCut cut0, AttnCut cut1, int32_t *chunk) {
+  if (n_seq > 0) k_length_order<<<(n_seq + 255) / 256, 256, 0, s>>>(n_seq, B, seq_slot, st, order, cut0, cut1, chunk);
 }
 
 // New block: every position masked, nothing processed; statistics kept or cleared.

@@ -18,6 +18,35 @@ def test_attention_context_splits_and_their_merge(prefix, batch, block):
     lengths = dict(prefix_lo=prefix, prefix_hi=prefix, prefix_dist="fixed") if batch == 1 else dict(prefix_lo=5, prefix_hi=prefix)
     compare_steps(small_bf16(batch=batch, n_q_heads=4, n_kv_heads=1, n_layers=3, block_size=block, steps=1, **lengths), 1, 2e-2, exact=False)
 
+@pytest.mark.parametrize("block,prefix", [(32, 1100), (16, 1000)])
+def test_a_step_does_not_depend_on_what_the_context_held_before(block, prefix):
+    """Bitwise: one request in a fresh context; after a long request was in another slot; after many attempts to finalise its block, which
+    raise the bound of the lengths that the host keeps; and by a slot list in device memory."""
+    pk, runner = _pk()
+    wl = small_bf16(batch=2, n_q_heads=4, n_kv_heads=1, block_size=block, prefix_lo=prefix, prefix_hi=prefix, prefix_dist="fixed", steps=1, extra_blocks=7000 // block)
+    sess = runner.open_session(wl, DEV)
+    f, tables = sess.focus, sess.page_tables
+    outs = Outs(pk, wl, 1)
+
+    def first_step(slot=None):
+        f.focus_prefill_kv([prefix], [tables[0]])
+        for t in outs.t.values():
+            t.zero_()
+        f.focus_step(1, seq_slot=slot, out=outs.struct)
+        return outs.host()
+    fresh = first_step()
+    long = prefix + 7000 // block * block
+    f.focus_prefill_kv([long], [tables[1]], seq_slot=[1])
+    after_a_long_one = first_step()
+    for _ in range(40):
+        f.focus_finalize_blocks(1)
+    after_finalising = first_step()
+    by_slot_list = first_step(torch.zeros(1, dtype=torch.int32, device=DEV))
+    for other in (after_a_long_one, after_finalising, by_slot_list):
+        for k in fresh:
+            assert np.array_equal(fresh[k], other[k]), k
+    f.focus_free()
+
 
 @pytest.mark.parametrize("shape", [dict(hidden=264, ffn=40, vocab=1003, batch=3, block_size=5),            # remainders of the 16-wide tiles
                                    dict(hidden=1032, ffn=520, vocab=515, batch=1, block_size=17),          # eight wavefronts, K not a multiple of 16
