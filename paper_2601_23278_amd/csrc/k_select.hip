@@ -212,6 +212,9 @@ __device__ __forceinline__ void conf_push(float v, int i, float &m, int &mi, flo
   if (v > m) { s = s * __expf(m - v) + 1.0f; m = v; mi = i; }
   else s += v == -INFINITY ? 0.f : __expf(v - m);     // (a row that starts with -inf: exp(-inf + inf) is not a number)
 }
+// A row without a number above -infinity has no maximum: token 0, so that what is committed always lies in the vocabulary.
+constexpr int kNoToken = 0x7fffffff;
+__device__ __forceinline__ int token_of(int mi) { return mi == kNoToken ? 0 : mi; }
 __device__ __forceinline__ void conf_merge(float om, int oi, float os, float &m, int &mi, float &s) {
   const float big = fmaxf(m, om);
   const float a = m == big ? 1.0f : __expf(m - big), b = om == big ? 1.0f : __expf(om - big);
@@ -229,7 +232,7 @@ __global__ __launch_bounds__(256) void k_confidence(const float *__restrict__ lo
   const float *x = logits + (size_t)r * vocab;
   const int nv = ((size_t)x & 15) == 0 ? vocab / 4 : 0;       // 16-byte pieces when the row is aligned
   float m = -INFINITY, sum = 0.f;
-  int mi = 0x7fffffff;
+  int mi = kNoToken;
   for (int i = threadIdx.x; i < nv; i += 256) {
     const float4 v = ((const float4 *)x)[i];
     conf_push(v.x, 4 * i, m, mi, sum);
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(256) void k_confidence(const float *__restrict__ lo
     m = smax[0]; mi = sidx[0]; sum = ssum[0];
     for (int i = 1; i < 4; ++i) conf_merge(smax[i], sidx[i], ssum[i], m, mi, sum);
     conf[r] = 1.0f / sum;
-    argmax[r] = mi;
+    argmax[r] = token_of(mi);
   }
 }
 
@@ -269,7 +272,7 @@ __global__ __launch_bounds__(256) void k_confidence_part(const float *__restrict
   const float *x = logits + (size_t)r * vocab;
   const bool vec = (((size_t)x) & 15) == 0;
   float m = -INFINITY;
-  int mi = 0x7fffffff;
+  int mi = kNoToken;
   const int nv = vec ? (c1 - c0) / 4 : 0;
   for (int i = threadIdx.x; i < nv; i += 256) {
     const float4 v = ((const float4 *)(x + c0))[i];
@@ -317,7 +320,7 @@ __global__ __launch_bounds__(256) void k_confidence_merge(const float *__restric
   if (r >= M) return;
   const float *p = part + (size_t)r * kConfParts * 3;
   float m = -INFINITY;
-  int mi = 0x7fffffff;
+  int mi = kNoToken;
   for (int i = 0; i < kConfParts; ++i) {
     const float pm = p[3 * i];
     const int pi = __float_as_int(p[3 * i + 1]);
@@ -326,7 +329,7 @@ __global__ __launch_bounds__(256) void k_confidence_merge(const float *__restric
   float sum = 0.f;
   for (int i = 0; i < kConfParts; ++i) sum += p[3 * i + 2] * __expf(p[3 * i] - m);   // an empty part has sum 0 and maximum -inf: adds 0
   conf[r] = 1.0f / sum;
-  argmax[r] = mi;
+  argmax[r] = token_of(mi);
 }
 
 // Merge of the per-wavefront triples that the fused vocabulary projection leaves (gemm_conf_partials): one workgroup per row, thread t
@@ -342,7 +345,7 @@ __global__ __launch_bounds__(256) void k_confidence_slots(const float *__restric
   if (r >= M) return;
   const float *p = part + (size_t)r * n_slots * 3;
   float m = -INFINITY, sum = 0.f;
-  int mi = 0x7fffffff;
+  int mi = kNoToken;
   for (int i = tid; i < n_slots; i += 256 * U) {
     float om[U], os[U];
     int oi[U];
@@ -365,7 +368,7 @@ __global__ __launch_bounds__(256) void k_confidence_slots(const float *__restric
   if (tid == 0) {
     for (int w = 1; w < 4; ++w) conf_merge(sm[w], si[w], ss[w], m, mi, sum);
     conf[r] = 1.0f / sum;
-    argmax[r] = mi;
+    argmax[r] = token_of(mi);
   }
 }
 

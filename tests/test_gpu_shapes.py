@@ -172,3 +172,20 @@ def test_confidence_merge_of_many_slots(vocab):
     wl = small_bf16(vocab=vocab, mask_token_id=vocab - 1, batch=5, n_layers=2, steps=1)
     compare_steps(wl, 1, 2e-2, exact=False)
     compare_without_logits(wl)
+
+
+@pytest.mark.parametrize("wl,logits", [(fi.workload("c1_tiny"), True), (small_bf16(), True), (small_bf16(batch=33, keep_ratio=1.0), True),
+                                       (small_bf16(vocab=41000, mask_token_id=40999), False)], ids=["fp32", "few rows", "many rows", "without logits"])
+def test_committed_tokens_lie_in_the_vocabulary_whatever_the_logits(wl, logits):
+    """Logits that are all NaN have no maximum: the steps commit tokens of the vocabulary all the same, and the next step embeds them."""
+    pk, runner = _pk()
+    sess = runner.open_session(wl, DEV)
+    sess.weights[1].fill_(float("nan"))                       # lm_head
+    outs = Outs(pk, wl, wl.batch)
+    lean = pk.make_step_out(**{k: v for k, v in outs.t.items() if logits or k != "logits"})
+    for _ in range(2):
+        sess.focus.focus_step(wl.batch, out=lean)
+        g = outs.host()
+        assert np.all((g["tokens"] >= 0) & (g["tokens"] < wl.vocab)) and np.all(g["n_decoded"] > 0)
+        assert np.all(np.isfinite(g["hidden_packed"]))
+    sess.focus.focus_free()
