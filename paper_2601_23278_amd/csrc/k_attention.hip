@@ -95,7 +95,7 @@ __global__ __launch_bounds__(256) void k_attn_row(const T *__restrict__ q, int q
     den += lsh[w] * c;
     num += osh[w][threadIdx.x] * c;
   }
-  out[(size_t)r * Hq * D + (size_t)hq * D + threadIdx.x] = (T)(den > 0.f ? num / den : 0.f);
+  out[(size_t)r * Hq * D + (size_t)hq * D + threadIdx.x] = (T)(den == 0.f ? 0.f : num / den);   // not a number stays that
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -490,7 +490,7 @@ __device__ __forceinline__ void combine_few(const AttnArgs &a, int r, int hq, in
       if (s0 + i < nsplit) { num.x += v[i].x * ws; num.y += v[i].y * ws; num.z += v[i].z * ws; num.w += v[i].w * ws; }
     }
   }
-  const float inv = den > 0.f ? 1.0f / den : 0.f;
+  const float inv = den == 0.f ? 0.f : 1.0f / den;
   bf16x4 o4;
   o4[0] = (bf16_t)(num.x * inv); o4[1] = (bf16_t)(num.y * inv); o4[2] = (bf16_t)(num.z * inv); o4[3] = (bf16_t)(num.w * inv);
   *(bf16x4 *)((bf16_t *)a.out + ((size_t)r * a.n_q_heads + hq) * 128 + col * 4) = o4;
@@ -544,7 +544,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
 #pragma unroll
     for (int i = 1; i < 8; ++i) v += osh[i][tid];
     den = red[4] + red[5] + red[6] + red[7];
-    ((bf16_t *)a.out)[((size_t)r * a.n_q_heads + hq) * 128 + tid] = (bf16_t)(den > 0.f ? v / den : 0.f);
+    ((bf16_t *)a.out)[((size_t)r * a.n_q_heads + hq) * 128 + tid] = (bf16_t)(den == 0.f ? 0.f : v / den);
   }
 }
 

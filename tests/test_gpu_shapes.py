@@ -174,6 +174,24 @@ def test_confidence_merge_of_many_slots(vocab):
     compare_without_logits(wl)
 
 
+@pytest.mark.parametrize("wl", [fi.workload("c1_tiny", n_layers=3), fi.workload("c1_tiny", n_layers=3, head_dim=128), small_bf16(head_dim=64),
+                                small_bf16(page_size=16), small_bf16(batch=33, prefix_lo=70, prefix_hi=90),
+                                small_bf16(prefix_lo=1000, prefix_hi=1100), small_bf16(batch=2, prefix_lo=8000, prefix_hi=8100)],
+                         ids=["fp32", "fp32 128", "bf16 64", "bf16 small pages", "one range", "few ranges", "many ranges"])
+def test_a_key_that_is_not_a_number_shows(wl):
+    """Attention over a prefix with a NaN key gives NaN to that sequence's rows (never a number that hides it), and to no others."""
+    pk, runner = _pk()
+    sess = runner.open_session(wl, DEV)
+    sess.kv_pool[wl.n_layers - 1, sess.page_tables[0][0], 0, :, 0, :] = float("nan")      # first token of sequence 0 in the last layer
+    outs = Outs(pk, wl, wl.batch)
+    sess.focus.focus_step(wl.batch, out=outs.struct)
+    g = outs.host()
+    cu = g["cu_seqlens"]
+    assert cu[1] > 0 and np.all(np.isnan(g["hidden_packed"][:cu[1]]))
+    assert np.all(np.isfinite(g["hidden_packed"][cu[1]:cu[-1]]))
+    sess.focus.focus_free()
+
+
 @pytest.mark.parametrize("wl,logits", [(fi.workload("c1_tiny"), True), (small_bf16(), True), (small_bf16(batch=33, keep_ratio=1.0), True),
                                        (small_bf16(vocab=41000, mask_token_id=40999), False)], ids=["fp32", "few rows", "many rows", "without logits"])
 def test_committed_tokens_lie_in_the_vocabulary_whatever_the_logits(wl, logits):
