@@ -13,16 +13,18 @@ template <typename T> __device__ __forceinline__ float to_f(T v) { return (float
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------------------------
-// fp32 models and the fallback path: one workgroup of four wavefronts per (row, query head), exact to fp32 rounding.  A wavefront takes
-// every fourth tile of 16 tokens with an online softmax of its own; the four are merged in wavefront order.  The launch is bound by the
-// chain of dependent loads and reductions (one wavefront that walked the tokens one by one took 17 to 37 us for 64 to 96 of them), so a
-// tile reads everything side by side: lane l computes a quarter of the product with token l % 16, two exchanges finish it, and then
-// every lane adds its own output columns over the 16 tokens (V is cached transposed).
-template <typename T, int NE>   // NE = D / 64 output columns per lane
-__global__ __launch_bounds__(256) void k_attn_row(const T *__restrict__ q, int q_stride, int Hq, Rows rows, RowIndex ri,
+// fp32 models and the fallback path, exact to fp32 rounding, in several forms (the rule stands at row_form()).
+//
+// One workgroup of four wavefronts per (row, query head).  A wavefront takes every fourth tile of 16 tokens with an online softmax of its
+// own; the four are merged in wavefront order.  The launch is bound by the chain of dependent loads and reductions (one wavefront that
+// walked the tokens one by one took 17 to 37 us for 64 to 96 of them), so a tile reads everything side by side: lane l computes a quarter
+// of the product with token l % 16, two exchanges finish it, and then every lane adds its own output columns over the 16 tokens (V is
+// cached transposed).
+template <typename T, int NE, int NW = 4>   // NE = D / 64 output columns per lane, NW wavefronts
+__global__ __launch_bounds__(NW * 64) void k_attn_row(const T *__restrict__ q, int q_stride, int Hq, Rows rows, RowIndex ri,
                                                   SlotState st, const uint64_t *vis_by_b, KvLayer kv, T *out) {
   constexpr int D = NE * 64, DQ = D / 4, TT = 16;
-  __shared__ float osh[4][D], msh[4], lsh[4];
+  __shared__ float osh[NW][D], msh[NW], lsh[NW];
   const int r = blockIdx.x;
   const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
   if (r >= M) return;
@@ -45,7 +47,7 @@ __global__ __launch_bounds__(256) void k_attn_row(const T *__restrict__ q, int q
   for (int e = 0; e < NE; ++e) o[e] = 0.f;
   float m = -INFINITY, l = 0.f;
   const size_t page_elems = (size_t)2 * Hkv * P * D;
-  for (int t0 = wave * TT; t0 < total; t0 += 4 * TT) {
+  for (int t0 = wave * TT; t0 < total; t0 += NW * TT) {
     const int t = min(t0 + tl, total - 1), page = pt[t / P];
     const T *kp = (const T *)kv.base + (size_t)page * page_elems + ((size_t)hk * P + (t % P)) * D + d0;
     float vv[NE][TT];
@@ -82,20 +84,79 @@ __global__ __launch_bounds__(256) void k_attn_row(const T *__restrict__ q, int q
     }
     m = mn;
   }
+  T *orow = out + (size_t)r * Hq * D + (size_t)hq * D;
+  if (NW == 1) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) orow[lane + 64 * e] = (T)(l == 0.f ? 0.f : o[e] / l);   // not a number stays that
+    return;
+  }
 #pragma unroll
   for (int e = 0; e < NE; ++e) osh[wave][lane + 64 * e] = o[e];
   if (lane == 0) { msh[wave] = m; lsh[wave] = l; }
   __syncthreads();
   if (wave >= NE) return;
-  const float mm = fmaxf(fmaxf(msh[0], msh[1]), fmaxf(msh[2], msh[3]));
+  float mm = msh[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) mm = fmaxf(mm, msh[w]);
   float num = 0.f, den = 0.f;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
+  for (int w = 0; w < NW; ++w) {
     const float c = msh[w] == -INFINITY ? 0.f : __expf(msh[w] - mm);
     den += lsh[w] * c;
     num += osh[w][threadIdx.x] * c;
   }
-  out[(size_t)r * Hq * D + (size_t)hq * D + threadIdx.x] = (T)(den == 0.f ? 0.f : num / den);   // not a number stays that
+  orow[threadIdx.x] = (T)(den == 0.f ? 0.f : num / den);
+}
+
+// One wavefront per (row, query head) that visits the tokens in order, all lanes on one token: for launches with enough rows to hide its
+// chain of loads and reductions, where it reads K in whole lines and holds few registers.
+template <typename T, int NE>
+__global__ __launch_bounds__(64) void k_attn_row_in_order(const T *__restrict__ q, int q_stride, int Hq, Rows rows, RowIndex ri,
+                                                          SlotState st, const uint64_t *vis_by_b, KvLayer kv, T *out) {
+  const int r = blockIdx.x;
+  const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
+  if (r >= M) return;
+  const int hq = blockIdx.y, lane = threadIdx.x;
+  const int D = NE * 64, Hkv = kv.n_kv_heads, P = kv.page_size;
+  const int hk = hq / (Hq / Hkv);
+  const int rm = ri.row_map[r], b = rm / ri.B;
+  const int slot = slot_of(ri.seq_slot, b, st);
+  const int L = st.prefix_len[slot];
+  const uint64_t vis = vis_by_b ? vis_by_b[b] : ~0ull;
+  const int32_t *pt = pages_of(st, slot);
+  const float scale = 1.0f / sqrtf((float)D);
+
+  float qv[NE], o[NE];
+  const T *qr = q + (size_t)r * q_stride + (size_t)hq * D;
+  for (int e = 0; e < NE; ++e) qv[e] = to_f(qr[lane + 64 * e]) * scale, o[e] = 0.f;
+  float m = -INFINITY, l = 0.f;
+  const size_t page_elems = (size_t)2 * Hkv * P * D;
+  for (int t = 0; t < L + ri.B; ++t) {
+    if (t >= L && !((vis >> (t - L)) & 1ull)) continue;
+    const T *kp = (const T *)kv.base + (size_t)pt[t / P] * page_elems + ((size_t)hk * P + (t % P)) * D;
+    const T *vp = (const T *)kv.base + (size_t)pt[t / P] * page_elems + (size_t)(Hkv + hk) * P * D + (t % P);
+    float s = 0.f;
+    for (int e = 0; e < NE; ++e) s += qv[e] * to_f(kp[lane + 64 * e]);
+    for (int x = 32; x > 0; x >>= 1) s += __shfl_xor(s, x);
+    const float mn = fmaxf(m, s), mu = mn == -INFINITY ? 0.f : mn, corr = __expf(m - mu), pr = __expf(s - mu);
+    l = l * corr + pr;
+    for (int e = 0; e < NE; ++e) o[e] = o[e] * corr + pr * to_f(vp[(size_t)(lane + 64 * e) * P]);
+    m = mn;
+  }
+  T *orow = out + (size_t)r * Hq * D + (size_t)hq * D;
+  for (int e = 0; e < NE; ++e) orow[lane + 64 * e] = (T)(l == 0.f ? 0.f : o[e] / l);   // not a number stays that
+}
+// Which form a launch takes.  From 4096 (row, head) pairs on (8192 with 64-wide heads) the wavefronts of the in-order kernel fill the chip,
+// and it is the faster one on pages of fewer than 64 tokens, whose V^T lines it finds in the L1 from one token to the next (4096 pairs x
+// 116 tokens, 128-wide bf16 heads 229 us, 268 with four wavefronts a row; 8192 x 46, 64-wide fp32 heads 110 and 138).  On longer pages each
+// token touches as many lines as the head is wide and pushes the last ones out (16384 pairs x 516 tokens, 128-wide fp32 heads: half
+// the time with four wavefronts a row); there a single round of rows whose heads share K and V is served by one wavefront each, which
+// leaves out the merge (4096 x 1516, groups of four heads: 4.6 ms, 5.4 with four wavefronts, 4.4 in order).
+enum RowForm { ROW_IN_ORDER, ROW_ONE_WAVEFRONT, ROW_FOUR_WAVEFRONTS };
+static RowForm row_form(long pairs, int head_dim, int page_size, int group) {
+  if (pairs < (head_dim == 64 ? 8192 : 4096)) return ROW_FOUR_WAVEFRONTS;
+  if (page_size < 64) return ROW_IN_ORDER;
+  return head_dim == 128 && group > 1 && pairs < 8192 ? ROW_ONE_WAVEFRONT : ROW_FOUR_WAVEFRONTS;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -560,6 +621,18 @@ static bool launch_attn_imp(hipStream_t s, dim3 grid, const AttnArgs &a, int g) 
   return true;
 }
 
+template <typename T> static void launch_rows(hipStream_t s, const AttnArgs &a, int group) {
+  const dim3 grid(a.rows.cap, a.n_q_heads);
+  const RowForm form = row_form((long)a.rows.cap * a.n_q_heads, a.kv.head_dim, a.kv.page_size, group);
+  const bool narrow = a.kv.head_dim == 64;
+  auto run = [&](auto kernel, int threads) {
+    kernel<<<grid, threads, 0, s>>>((const T *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (T *)a.out);
+  };
+  if (form == ROW_IN_ORDER) run(narrow ? k_attn_row_in_order<T, 1> : k_attn_row_in_order<T, 2>, 64);
+  else if (form == ROW_ONE_WAVEFRONT) run(k_attn_row<T, 2, 1>, 64);
+  else run(narrow ? k_attn_row<T, 1> : k_attn_row<T, 2>, 256);
+}
+
 bool attention(hipStream_t s, const AttnArgs &a) {
   if (a.rows.cap <= 0 || a.n_seq <= 0) return false;
   const int g = a.n_q_heads / a.kv.n_kv_heads;
@@ -593,15 +666,8 @@ bool attention(hipStream_t s, const AttnArgs &a) {
     else if (a.launch_splits > 1) k_attn_combine_few<<<dim3(a.rows.cap, (a.n_q_heads + 7) / 8), 256, 0, s>>>(a);
     return fused;
   }
-  dim3 grid(a.rows.cap, a.n_q_heads);
-  const int ne = a.kv.head_dim / 64;
-  if (a.dtype == FOCUS_F32) {
-    if (ne == 1) k_attn_row<float, 1><<<grid, 256, 0, s>>>((const float *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (float *)a.out);
-    else k_attn_row<float, 2><<<grid, 256, 0, s>>>((const float *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (float *)a.out);
-  } else {
-    if (ne == 1) k_attn_row<bf16_t, 1><<<grid, 256, 0, s>>>((const bf16_t *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (bf16_t *)a.out);
-    else k_attn_row<bf16_t, 2><<<grid, 256, 0, s>>>((const bf16_t *)a.q, a.q_stride, a.n_q_heads, a.rows, a.ri, a.st, a.vis_by_b, a.kv, (bf16_t *)a.out);
-  }
+  if (a.dtype == FOCUS_F32) launch_rows<float>(s, a, g);
+  else launch_rows<bf16_t>(s, a, g);
   return false;
 }
 

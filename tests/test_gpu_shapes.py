@@ -60,6 +60,21 @@ def test_fp32_projections_and_attention(shape):
     compare_steps(fi.workload("c1_tiny", **dict(shape, **budget)), 2, 1e-3, exact=True)
 
 
+@pytest.mark.parametrize("shape", [dict(page_size=16, block_size=5), dict(page_size=16, block_size=32), dict(head_dim=64, block_size=32), dict(head_dim=64, page_size=16, block_size=5),
+                                   dict(page_size=16, n_q_heads=16, n_kv_heads=4, batch=8, keep_ratio=1.0, prefill="synthetic"),                    # 4096 (row, head) pairs
+                                   dict(head_dim=64, page_size=32, n_q_heads=32, n_kv_heads=8, batch=8, keep_ratio=1.0, prefill="synthetic")])       # 8192
+def test_bf16_attention_off_the_matrix_cores(shape):
+    """Heads of 64 and pages of other than 64 tokens, with prompts (whose last blocks are ragged), and enough rows for the in-order kernel."""
+    compare_steps(small_bf16(**dict(dict(prefix_lo=1, prefix_hi=150, prefill="prompt", n_layers=2, steps=1), **shape)), 1, 2e-2, exact=False)
+
+
+@pytest.mark.parametrize("shape", [dict(head_dim=128, page_size=16), dict(head_dim=128, page_size=64), dict(head_dim=64, page_size=8, batch=16)])
+def test_fp32_attention_of_many_rows(shape):
+    """4096 to 8192 (row, head) pairs: in order on pages of less than 64 tokens, one wavefront a row on longer ones for groups of heads."""
+    compare_steps(fi.workload("c1_tiny", **dict(dict(n_q_heads=16, n_kv_heads=4, batch=8, block_size=32, budget_mode=1, keep_ratio=1.0, prefix_lo=1,
+                                                     prefix_hi=90, prefill="synthetic"), **shape)), 1, 1e-3, exact=True)
+
+
 @pytest.mark.parametrize("shape", [dict(page_size=1, prefix_lo=3, prefix_hi=5), dict(page_size=1, prefix_lo=61, prefix_hi=64), dict(prefix_lo=0, prefix_hi=1)])
 def test_admission_upload(shape):
     """Page tables longer than the prompts, shorter, and prompts without tokens."""
