@@ -712,7 +712,7 @@ static bool launch_shape(hipStream_t s, PipeShape p, const void *A, const void *
 
 // The shape with the least estimated time.  A compute unit spends about 0.62 + 0.0031 BM us (0.9 at height 64) on a 64-wide slab of a
 // BM x 256 tile, takes one tile at a time (of height 64 two, each at half the pace), and a launch has about 10 us of its own; K cut into
-// parts costs writing the fp32 partial sums and reading them back (about 4.5 TB/s), one more launch, and half a microsecond per part.
+// parts costs writing the fp32 partial sums and reading them back (about 4.7 TB/s), one more launch, and 0.4 us per part.
 // Measured with weights that come from HBM: 2048 x 4096 x 12288 in two parts of 256 rows 184 us (227 in 128-row tiles of eight
 // wavefronts), 1024 rows in four parts 103 (136), 1536 x 6144 x 4096 in tiles of 160 rows 76 (123), 777 x 24576 x 4096 in 160 rows 162
 // (182), 276 rows of it 80 (95).  Over 352 launches of 129 to 8192 rows the shape taken is on average 0.7 % slower than the best one (at
@@ -730,7 +730,7 @@ static PipeShape pipe_shape(int N, int K, Rows rows, int epi, size_t scratch_byt
   double best_us = 1e30;
   auto consider = [&](PipeShape p, long tiles, double slab_us) {
     const double us = 10 + (double)((tiles * p.splits + 255) / 256) * (nk / p.splits) * slab_us +
-                      (p.splits > 1 ? 3 + 0.5 * p.splits + (p.splits * (double)est * N * 4e-6 + out_mb) / 4.5 : 0);
+                      (p.splits > 1 ? 3 + 0.4 * p.splits + (p.splits * (double)est * N * 4e-6 + out_mb) / 4.7 : 0);
     if (us < best_us) { best_us = us; best = p; }
   };
   for (int bm : heights) {
