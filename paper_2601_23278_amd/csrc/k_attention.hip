@@ -208,12 +208,6 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
     if (acc == 0x9e3779b9u && a.n_seq < 0) ((unsigned *)a.out)[0] = acc;   // never true: keeps the loads
     return;
   }
-  // Without such workgroups the last ones to start pull the next projection's weights into the memory-side cache: those without K/V
-  // of their own at once, the others (the shortest sequences) once through it; any earlier and the K/V stream would push them out again
-  auto warm_next = [&] {
-    const unsigned acc = (int)gridDim.x > groups * a.launch_splits ? 0u : warm_touch(a.warm.ptr, a.warm.bytes, NW * 64);
-    if (acc == 0x9e3779b9u && a.n_seq < 0) ((unsigned *)a.out)[0] = acc;   // never true: keeps the loads
-  };
   const int chunk = *a.chunk;
   const int bo = group / Hkv, hk = group % Hkv;
   const int b = a.order ? a.order[bo] : bo;
@@ -221,7 +215,6 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
   if (nr <= 0) {
     if (BJ > 0 && a.imp_partial && split == 0)           // a sequence without query rows: its importance sums are zero
       for (int i = threadIdx.x; i < g * a.ri.B; i += NW * 64) a.imp_partial[((size_t)b * Hq + hk * g) * a.ri.B + i] = 0.f;
-    warm_next();
     return;
   }
   const int slot = slot_of(a.ri.seq_slot, b, a.st);
@@ -230,7 +223,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
   // split workgroups this launch has; the last one takes everything that is left.  So a launch whose geometry was fixed when
   // the prefixes were shorter (a captured graph replayed after blocks became prefix) still attends to every token.
   const int nsplit = min((total + chunk - 1) / chunk, a.launch_splits);
-  if (split >= nsplit) { warm_next(); return; }
+  if (split >= nsplit) return;
   const int t0 = split * chunk;
   const int t1 = split == nsplit - 1 ? total : t0 + chunk;
   const uint64_t vis = a.vis_by_b ? a.vis_by_b[b] : ~0ull;
@@ -514,7 +507,11 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
       }
     }
   }
-  warm_next();
+  // the last workgroups to start (the shortest sequences), once through their own K/V, pull the next projection's
+  // weights into the memory-side cache: any earlier and the K/V stream would push them out again (workgroups without K/V that did it
+  // at once cost 23 contexts of up to 1500 tokens 3 us a launch and gained the projection nothing)
+  const unsigned warm_acc = (int)gridDim.x > groups * a.launch_splits ? 0u : warm_touch(a.warm.ptr, a.warm.bytes, NW * 64);
+  if (warm_acc == 0x9e3779b9u && a.n_seq < 0) ((unsigned *)a.out)[0] = warm_acc;   // never true: keeps the loads
 }
 
 // Merge of the K/V splits of one (row, head): out = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M).  Latency-bound: one thread per
