@@ -149,9 +149,10 @@ Plan make_plan(const focus_config &c) {
   p.off_conf = take(rows * 4);
   p.off_argmax = take(rows * 4);
   p.off_prompt = take(nb * (size_t)c.max_prefix_len * 4);
-  // upload of an admission (page tables and four numbers per sequence): over the buffers of the layers and the prompts, which come after
-  // it.  It fits: table_stride + 4 <= max_prefix_len + B + 4, and a sequence has 8 B numbers of the residual stream at least
-  p.off_admit = p.off_resid;
+  // upload of an admission (page tables and four numbers per sequence): where the prompts go afterwards, if it fits, else over the buffers of
+  // the layers and the prompts.  There it fits: table_stride + 4 <= max_prefix_len + B + 4, and a sequence has 8 B numbers of the residual
+  // stream at least
+  p.off_admit = (size_t)p.table_stride + 4 <= (size_t)c.max_prefix_len ? p.off_prompt : p.off_resid;
   p.off_prompt_off = take(nb * 4);
   p.off_prompt_len = take(nb * 4);
   p.off_slot_list = take(nb * 4);
