@@ -327,6 +327,8 @@ fk::AttnCut attention_cut(const focus_ctx *c, int max_total, int n_seq, int rows
   fk::AttnCut cut{n_seq * g.n_kv_heads, rows_per_seq * (g.n_q_heads / g.n_kv_heads), importance, 1};
   const size_t room = c->plan.part_entries / std::max<size_t>(1, (size_t)rows_cap * g.n_q_heads);      // entries: rows * H_q * splits
   cut.splits = (int)std::max<size_t>(1, std::min<size_t>(room, fk::attention_parts(max_total, cut.groups, cut.pairs, importance)));
+  const int chunk = fk::attention_chunk(max_total, cut);
+  cut.splits = (max_total + chunk - 1) / chunk;      // no workgroups without tokens where max_total is the real length (they cannot warm anything)
   return cut;
 }
 
