@@ -302,21 +302,24 @@ static void launch_mfma(hipStream_t s, const void *A, const void *W, int N, int 
 }
 
 // ---------------------------------------------------------------------------------------------
-// BM x 256 x 64 tiles, four wavefronts, one workgroup per CU (two at BM = 64), K-slabs loaded straight into LDS
+// BM x 256 x 64 tiles, four wavefronts, one workgroup per CU, K-slabs loaded straight into LDS
 // (buffer_load_dwordx4 ... lds: lane l of an instruction fills the 16-byte slot l of a 1 KB block = 8 tile rows, so
 // the bank swizzle is applied by choosing which chunk a lane fetches; rows beyond the matrix fall outside the buffer
-// descriptor and read as zero), two LDS stages, software-pipelined by hand:
+// descriptor and read as zero), software-pipelined by hand:
 //   * the fragments of k-step s + 1 are read from LDS while the MFMAs of step s run (two register sets);
 //   * one barrier per slab, placed before the last k-step: by then every wavefront has read all of the current slab
-//     and the next one has landed, so the loads of the slab after the next start right behind the barrier;
-//   * loads are spread between the MFMAs (a burst of 8 direct-to-LDS loads per wavefront stalls the matrix pipe for
-//     longer than the loads take on their own: measured 37 % of the MFMA rate against 100 % when interleaved);
-//   * the loop handles two slabs per trip, so the stage is a compile-time constant, LDS addresses are loop-invariant
-//     registers plus immediates, and the loads take their slab offset from a scalar register: no vector ALU work
-//     competes with the MFMAs for issue slots.
-// The waits for the loads are explicit: the compiler does not order LDS reads behind direct-to-LDS loads.
-// LDS layout: A stage 0, A stage 1, W stage 0, W stage 1 (so that both stages of an operand are within the 16-bit
-// immediate offset of one base register).
+//     and the next one has landed, so the stage of the current slab can be filled again right behind the barrier;
+//   * three LDS stages of the weights, and of the rows where they fit (up to 160 of them: 156 KB; above two: 160 KB at 256), so that
+//     loads have a whole slab's time more to arrive.  With two stages every height took the same 0.95 us or more for a slab, which
+//     is how long a slab takes to come from memory, whatever there was to multiply: 4096 columns, K = 12288, weights from HBM, 256
+//     tiles of 64 / 96 / 128 / 160 / 192 / 256 rows 188 / 201 / 214 / 225 / 244 / 322 us, now 140 / 158 / 180 / 204 / 235 / 312.  At 192
+//     rows and above it is power that binds (1.6 GHz of 2.4 under real values; the matrix cores busy in 86 % of the cycles of a slab);
+//   * loads are spread evenly between the MFMAs (a burst of 8 direct-to-LDS loads per wavefront stalls the matrix pipe for
+//     longer than the loads take on their own: measured 37 % of the MFMA rate against 100 % when interleaved), and they
+//     take their slab and stage offsets from scalar registers: next to no vector ALU work competes with the MFMAs for issue slots.
+// The waits for the loads are explicit, and so is the barrier: the compiler does not order LDS reads behind direct-to-LDS loads, but it
+// lets a workgroup fence wait for all of them.
+// LDS layout: the stages of the rows, then those of the weights.
 #define FK_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
 // Workgroup barrier that orders LDS traffic only: outstanding global loads (which the kernel waits for by count) are
@@ -338,8 +341,12 @@ template <int CTRL> __device__ __forceinline__ void lane_max_step(float &m, int 
   if (om > m || (om == m && oi < mi)) { m = om; mi = oi; }     // equal maxima: the lower column
 }
 
+constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }   // s_waitcnt vmcnt(n) only
+constexpr int pipe_stages_a(int bm) { return bm <= 160 ? 3 : 2; }
+constexpr int kPipeStagesW = 3;
+
 template <int BM, int EPI, int BN = 256>
-__global__ __launch_bounds__(256, BM <= 64 ? 2 : 1) void k_gemm_pipe(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W, int N, int K,
+__global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W, int N, int K,
                                                       Rows rows, void *out, int ldo, int tiles_m, int tiles_n, const void *warm,
                                                       unsigned warm_bytes, int splits, size_t split_stride) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer-resource builtins exist in the device pass only
@@ -355,10 +362,14 @@ __global__ __launch_bounds__(256, BM <= 64 ? 2 : 1) void k_gemm_pipe(const bf16_
   constexpr int BK = 64, WCOLS = NW / WROWS, WM = BM / WROWS, WN = BN / WCOLS, TM = WM / 32, TN = WN / 32;
   static_assert(WM % 32 == 0 && WN % 32 == 0 && (BM / 8) % NW == 0 && (BN / 8) % NW == 0 && (!SILU_W || TN % 2 == 0), "tile shape");
   constexpr int IA = BM / 8 / NW, IB = BN / 8 / NW, NI = IA + IB;
-  constexpr int ASTAGE = BM * 128, WSTAGE = BN * 128, WBASE = 2 * ASTAGE, NMF = TM * TN;
-  // loads issued in the k-step right behind the barrier; the rest follow in the first k-steps of the next slab
-  constexpr int L0 = NI / 2 < NMF ? NI / 2 : NMF, L1 = NI - L0 < NMF ? NI - L0 : NMF, L2 = NI - L0 - L1;
-  static_assert(L2 <= NMF && TM + TN <= NMF, "one load and one fragment read per MFMA at most");
+  constexpr int SA = pipe_stages_a(BM), SW = kPipeStagesW;
+  constexpr int ASTAGE = BM * 128, WSTAGE = BN * 128, WBASE = SA * ASTAGE, NMF = TM * TN;
+  // Loads of a window (barrier to barrier, four k-steps): the rows first, then the weights, a quarter in each k-step
+  constexpr int L0 = (NI + 3) / 4, L1 = (NI - L0 + 2) / 3, L2 = (NI - L0 - L1 + 1) / 2, L3 = NI - L0 - L1 - L2;
+  static_assert(L0 <= NMF && TM + TN <= NMF, "one load and one fragment read per MFMA at most");
+  // Loads that may still be on their way at the barrier.  The slab that comes next was asked for in the window before this one, but with
+  // two stages its rows in this window: so those behind them, all of this window's or the weights, and the warm-up loads that end windows.
+  constexpr int FLY = SA > 2 ? NI + 2 : IB + 1;
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_pipe[];
   unsigned char *const lds = lds_pipe;
   const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
@@ -414,14 +425,15 @@ __global__ __launch_bounds__(256, BM <= 64 ? 2 : 1) void k_gemm_pipe(const bf16_
   const int warm_stride = warm_hits ? max(1, nk / (int)warm_hits) : 1;
   unsigned warm_off = (unsigned)max(warm_rank, 0) * (warm_hits * HIT), warm_left = warm_hits;
   int warm_next = 0;
-  unsigned warm_sink = 0, warm_prev = 0;
+  unsigned warm_sink = 0, warm_even = 0, warm_odd = 0;
   const unsigned warm_lane = lane * 128 + wave * 8192;
-  auto gl = [&](int i, int soff, int buf) {   // load instruction i (A: 0 .. IA-1, W: IA .. NI-1) of the slab at byte offset soff
+  // load instruction i (A: 0 .. IA-1, W: IA .. NI-1) of the slabs at byte offsets so_a, so_w into the stages at byte offsets st_a, st_w
+  auto gl = [&](int i, unsigned so_a, int st_a, unsigned so_w, int st_w) {
     if (i < IA)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, FK_LDS_PTR(lds + buf * ASTAGE + (wave * IA + (i < IA ? i : 0)) * 1024), 16, voa[i < IA ? i : 0], soff, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, FK_LDS_PTR(lds + st_a + (wave * IA + (i < IA ? i : 0)) * 1024), 16, voa[i < IA ? i : 0], so_a, 0, 0);
     else
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, FK_LDS_PTR(lds + WBASE + buf * WSTAGE + (wave * IB + (i < IA ? 0 : i - IA)) * 1024), 16,
-                                               vob[i < IA ? 0 : i - IA], soff, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, FK_LDS_PTR(lds + WBASE + st_w + (wave * IB + (i < IA ? 0 : i - IA)) * 1024), 16,
+                                               vob[i < IA ? 0 : i - IA], so_w, 0, 0);
   };
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -440,61 +452,75 @@ __global__ __launch_bounds__(256, BM <= 64 ? 2 : 1) void k_gemm_pipe(const bf16_
     pb[ks] = lds + WBASE + (wn + frow) * 128 + (((2 * ks + fch) ^ sw) << 4);
   }
   bf16x8 fa[2][TM], fb[2][TN];
-  auto rd = [&](int s, int ks, int buf, int slot) {   // s-th fragment read of a k-step, in the order the MFMAs need them
+  auto rd = [&](int s, int ks, int st_a, int st_w, int slot) {   // s-th fragment read of a k-step, in the order the MFMAs need them
     const int f = s == 0 ? TM : (s == 1 ? 0 : (s <= TN ? TM + s - 1 : s - TN));   // W0, A0, W1 .. W(TN-1), A1 .. A(TM-1)
-    if (f < TM) fa[slot][f < TM ? f : 0] = *(const bf16x8 *)(pa[ks] + buf * ASTAGE + (f < TM ? f : 0) * 4096);
-    else fb[slot][f < TM ? 0 : f - TM] = *(const bf16x8 *)(pb[ks] + buf * WSTAGE + (f < TM ? 0 : f - TM) * 4096);
+    if (f < TM) fa[slot][f < TM ? f : 0] = *(const bf16x8 *)(pa[ks] + st_a + (f < TM ? f : 0) * 4096);
+    else fb[slot][f < TM ? 0 : f - TM] = *(const bf16x8 *)(pb[ks] + st_w + (f < TM ? 0 : f - TM) * 4096);
   };
-  const int last = (nk - 1) * (BK * 2);
+  auto slab_off = [&](int kt) { return kt < nk ? (unsigned)kt * (BK * 2) : 0x80000000u; };   // beyond the last slab nothing is moved
+  // before the loop: the rows of slabs 0 .. SA - 2 and the weights of slabs 0 .. SW - 2, a warm-up load that moves nothing as at the end of
+  // every window (the waits count it), and the first k-step's share of the window that ends at the first barrier
 #pragma unroll
-  for (int i = 0; i < NI; ++i) gl(i, 0, 0);
+  for (int q = 0; q < SW - 1; ++q)
 #pragma unroll
-  for (int i = 0; i < L0; ++i) gl(i, min(BK * 2, last), 1);
-  __builtin_amdgcn_s_waitcnt(0x0F70 | L0);   // vmcnt(L0): slab 0 has landed
-  lds_barrier(); 
+    for (int i = 0; i < NI; ++i)
+      if (i >= IA || q < SA - 1) gl(i, slab_off(q), q * ASTAGE, slab_off(q), q * WSTAGE);
+  __builtin_amdgcn_sched_barrier(0);
+  warm_odd = __builtin_amdgcn_raw_buffer_load_b32(rs_p, warm_lane, 0x80000000u, 0);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int s = 0; s < TM + TN; ++s) rd(s, 0, 0, 0);
+  for (int i = 0; i < L0; ++i) gl(i, slab_off(SA - 1), (SA - 1) * ASTAGE, slab_off(SW - 1), (SW - 1) * WSTAGE);
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(L0 + 1 + (SW - 2) * IB + (SA - 2) * IA));   // slab 0 has landed
+  asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+  for (int s = 0; s < TM + TN; ++s) rd(s, 0, 0, 0, 0);
 
   // one k-step: the MFMAs on register set `cur`; behind MFMA s, fragment read s of the next k-step, and (when nl > 0)
   // a load on every NMF / nl-th MFMA
-#define FK_STEP(cur, next_ks, next_buf, nl, lfirst, lsoff, lbuf)                                        \
+#define FK_STEP(cur, next_ks, ra, rw, nl, lfirst, so_a, st_a, so_w, st_w)                               \
   {                                                                                                     \
     _Pragma("unroll") for (int s = 0; s < NMF; ++s) {                                                   \
       const int i = s / TN, j = s % TN;                                                                 \
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][i], fb[cur][j], acc[i][j], 0, 0, 0);  \
-      if (s < TM + TN) rd(s, next_ks, next_buf, (cur) ^ 1);                                             \
+      if (s < TM + TN) rd(s, next_ks, ra, rw, (cur) ^ 1);                                               \
       if ((nl) > 0 && s % (NMF / ((nl) > 0 ? (nl) : 1)) == NMF / ((nl) > 0 ? (nl) : 1) - 1 && s / (NMF / ((nl) > 0 ? (nl) : 1)) < (nl)) \
-        gl((lfirst) + s / (NMF / ((nl) > 0 ? (nl) : 1)), lsoff, lbuf);                                  \
+        gl((lfirst) + s / (NMF / ((nl) > 0 ? (nl) : 1)), so_a, st_a, so_w, st_w);                       \
       __builtin_amdgcn_sched_barrier(0);                                                                \
     }                                                                                                   \
   }
-  // one slab held in stage `buf`; beyond the last slab the loads repeat it (into a stage nobody reads any more), so the
-  // loop body has no branches
-#define FK_SLAB(buf, kt)                                                                                \
+  int ra = 0, rw = 0;                                       // stages of the slab that is multiplied
+  int la = (SA - 1) * ASTAGE, lw = (SW - 1) * WSTAGE;       // stages that are filled: the ones the slab before it has left
+  // one slab; its warm-up load goes out behind all loads of its window, and what it returned is folded two windows later
+#define FK_SLAB(kt, warm_value)                                                                         \
   {                                                                                                     \
-    const int so1 = min(((kt) + 1) * (BK * 2), last), so2 = min(((kt) + 2) * (BK * 2), last);           \
-    FK_STEP(0, 1, buf, L1, L0, so1, (buf) ^ 1)                                                          \
-    FK_STEP(1, 2, buf, L2, L0 + L1, so1, (buf) ^ 1)                                                     \
+    unsigned so_a = slab_off((kt) + SA - 1), so_w = slab_off((kt) + SW - 1);                            \
+    FK_STEP(0, 1, ra, rw, L1, L0, so_a, la, so_w, lw)                                                   \
+    FK_STEP(1, 2, ra, rw, L2, L0 + L1, so_a, la, so_w, lw)                                              \
+    FK_STEP(0, 3, ra, rw, L3, L0 + L1 + L2, so_a, la, so_w, lw)                                         \
     {                                                                                                   \
       const bool hit = (kt) == warm_next && warm_left > 0;                                              \
       const unsigned so = hit ? warm_off : 0x80000000u;                                                 \
-      warm_sink ^= warm_prev;                                                                           \
-      warm_prev = __builtin_amdgcn_raw_buffer_load_b32(rs_p, warm_lane, so, 0);                         \
+      warm_sink ^= warm_value;                                                                          \
+      warm_value = __builtin_amdgcn_raw_buffer_load_b32(rs_p, warm_lane, so, 0);                        \
       warm_off += hit ? HIT : 0u; warm_left -= hit ? 1u : 0u; warm_next += hit ? warm_stride : 0;       \
+      __builtin_amdgcn_sched_barrier(0);                                                                \
     }                                                                                                   \
-    FK_STEP(0, 3, buf, 0, 0, so1, (buf) ^ 1)                                                            \
-    __builtin_amdgcn_s_waitcnt(0x0F71); /* vmcnt(1): all but the warm-up load: this wavefront's part of the next slab has landed */ \
-    lds_barrier();                     /* ... and everyone's; everyone has read all of this slab */    \
-    FK_STEP(1, 0, (buf) ^ 1, L0, 0, so2, buf)                                                           \
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(FLY));   /* this wavefront's part of the next slab has landed */ \
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   /* ... and everyone's; everyone has read all of this slab */ \
+    la = ra; lw = rw;                                                                                   \
+    ra = ra == (SA - 1) * ASTAGE ? 0 : ra + ASTAGE;                                                     \
+    rw = rw == (SW - 1) * WSTAGE ? 0 : rw + WSTAGE;                                                     \
+    so_a = slab_off((kt) + SA); so_w = slab_off((kt) + SW);                                             \
+    FK_STEP(1, 0, ra, rw, L0, 0, so_a, la, so_w, lw)                                                    \
   }
   for (int kt = 0; kt < nk; kt += 2) {
-    FK_SLAB(0, kt)
-    FK_SLAB(1, kt + 1)
+    FK_SLAB(kt, warm_even)
+    FK_SLAB(kt + 1, warm_odd)
   }
 #undef FK_SLAB
 #undef FK_STEP
   __builtin_amdgcn_s_waitcnt(0x0F70);
-  if ((warm_sink ^ warm_prev) == 0x9e3779b9u && warm_bytes == 1) ((unsigned *)out)[0] = warm_sink;   // keeps the warm-up loads alive; never true
+  if ((warm_sink ^ warm_even ^ warm_odd) == 0x9e3779b9u && warm_bytes == 1) ((unsigned *)out)[0] = warm_sink;   // keeps the warm-up loads alive; never true
   // epilogue: accumulator register r of lane l is C[8 * (r / 4) + 4 * (l / 32) + r % 4][l % 32] of its 32x32 tile.
   // A tile that lies inside the matrix takes the path without per-element bounds checks.
   const bool inside = m0 + BM <= M && n0 + (SILU_W ? BN / 2 : BN) <= (SILU_W ? N / 2 : N);
@@ -661,7 +687,7 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float *__restrict__
 template <int BM, int EPI, int BN = 256>
 static bool launch_pipe(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, int K, Rows rows, void *out, int ldo, Warm warm, int splits = 1,
                         size_t split_stride = 0) {
-  constexpr int kLds = 2 * (BM + BN) * 128;
+  constexpr int kLds = (pipe_stages_a(BM) * BM + kPipeStagesW * BN) * 128;
   constexpr bool SILU_W = EPI == EPI_SILU_MUL || EPI == EPI_PARTIAL_SILU;
   static bool ready = false;             // the dynamic LDS size has to be allowed once per kernel
   if (!ready) {
@@ -710,16 +736,13 @@ static bool launch_shape(hipStream_t s, PipeShape p, const void *A, const void *
   return launch_pipe_epi<256>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
 }
 
-// The shape with the least estimated time.  A compute unit spends about 0.62 + 0.0031 BM us (0.9 at height 64) on a 64-wide slab of a
-// BM x 256 tile, takes one tile at a time (of height 64 two, each at half the pace), and a launch has about 10 us of its own; K cut into
-// parts costs writing the fp32 partial sums and reading them back (about 4.7 TB/s), one more launch, and 0.4 us per part.
-// Measured with weights that come from HBM: 2048 x 4096 x 12288 in two parts of 256 rows 184 us (227 in 128-row tiles of eight
-// wavefronts), 1024 rows in four parts 103 (136), 1536 x 6144 x 4096 in tiles of 160 rows 76 (123), 777 x 24576 x 4096 in 160 rows 162
-// (182), 276 rows of it 80 (95).  Over 352 launches of 129 to 8192 rows the shape taken is on average 0.7 % slower than the best one (at
-// most 18 %); of those above 30 us nine in ten are estimated at 0.87 to 1.18 of their time.  The cost per part and height 64 were fitted
-// to whole layers, where the previous launch has read most of the weights ahead: without them launches of 161 to 230 rows of the
-// 4096-wide layers were 2 to 5 % slower than 128-row tiles of eight wavefronts (200 rows 211 us a layer, 201 with those, now 201), with a
-// full microsecond per part those of 129 to 1100 rows of 1024-wide layers up to 7 %.
+// The shape with the least estimated time.  A compute unit takes one tile at a time and spends about 0.30 + 0.0046 BM us (0.08 more at
+// height 64) on a 64-wide slab of a BM x 256 tile, up to a fifth less when part of the chip is idle; K cut into parts costs writing the
+// fp32 partial sums and reading them back (about 4.4 TB/s), 2.5 us for one more launch, and a microsecond per part.
+// Fitted to 207 problems of 129 to 8192 rows (2048 to 24576 columns, K 2048 to 12288, eight weight matrices in turn): the shape taken is
+// on average 0.2 % slower than the best one (at most 10 %).  A few of them, us: 2048 x 4096 x 12288 171 in 128 rows, 1310 rows of it 121
+// in two parts of 192, 1024 rows 97 in four of 256, 1536 x 6144 x 4096 68 in 160 rows, 777 x 24576 x 4096 138 in 160, 2048 x 2048 x 2048
+// 23 in 64.
 // (Shapes are chosen for the expected row count; the grids cover rows.cap.)
 static PipeShape pipe_shape(int N, int K, Rows rows, int epi, size_t scratch_bytes) {
   static const int heights[] = {256, 224, 192, 160, 128, 96, 64};
@@ -729,8 +752,9 @@ static PipeShape pipe_shape(int N, int K, Rows rows, int epi, size_t scratch_byt
   PipeShape best{256, 256, 1};
   double best_us = 1e30;
   auto consider = [&](PipeShape p, long tiles, double slab_us) {
-    const double us = 10 + (double)((tiles * p.splits + 255) / 256) * (nk / p.splits) * slab_us +
-                      (p.splits > 1 ? 3 + 0.4 * p.splits + (p.splits * (double)est * N * 4e-6 + out_mb) / 4.7 : 0);
+    const double rounds = (double)((tiles * p.splits + 255) / 256), idle = 1 - std::min(1.0, tiles * p.splits / 256.0);
+    const double us = 4 + rounds * (nk / p.splits) * slab_us * (1 - 0.185 * idle) +
+                      (p.splits > 1 ? 2.5 + p.splits + (p.splits * (double)est * N * 4e-6 + out_mb) / 4.4 : 0);
     if (us < best_us) { best_us = us; best = p; }
   };
   for (int bm : heights) {
@@ -738,11 +762,11 @@ static PipeShape pipe_shape(int N, int K, Rows rows, int epi, size_t scratch_byt
     for (int splits = 1; splits <= 16; splits *= 2) {
       // an even number of slabs per part, at least four; sums in 16-byte pieces
       if (splits > 1 && (nk % (splits * 2) || nk / splits < 4 || N % 8 || (size_t)splits * rows.cap * N * 4 > scratch_bytes)) break;
-      consider(PipeShape{bm, 256, splits}, tiles, 0.62 + 0.0031 * bm + (bm == 64 ? 0.08 : 0));
+      consider(PipeShape{bm, 256, splits}, tiles, 0.30 + 0.0046 * bm + (bm == 64 ? 0.075 : 0));
     }
   }
   if (N % 192 == 0 && (epi == EPI_STORE || epi == EPI_ADD_F32 || epi == EPI_STORE_F32))
-    consider(PipeShape{256, 192, 1}, (long)((est + 255) / 256) * (N / 192), 1.25);
+    consider(PipeShape{256, 192, 1}, (long)((est + 255) / 256) * (N / 192), 1.115);
   return best;
 }
 
