@@ -35,6 +35,7 @@ struct Plan {
       off_moe_ntiles, off_moe_pos, off_moe_arow, off_moe_aexp, off_moe_act, off_moe_y;
   size_t off_n_dec;                  // tokens decoded by the current step of focus_run_steps
   size_t off_splitk, splitk_bytes;   // fp32 partial sums of K-split projections (launches with few rows)
+  size_t off_layer_scratch, layer_scratch_bytes;   // what the layers leave free of the region that ends with the logits: for the same purpose
   size_t bytes, part_entries;
   int table_stride, max_rows, max_pos, moe_tile_slots;
 };
@@ -100,6 +101,8 @@ bool lay_prefill(const focus_config &c, const Plan &base, size_t blocks, bool ga
   p.off_gate_up = gate_up ? take(rows * 2 * ffn_w * es) : at;
   p.off_act = take(rows * ffn_w * es);
   plan_moe(p, c, rows, take);
+  p.off_layer_scratch = at;
+  p.layer_scratch_bytes = at < base.off_partial ? base.off_partial - at : 0;
   return at <= base.off_partial;
 }
 
@@ -132,6 +135,8 @@ Plan make_plan(const focus_config &c) {
   p.off_gate_up = take(rows * 2 * ffn_w * es);
   p.off_act = take(rows * ffn_w * es);
   p.off_logits = take(rows * (size_t)c.vocab * 4);
+  p.off_layer_scratch = p.off_logits;
+  p.layer_scratch_bytes = at - p.off_logits;
   // a prefill pass uses everything from off_resid up to here, ten times the rows of a step for the usual vocabularies
   p.off_partial = take(2 * nb * c.n_q_heads * B * 4);
   p.off_delta = take(rows * 4);
@@ -235,6 +240,13 @@ struct focus_ctx {
             at<int32_t>(plan.off_page_count), cfg.max_prefix_len, at<uint64_t>(plan.off_cached)};
   }
   fk::Scratch scratch() const { return fk::Scratch{plan.splitk_bytes ? ws + plan.off_splitk : nullptr, plan.splitk_bytes}; }
+  // The layers' projections write their K parts where the logits of the step will be, if there is more room: the parts of a launch are as
+  // far apart as the bound of its row count, and where only the device knows the count that bound is a whole block per sequence
+  // (1310 of 3072 rows, 4096 columns, K = 12288: 187 us uncut, 121 in two parts, which 64 MB do not hold).
+  fk::Scratch layer_scratch(const Plan &p) const {
+    const fk::Scratch s = scratch();
+    return s.bytes && p.layer_scratch_bytes > s.bytes ? fk::Scratch{ws + p.off_layer_scratch, p.layer_scratch_bytes} : s;
+  }
   bool moe_layer(int l) const { return cfg.n_experts > 0 && l >= cfg.first_moe_layer; }
   fk::KvLayer kv_layer(int l) const {
     size_t layer_bytes = (size_t)cfg.n_pages * 2 * cfg.n_kv_heads * cfg.page_size * cfg.head_dim * esize(cfg.dtype);
@@ -343,7 +355,7 @@ void layer_qkv(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, const float
   { Timed t(c, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid, c->attn_norm[l], normed, g.hidden, g.rms_eps, rs.rows); }
   { Timed t(c, s, FOCUS_KC_GEMM);
     fk::gemm(s, g.dtype, normed, (const char *)c->w_qkv[l] + skip * es * g.hidden, qkv_w - skip, g.hidden, rs.rows, fk::EPI_STORE, qkv + skip * es, qkv_w,
-             fk::Warm(), c->scratch()); }
+             fk::Warm(), c->layer_scratch(pl)); }
   { Timed t(c, s, FOCUS_KC_KV_WRITE);
     fk::rope_kv_write(s, g.dtype, qkv, g.n_q_heads, rs.rows, rs.ri, rs.pl ? rs.st : c->slots(), c->kv_layer(l), c->at<float2>(pl.off_rope), rs.n_seq, rs.cu); }
 }
@@ -377,7 +389,7 @@ void layer_rest(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *res
     Timed t(c, s, FOCUS_KC_IMPORTANCE);
     fk::importance(s, g.dtype, q, rs.cu, rs.n_seq, g.block_size, g.n_q_heads, g.n_kv_heads, g.head_dim, g.maxpool_k, rs.ri.seq_slot, c->slots(), c->kv_layer(l), imp_partial);
   }
-  { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, attn, c->w_o[l], g.hidden, q_w, rs.rows, fk::EPI_ADD_F32, resid, g.hidden, fk::Warm(), c->scratch()); }
+  { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, attn, c->w_o[l], g.hidden, q_w, rs.rows, fk::EPI_ADD_F32, resid, g.hidden, fk::Warm(), c->layer_scratch(pl)); }
   { Timed t(c, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid, c->mlp_norm[l], normed, g.hidden, g.rms_eps, rs.rows); }
   const size_t qkv_bytes = (size_t)(g.n_q_heads + 2 * g.n_kv_heads) * g.head_dim * g.hidden * esize(g.dtype);
   const fk::Warm next_qkv = l + 1 < g.n_layers ? fk::Warm{c->w_qkv[l + 1], qkv_bytes} : fk::Warm();
@@ -397,12 +409,12 @@ void swiglu_ffn(focus_ctx *c, hipStream_t s, const RowSet &rs, const void *norme
   if (fk::gemm_fuses_silu_mul(g.dtype, normed, w_gate_up, 2 * ffn, g.hidden, rs.rows.cap)) {
     Timed t(c, s, FOCUS_KC_GEMM);
     fk::gemm(s, g.dtype, normed, w_gate_up, 2 * ffn, g.hidden, rs.rows, fk::EPI_SILU_MUL, act, ffn,
-             fk::Warm{w_down, (size_t)g.hidden * ffn * esize(g.dtype)}, c->scratch());
+             fk::Warm{w_down, (size_t)g.hidden * ffn * esize(g.dtype)}, c->layer_scratch(pl));
   } else {
-    { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, normed, w_gate_up, 2 * ffn, g.hidden, rs.rows, fk::EPI_STORE, gate_up, 2 * ffn, fk::Warm(), c->scratch()); }
+    { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, normed, w_gate_up, 2 * ffn, g.hidden, rs.rows, fk::EPI_STORE, gate_up, 2 * ffn, fk::Warm(), c->layer_scratch(pl)); }
     { Timed t(c, s, FOCUS_KC_POINTWISE); fk::silu_mul(s, g.dtype, gate_up, act, ffn, rs.rows); }
   }
-  { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, act, w_down, g.hidden, ffn, rs.rows, fk::EPI_ADD_F32, resid, g.hidden, warm_after, c->scratch()); }
+  { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, act, w_down, g.hidden, ffn, rs.rows, fk::EPI_ADD_F32, resid, g.hidden, warm_after, c->layer_scratch(pl)); }
 }
 
 // Mixture-of-experts feed-forward on normalised rows, added to the residual stream: router logits -> picks and weights ->
@@ -426,7 +438,7 @@ void moe_ffn(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid,
   a.out_experts = c->route_by_row_id && c->out_route_experts ? c->out_route_experts + (size_t)l * plane : nullptr;
   a.out_weights = c->route_by_row_id && c->out_route_weights ? c->out_route_weights + (size_t)l * plane : nullptr;
   { Timed t(c, s, FOCUS_KC_GEMM);
-    fk::gemm(s, g.dtype, normed, c->w_router[l], g.n_experts, g.hidden, rs.rows, fk::EPI_STORE_F32, c->at<float>(pl.off_moe_logits), g.n_experts, fk::Warm(), c->scratch()); }
+    fk::gemm(s, g.dtype, normed, c->w_router[l], g.n_experts, g.hidden, rs.rows, fk::EPI_STORE_F32, c->at<float>(pl.off_moe_logits), g.n_experts, fk::Warm(), c->layer_scratch(pl)); }
   { Timed t(c, s, FOCUS_KC_ROUTE); fk::moe_route(s, a); fk::moe_group(s, a); }
   { Timed t(c, s, FOCUS_KC_EXPERTS); fk::moe_experts(s, a); }
   // the shared expert adds into the residual stream before the routed sum (both orders are the same sum)
