@@ -344,8 +344,11 @@ template <int CTRL> __device__ __forceinline__ void lane_max_step(float &m, int 
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }   // s_waitcnt vmcnt(n) only
 constexpr int pipe_stages_a(int bm) { return bm <= 160 ? 3 : 2; }
 constexpr int kPipeStagesW = 3;
+constexpr int kNonTemporal = 2;      // cache policy of a load (NT bit): what is read once does not push other lines out
 
-template <int BM, int EPI, int BN = 256>
+// ONE: the launch has one row of tiles, so that every weight is read by one workgroup only, past the caches (151936 columns, K = 4096:
+// 8 rows 217 us, 232 with plain loads; 128 rows 233 and 248; with two and more rows of tiles it is the same or slower, 374 -> 382)
+template <int BM, int EPI, int BN = 256, bool ONE = false>
 __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W, int N, int K,
                                                       Rows rows, void *out, int ldo, int tiles_m, int tiles_n, const void *warm,
                                                       unsigned warm_bytes, int splits, size_t split_stride) {
@@ -433,7 +436,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, FK_LDS_PTR(lds + st_a + (wave * IA + (i < IA ? i : 0)) * 1024), 16, voa[i < IA ? i : 0], so_a, 0, 0);
     else
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, FK_LDS_PTR(lds + WBASE + st_w + (wave * IB + (i < IA ? 0 : i - IA)) * 1024), 16,
-                                               vob[i < IA ? 0 : i - IA], so_w, 0, 0);
+                                               vob[i < IA ? 0 : i - IA], so_w, 0, ONE ? kNonTemporal : 0);
   };
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -684,19 +687,21 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float *__restrict__
   }
 }
 
-template <int BM, int EPI, int BN = 256>
+template <int BM, int EPI, int BN = 256, bool ONE = false>
 static bool launch_pipe(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, int K, Rows rows, void *out, int ldo, Warm warm, int splits = 1,
                         size_t split_stride = 0) {
   constexpr int kLds = (pipe_stages_a(BM) * BM + kPipeStagesW * BN) * 128;
   constexpr bool SILU_W = EPI == EPI_SILU_MUL || EPI == EPI_PARTIAL_SILU;
+  if constexpr (!ONE && BM <= 128 && (EPI == EPI_CONF || EPI == EPI_STORE_F32))      // the vocabulary projection of few rows
+    if (rows.expected() <= BM && splits == 1) return launch_pipe<BM, EPI, BN, true>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
   static bool ready = false;             // the dynamic LDS size has to be allowed once per kernel
   if (!ready) {
-    if (hipFuncSetAttribute((const void *)k_gemm_pipe<BM, EPI, BN>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess) return false;
+    if (hipFuncSetAttribute((const void *)k_gemm_pipe<BM, EPI, BN, ONE>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess) return false;
     ready = true;
   }
   const int tiles_m = (rows.cap + BM - 1) / BM, tiles_n = SILU_W ? (N / 2 + BN / 2 - 1) / (BN / 2) : (N + BN - 1) / BN;
   const int grid = ((tiles_m * tiles_n * splits + 7) / 8) * 8;
-  k_gemm_pipe<BM, EPI, BN><<<grid, 256, kLds, s>>>(a, w, N, K, rows, out, ldo, tiles_m, tiles_n, warm.ptr, (unsigned)std::min<size_t>(warm.bytes, 0x7fffffffu),
+  k_gemm_pipe<BM, EPI, BN, ONE><<<grid, 256, kLds, s>>>(a, w, N, K, rows, out, ldo, tiles_m, tiles_n, warm.ptr, (unsigned)std::min<size_t>(warm.bytes, 0x7fffffffu),
                                                    splits, split_stride);
   return true;
 }

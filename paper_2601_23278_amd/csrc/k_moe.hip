@@ -192,6 +192,7 @@ enum { GG_DOWN = 0, GG_GATE_UP = 1, GG_DENSE_PARTIAL = 2, GG_DENSE_PARTIAL_SILU 
 
 #define FK_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }   // s_waitcnt vmcnt(n) only
+constexpr int kNonTemporal = 2;      // cache policy of the weight loads (NT bit): every weight is read once, past the caches
 constexpr int kGroupLds = (2 * kMoeTileRows + 3 * 128) * 128;
 
 template <int MODE>
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(256, 2) void k_group_gemm(GroupGemm g) {
     const unsigned so = kt < nk ? (unsigned)kt * 128u : 0x80000000u;
 #pragma unroll
     for (int q = 0; q < IB; ++q)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, FK_LDS_PTR(lds + WBASE + stage * WSTAGE + (wave * IB + q) * 1024), 16, vob[q], so, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, FK_LDS_PTR(lds + WBASE + stage * WSTAGE + (wave * IB + q) * 1024), 16, vob[q], so, 0, kNonTemporal);
   };
   f32x16 acc[2][2];
 #pragma unroll
