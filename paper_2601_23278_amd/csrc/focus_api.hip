@@ -344,6 +344,20 @@ fk::AttnCut attention_cut(const focus_ctx *c, int max_total, int n_seq, int rows
   return cut;
 }
 
+// RMSNorm of rows of the residual stream -> projection of the result (through `normed`, unless one launch does both).
+// norm_w null: `normed` holds the normalised rows already.
+void norm_and_project(focus_ctx *c, hipStream_t s, const float *resid, const void *norm_w, void *normed, const void *w, int n, fk::Rows rows, int epilogue, void *out,
+                      int ldo, fk::Warm warm, fk::Scratch scratch) {
+  const focus_config &g = c->cfg;
+  if (norm_w && fk::gemm_fuses_rmsnorm(g.dtype, resid, norm_w, w, n, g.hidden, rows.cap)) {
+    Timed t(c, s, FOCUS_KC_GEMM);
+    fk::gemm_of_rmsnorm(s, resid, norm_w, g.rms_eps, w, n, g.hidden, rows, epilogue, out, ldo);
+    return;
+  }
+  if (norm_w) { Timed t(c, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid, norm_w, normed, g.hidden, g.rms_eps, rows); }
+  { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, normed, w, n, g.hidden, rows, epilogue, out, ldo, warm, scratch); }
+}
+
 // rmsnorm -> QKV projection -> rotary + K/V write, for every row of the set (App. C ordering).
 // kv_only: nothing of the layer but its keys and values is wanted; the query columns are then left as they are.
 void layer_qkv(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, const float *resid, bool kv_only = false) {
@@ -352,17 +366,15 @@ void layer_qkv(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, const float
   const int qkv_w = (g.n_q_heads + 2 * g.n_kv_heads) * g.head_dim, skip = kv_only ? g.n_q_heads * g.head_dim : 0;
   const size_t es = esize(g.dtype);
   char *normed = c->at<char>(pl.off_normed), *qkv = c->at<char>(pl.off_qkv);
-  { Timed t(c, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid, c->attn_norm[l], normed, g.hidden, g.rms_eps, rs.rows); }
-  { Timed t(c, s, FOCUS_KC_GEMM);
-    fk::gemm(s, g.dtype, normed, (const char *)c->w_qkv[l] + skip * es * g.hidden, qkv_w - skip, g.hidden, rs.rows, fk::EPI_STORE, qkv + skip * es, qkv_w,
-             fk::Warm(), c->layer_scratch(pl)); }
+  norm_and_project(c, s, resid, c->attn_norm[l], normed, (const char *)c->w_qkv[l] + skip * es * g.hidden, qkv_w - skip, rs.rows, fk::EPI_STORE, qkv + skip * es, qkv_w,
+                   fk::Warm(), c->layer_scratch(pl));
   { Timed t(c, s, FOCUS_KC_KV_WRITE);
     fk::rope_kv_write(s, g.dtype, qkv, g.n_q_heads, rs.rows, rs.ri, rs.pl ? rs.st : c->slots(), c->kv_layer(l), c->at<float2>(pl.off_rope), rs.n_seq, rs.cu); }
 }
 
-void swiglu_ffn(focus_ctx *c, hipStream_t s, const RowSet &rs, const void *normed, const void *w_gate_up, const void *w_down, int ffn,
+void swiglu_ffn(focus_ctx *c, hipStream_t s, const RowSet &rs, const void *norm_w, void *normed, const void *w_gate_up, const void *w_down, int ffn,
                 float *resid, fk::Warm warm_after);
-void moe_ffn(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid, const void *normed);
+void moe_ffn(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid, void *normed);
 
 // attention -> O projection (+residual) -> rmsnorm -> feed-forward (+residual).
 // imp_partial: Eq. 2 of this layer is wanted at that address ([n, H_q, B] per-head sums); the attention launch computes it on the
@@ -390,28 +402,27 @@ void layer_rest(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *res
     fk::importance(s, g.dtype, q, rs.cu, rs.n_seq, g.block_size, g.n_q_heads, g.n_kv_heads, g.head_dim, g.maxpool_k, rs.ri.seq_slot, c->slots(), c->kv_layer(l), imp_partial);
   }
   { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, attn, c->w_o[l], g.hidden, q_w, rs.rows, fk::EPI_ADD_F32, resid, g.hidden, fk::Warm(), c->layer_scratch(pl)); }
-  { Timed t(c, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid, c->mlp_norm[l], normed, g.hidden, g.rms_eps, rs.rows); }
   const size_t qkv_bytes = (size_t)(g.n_q_heads + 2 * g.n_kv_heads) * g.head_dim * g.hidden * esize(g.dtype);
   const fk::Warm next_qkv = l + 1 < g.n_layers ? fk::Warm{c->w_qkv[l + 1], qkv_bytes} : fk::Warm();
   if (c->moe_layer(l)) {
+    { Timed t(c, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid, c->mlp_norm[l], normed, g.hidden, g.rms_eps, rs.rows); }
     moe_ffn(c, s, l, rs, resid, normed);
     return;
   }
-  swiglu_ffn(c, s, rs, normed, c->w_gate_up[l], c->w_down[l], g.ffn, resid, next_qkv);
+  swiglu_ffn(c, s, rs, c->mlp_norm[l], normed, c->w_gate_up[l], c->w_down[l], g.ffn, resid, next_qkv);
 }
 
-// SwiGLU feed-forward on normalised rows, added to the residual stream: gate/up -> SiLU*up -> down.
-void swiglu_ffn(focus_ctx *c, hipStream_t s, const RowSet &rs, const void *normed, const void *w_gate_up, const void *w_down, int ffn,
+// SwiGLU feed-forward, added to the residual stream: (RMSNorm, where norm_w is given, else `normed` holds its result) -> gate/up -> SiLU*up -> down.
+void swiglu_ffn(focus_ctx *c, hipStream_t s, const RowSet &rs, const void *norm_w, void *normed, const void *w_gate_up, const void *w_down, int ffn,
                 float *resid, fk::Warm warm_after) {
   const focus_config &g = c->cfg;
   const Plan &pl = rs.pl ? *rs.pl : c->plan;
   void *gate_up = c->at<char>(pl.off_gate_up), *act = c->at<char>(pl.off_act);
   if (fk::gemm_fuses_silu_mul(g.dtype, normed, w_gate_up, 2 * ffn, g.hidden, rs.rows.cap)) {
-    Timed t(c, s, FOCUS_KC_GEMM);
-    fk::gemm(s, g.dtype, normed, w_gate_up, 2 * ffn, g.hidden, rs.rows, fk::EPI_SILU_MUL, act, ffn,
-             fk::Warm{w_down, (size_t)g.hidden * ffn * esize(g.dtype)}, c->layer_scratch(pl));
+    norm_and_project(c, s, resid, norm_w, normed, w_gate_up, 2 * ffn, rs.rows, fk::EPI_SILU_MUL, act, ffn,
+                     fk::Warm{w_down, (size_t)g.hidden * ffn * esize(g.dtype)}, c->layer_scratch(pl));
   } else {
-    { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, normed, w_gate_up, 2 * ffn, g.hidden, rs.rows, fk::EPI_STORE, gate_up, 2 * ffn, fk::Warm(), c->layer_scratch(pl)); }
+    norm_and_project(c, s, resid, norm_w, normed, w_gate_up, 2 * ffn, rs.rows, fk::EPI_STORE, gate_up, 2 * ffn, fk::Warm(), c->layer_scratch(pl));
     { Timed t(c, s, FOCUS_KC_POINTWISE); fk::silu_mul(s, g.dtype, gate_up, act, ffn, rs.rows); }
   }
   { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, act, w_down, g.hidden, ffn, rs.rows, fk::EPI_ADD_F32, resid, g.hidden, warm_after, c->layer_scratch(pl)); }
@@ -419,7 +430,7 @@ void swiglu_ffn(focus_ctx *c, hipStream_t s, const RowSet &rs, const void *norme
 
 // Mixture-of-experts feed-forward on normalised rows, added to the residual stream: router logits -> picks and weights ->
 // entries sorted by expert -> grouped gate/up and down projections -> weighted sum; plus the shared expert, if any.
-void moe_ffn(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid, const void *normed) {
+void moe_ffn(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid, void *normed) {
   const focus_config &g = c->cfg;
   const Plan &pl = rs.pl ? *rs.pl : c->plan;
   const size_t plane = (size_t)g.max_batch * g.block_size * g.experts_per_token;
@@ -442,7 +453,7 @@ void moe_ffn(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid,
   { Timed t(c, s, FOCUS_KC_ROUTE); fk::moe_route(s, a); fk::moe_group(s, a); }
   { Timed t(c, s, FOCUS_KC_EXPERTS); fk::moe_experts(s, a); }
   // the shared expert adds into the residual stream before the routed sum (both orders are the same sum)
-  if (g.shared_ffn > 0) swiglu_ffn(c, s, rs, normed, c->w_shared_gate_up[l], c->w_shared_down[l], g.shared_ffn, resid, fk::Warm());
+  if (g.shared_ffn > 0) swiglu_ffn(c, s, rs, nullptr, normed, c->w_shared_gate_up[l], c->w_shared_down[l], g.shared_ffn, resid, fk::Warm());
   { Timed t(c, s, FOCUS_KC_ROUTE); fk::moe_combine(s, a); }
 }
 
@@ -852,17 +863,19 @@ int focus_step(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int32_t *s
 
   // decode and verify
   void *normed = ctx->at<char>(pl.off_normed);
-  { Timed t(ctx, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid_p, ctx->final_norm, normed, g.hidden, g.rms_eps, packed.rows); }
+  const bool norm_inside = fk::gemm_fuses_rmsnorm(g.dtype, resid_p, ctx->final_norm, ctx->lm_head, g.vocab, g.hidden, packed.rows.cap);
+  if (!norm_inside) { Timed t(ctx, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid_p, ctx->final_norm, normed, g.hidden, g.rms_eps, packed.rows); }
   // without a logits output the projection reduces every row to (max, sum exp, arg-max) triples per column range in its epilogue
   // and the logits never reach memory; the triples take the place of the logits in the workspace
   int conf_slots = 0;
   bool fused_conf = false;
-  if (!o.logits) {
+  if (!o.logits && !norm_inside) {
     Timed t(ctx, s, FOCUS_KC_GEMM);
     fused_conf = fk::gemm_conf_partials(s, g.dtype, normed, ctx->lm_head, g.vocab, g.hidden, packed.rows, ctx->at<float>(pl.off_logits),
                                         (size_t)ctx->plan.max_rows * g.vocab * 4, &conf_slots);
   }
-  if (!fused_conf) { Timed t(ctx, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, normed, ctx->lm_head, g.vocab, g.hidden, packed.rows, fk::EPI_STORE_F32, logits, g.vocab, fk::Warm(), ctx->scratch()); }
+  if (!fused_conf)
+    norm_and_project(ctx, s, resid_p, norm_inside ? ctx->final_norm : nullptr, normed, ctx->lm_head, g.vocab, packed.rows, fk::EPI_STORE_F32, logits, g.vocab, fk::Warm(), ctx->scratch());
   {
     Timed t(ctx, s, FOCUS_KC_DECODE);
     if (fused_conf) fk::confidence_from_partials(s, ctx->at<float>(pl.off_logits), conf_slots, packed.rows, conf, amax);

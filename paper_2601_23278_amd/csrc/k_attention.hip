@@ -26,23 +26,25 @@ __global__ __launch_bounds__(NW * 64) void k_attn_row(const T *__restrict__ q, i
   constexpr int D = NE * 64, DQ = D / 4, TT = 16;
   __shared__ float osh[NW][D], msh[NW], lsh[NW];
   const int r = blockIdx.x;
+  const int rm = ri.row_map[r], hq = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int tl = lane & (TT - 1), d0 = (lane >> 4) * DQ;
+  float qv[DQ], o[NE];
+  const T *qr = q + (size_t)r * q_stride + (size_t)hq * D + d0;
+#pragma unroll
+  for (int i = 0; i < DQ; ++i) qv[i] = to_f(qr[i]);
+  loads_asked_for();
   const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
   if (r >= M) return;
-  const int hq = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int Hkv = kv.n_kv_heads, P = kv.page_size;
   const int hk = hq / (Hq / Hkv);
-  const int rm = ri.row_map[r], b = rm / ri.B;
+  const int b = rm / ri.B;
   const int slot = slot_of(ri.seq_slot, b, st);
   const int L = st.prefix_len[slot], total = L + ri.B;
   const uint64_t vis = vis_by_b ? vis_by_b[b] : ~0ull;
   const int32_t *pt = pages_of(st, slot);
   const float scale = 1.0f / sqrtf((float)D);
-  const int tl = lane & (TT - 1), d0 = (lane >> 4) * DQ;
-
-  float qv[DQ], o[NE];
-  const T *qr = q + (size_t)r * q_stride + (size_t)hq * D + d0;
 #pragma unroll
-  for (int i = 0; i < DQ; ++i) qv[i] = to_f(qr[i]) * scale;
+  for (int i = 0; i < DQ; ++i) qv[i] *= scale;
 #pragma unroll
   for (int e = 0; e < NE; ++e) o[e] = 0.f;
   float m = -INFINITY, l = 0.f;
@@ -212,14 +214,15 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
   const int chunk = *a.chunk;
   const int bo = group / Hkv, hk = group % Hkv;
   const int b = a.order ? a.order[bo] : bo;
-  const int r0 = a.cu[b], nr = a.cu[b + 1] - r0;
+  const int slot = slot_of(a.ri.seq_slot, b, a.st);
+  const int r0 = a.cu[b], nr = a.cu[b + 1] - r0, L = a.st.prefix_len[slot], total = L + a.ri.B;
+  const uint64_t vis = a.vis_by_b ? a.vis_by_b[b] : ~0ull;
+  loads_asked_for();
   if (nr <= 0) {
     if (BJ > 0 && a.imp_partial && split == 0)           // a sequence without query rows: its importance sums are zero
       for (int i = threadIdx.x; i < g * a.ri.B; i += NW * 64) a.imp_partial[((size_t)b * Hq + hk * g) * a.ri.B + i] = 0.f;
     return;
   }
-  const int slot = slot_of(a.ri.seq_slot, b, a.st);
-  const int L = a.st.prefix_len[slot], total = L + a.ri.B;
   // Splits that have tokens: the sequence's own length decides (it is read here, on the device), bounded by the number of
   // split workgroups this launch has; the last one takes everything that is left.  So a launch whose geometry was fixed when
   // the prefixes were shorter (a captured graph replayed after blocks became prefix) still attends to every token.
@@ -227,7 +230,6 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
   if (split >= nsplit) return;
   const int t0 = split * chunk;
   const int t1 = split == nsplit - 1 ? total : t0 + chunk;
-  const uint64_t vis = a.vis_by_b ? a.vis_by_b[b] : ~0ull;
   const int32_t *pt = pages_of(a.st, slot);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, col = lane & 31;
   // fused importance: only the workgroup of the last K/V range of the sequence (it is the one that ends with the block's tokens)
@@ -531,9 +533,20 @@ __device__ __forceinline__ int combine_splits(const AttnArgs &a, int r) {     //
   return min((a.st.prefix_len[slot] + a.ri.B + chunk - 1) / chunk, a.launch_splits);
 }
 constexpr int kCombineFew = 16;
-__device__ __forceinline__ void combine_few(const AttnArgs &a, int r, int hq, int nsplit, int col) {   // by 32 lanes
+__device__ __forceinline__ void combine_few(const AttnArgs &a, int r, int hq, int col) {   // by 32 lanes
   const size_t pi = ((size_t)r * a.n_q_heads + hq) * a.launch_splits;
-  const float2 ml = col < nsplit ? *(const float2 *)(a.part_ml + (pi + col) * 2) : make_float2(-INFINITY, 0.f);
+  // the partials of the first four splits are asked for before the chain row -> sequence -> length says how many the row has
+  float2 ml = *(const float2 *)(a.part_ml + (pi + min(col, a.launch_splits - 1)) * 2);
+  float4 v[4];
+  auto load = [&](int s0, int n) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = *(const float4 *)(a.part_o + (pi + min(s0 + i, n - 1)) * 128 + col * 4);
+  };
+  load(0, a.launch_splits);
+  loads_asked_for();
+  const int nsplit = combine_splits(a, r);
+  if (nsplit <= 1) return;
+  if (col >= nsplit) ml = make_float2(-INFINITY, 0.f);
   float mm = ml.x;
   for (int o = 16; o > 0; o >>= 1) mm = fmaxf(mm, __shfl_xor(mm, o));
   const float w = ml.x == -INFINITY ? 0.f : exp2f(ml.x - mm);
@@ -541,9 +554,7 @@ __device__ __forceinline__ void combine_few(const AttnArgs &a, int r, int hq, in
   for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o);
   float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int s0 = 0; s0 < nsplit; s0 += 4) {
-    float4 v[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = *(const float4 *)(a.part_o + (pi + min(s0 + i, nsplit - 1)) * 128 + col * 4);
+    if (s0 > 0) load(s0, nsplit);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float ws = s0 + i < nsplit ? __shfl(w, s0 + i, 32) : 0.f;
@@ -557,20 +568,21 @@ __device__ __forceinline__ void combine_few(const AttnArgs &a, int r, int hq, in
 }
 __global__ __launch_bounds__(256) void k_attn_combine_few(AttnArgs a) {
   const int r = blockIdx.x, hq = blockIdx.y * 8 + (threadIdx.x >> 5);
-  const int nsplit = combine_splits(a, r);
-  if (nsplit > 1 && hq < a.n_q_heads) combine_few(a, r, hq, nsplit, threadIdx.x & 31);
+  if (hq < a.n_q_heads) combine_few(a, r, hq, threadIdx.x & 31);
 }
 __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
   __shared__ float wsh[256], osh[8][128], red[8];
   const int r = blockIdx.x, hq = blockIdx.y, tid = threadIdx.x, grp = tid >> 5, col = tid & 31;
+  const size_t pi = ((size_t)r * a.n_q_heads + hq) * a.launch_splits;
+  const float m0 = a.part_ml[(pi + min(tid, a.launch_splits - 1)) * 2];
+  loads_asked_for();
   const int nsplit = combine_splits(a, r);
   if (nsplit <= kCombineFew) {       // the order of the sums is the sequence's, whichever of the two the launch has
-    if (nsplit > 1 && __builtin_amdgcn_readfirstlane(tid >> 6) == 0) combine_few(a, r, hq, nsplit, col);   // both halves alike
+    if (nsplit > 1 && __builtin_amdgcn_readfirstlane(tid >> 6) == 0) combine_few(a, r, hq, col);   // both halves alike
     return;
   }
-  const size_t pi = ((size_t)r * a.n_q_heads + hq) * a.launch_splits;
-  float mm = -INFINITY;
-  for (int s = tid; s < nsplit; s += 256) mm = fmaxf(mm, a.part_ml[(pi + s) * 2]);
+  float mm = tid < nsplit ? m0 : -INFINITY;
+  for (int s = tid + 256; s < nsplit; s += 256) mm = fmaxf(mm, a.part_ml[(pi + s) * 2]);
   for (int o = 32; o > 0; o >>= 1) mm = fmaxf(mm, __shfl_xor(mm, o));
   if ((tid & 63) == 0) red[tid >> 6] = mm;
   __syncthreads();

@@ -78,33 +78,79 @@ static void launch_valu(hipStream_t s, const void *A, const void *W, int N, int 
 // global memory (a 16-byte load per operand feeds four products; both operands permute k alike), and the partial tiles are added in
 // wavefront order through LDS: 5.2 us.
 // SiLU*up: the workgroup computes the gate and the up tile of the same columns and stores silu(gate) * up.
+// NORM: A holds rows of the residual stream and the product is that of their RMSNorm: each workgroup first adds up the squares of its rows
+// (for 256 columns in the order of k_rmsnorm, so that the sums are the same bit for bit) and scales the rows it holds in registers.  The
+// norm's own launch, 2.8 to 3.5 us in a chain of such launches, is gone; these take up to 0.5 us more.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-template <int NW, int EPI>
+template <int NW, int EPI, bool NORM>
 __global__ __launch_bounds__(NW * 64) void k_gemm_f32(const float *__restrict__ A, const float *__restrict__ W, int N, int K, Rows rows,
-                                                      float *out, int ldo) {
-  constexpr int NB = EPI == EPI_SILU_MUL ? 2 : 1, U = 4;
+                                                      float *out, int ldo, const float *__restrict__ norm_w, float eps) {
+  constexpr int NB = EPI == EPI_SILU_MUL ? 2 : 1, U = NW;        // (K = 1024 with eight wavefronts: one trip)
   __shared__ f32x4 part[NB][NW][64];
+  __shared__ float squares[NORM ? NW : 1][64];
   const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
   const int ncol = N / NB, n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
-  if (m0 >= M) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, kq = (lane >> 4) * 4;
   const float *pa = A + (size_t)min(m0 + r, M - 1) * K, *pw[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) pw[b] = W + (size_t)(b * ncol + min(n0 + r, ncol - 1)) * K;
-  f32x4 acc[NB];
+  f32x4 acc[NB], va[U], vw[NB][U], vn[U];
 #pragma unroll
   for (int b = 0; b < NB; ++b) acc[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  for (int c = wave; c * 16 < K; c += NW * U) {
-    f32x4 va[U], vw[NB][U];
+  auto load = [&](int c) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int k = (c + u * NW) * 16 + kq;
       const bool in = k < K;                              // K is a multiple of 4: a piece is inside or outside as a whole
       va[u] = in ? *(const f32x4 *)(pa + k) : zero;
+      if (NORM) vn[u] = in ? *(const f32x4 *)(norm_w + k) : zero;
 #pragma unroll
       for (int b = 0; b < NB; ++b) vw[b][u] = in ? *(const f32x4 *)(pw[b] + k) : zero;
     }
+  };
+  if (m0 >= M) return;                                    // first: a launch without rows (blocks that are not finished) ends 1 us earlier
+  load(wave);
+  float old[4];                                           // EPI_ADD_F32: what the first wavefront adds to
+  if (EPI == EPI_ADD_F32 && wave == 0)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) old[i] = out[(size_t)min(m0 + kq + i, M - 1) * ldo + min(n0 + r, ncol - 1)];
+  loads_asked_for();
+  float inv = 0.f;                                        // of row r
+  if (NORM) {
+    float ss = 0.f;
+    for (int c = wave; c * 16 < K; c += NW * U) {
+      if (c != wave) load(c);
+      float q[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) q[u] = va[u][0] * va[u][0] + va[u][1] * va[u][1] + va[u][2] * va[u][2] + va[u][3] * va[u][3];
+#pragma unroll
+      for (int h = U / 2; h > 0; h /= 2)
+#pragma unroll
+        for (int u = 0; u < h; ++u) q[u] += q[u + h];
+      ss += q[0];
+    }
+    squares[wave][lane] = ss;
+    __syncthreads();
+    float q[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) q[w] = squares[w][lane];
+#pragma unroll
+    for (int h = NW / 2; h > 0; h /= 2)
+#pragma unroll
+      for (int w = 0; w < h; ++w) q[w] += q[w + h];
+    ss = q[0] + __shfl_xor(q[0], 32);
+    ss += __shfl_xor(ss, 16);
+    inv = 1.0f / sqrtf(ss / (float)K + eps);
+  }
+  const bool one_trip = K <= NW * U * 16;                 // (more than one: the squares have used the registers)
+  for (int c = wave; c * 16 < K; c += NW * U) {
+    if (c != wave || (NORM && !one_trip)) load(c);
+    if (NORM)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) va[u][e] = va[u][e] * inv * vn[u][e];
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -128,17 +174,23 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_f32(const float *__restrict__ 
     if (gm >= M || gn >= ncol) continue;
     float *o = out + (size_t)gm * ldo + gn;
     if (EPI == EPI_SILU_MUL) *o = acc[0][i] / (1.0f + __expf(-acc[0][i])) * acc[NB - 1][i];
-    else if (EPI == EPI_ADD_F32) *o += acc[0][i];
+    else if (EPI == EPI_ADD_F32) *o = old[i] + acc[0][i];
     else *o = acc[0][i];
   }
 }
 
-template <int NW>
-static void launch_f32(hipStream_t s, const float *A, const float *W, int N, int K, Rows rows, int epi, float *out, int ldo) {
+template <int NW, bool NORM>
+static void launch_f32(hipStream_t s, const float *A, const float *W, int N, int K, Rows rows, int epi, float *out, int ldo, const float *norm_w, float eps) {
   const dim3 grid(((epi == EPI_SILU_MUL ? N / 2 : N) + 15) / 16, (rows.cap + 15) / 16);
-  if (epi == EPI_SILU_MUL) k_gemm_f32<NW, EPI_SILU_MUL><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo);
-  else if (epi == EPI_ADD_F32) k_gemm_f32<NW, EPI_ADD_F32><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo);
-  else k_gemm_f32<NW, EPI_STORE_F32><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo);
+  if (epi == EPI_SILU_MUL) k_gemm_f32<NW, EPI_SILU_MUL, NORM><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo, norm_w, eps);
+  else if (epi == EPI_ADD_F32) k_gemm_f32<NW, EPI_ADD_F32, NORM><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo, norm_w, eps);
+  else k_gemm_f32<NW, EPI_STORE_F32, NORM><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo, norm_w, eps);
+}
+template <bool NORM>
+static void launch_f32(hipStream_t s, const float *A, const float *W, int N, int K, Rows rows, int epi, float *out, int ldo, const float *norm_w = nullptr,
+                       float eps = 0.f) {
+  if (K >= 512) launch_f32<8, NORM>(s, A, W, N, K, rows, epi, out, ldo, norm_w, eps);
+  else launch_f32<4, NORM>(s, A, W, N, K, rows, epi, out, ldo, norm_w, eps);
 }
 // 16-byte loads need K a multiple of 4 and aligned operands.  A workgroup reads its operands without sharing them, so from about 1024
 // tiles of 64 x 64 on k_gemm_valu is the faster one (rows x N x K, us, valu / this: 64 x 1024 x 1024 136 / 6, 1024 x 1024 x 1024
@@ -663,26 +715,43 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__
 template <int EPI>
 __global__ __launch_bounds__(256) void k_splitk_reduce(const float *__restrict__ part, int splits, size_t split_stride, Rows rows, int N,
                                                        void *out, int ldo) {
-  const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
+  constexpr int U = 4;
   const int ncol = EPI == EPI_SILU_MUL ? N / 2 : N, per_row = ncol / 4;
   const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-  const int m = (int)(idx / per_row), c = (int)(idx % per_row) * 4;
-  if (m >= M) return;
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
-  for (int s = 0; s < splits; ++s) {
-    const float *p = part + s * split_stride + (size_t)m * N + c;
-    const float4 v = *(const float4 *)p;
-    a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
-    if (EPI == EPI_SILU_MUL) {
-      const float4 u = *(const float4 *)(p + N / 2);
-      b.x += u.x; b.y += u.y; b.z += u.z; b.w += u.w;
+  const int m = (int)(idx / per_row), c = (int)(idx % per_row) * 4, mc = min(m, rows.cap - 1);
+  float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a, v[U], u[U];
+  const float *p = part + (size_t)mc * N + c;
+  auto load = [&](int s0) {
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const float *q = p + (size_t)min(s0 + i, splits - 1) * split_stride;
+      v[i] = *(const float4 *)q;
+      if (EPI == EPI_SILU_MUL) u[i] = *(const float4 *)(q + N / 2);
     }
+  };
+  load(0);
+  float old[4];
+  if (EPI == EPI_ADD_F32)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) old[i] = ((const float *)out)[(size_t)mc * ldo + c + i];
+  loads_asked_for();
+  const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
+  if (m >= M) return;
+  for (int s0 = 0; s0 < splits; s0 += U) {
+    if (s0 > 0) load(s0);
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+      if (s0 + i < splits) {
+        a.x += v[i].x; a.y += v[i].y; a.z += v[i].z; a.w += v[i].w;
+        if (EPI == EPI_SILU_MUL) { b.x += u[i].x; b.y += u[i].y; b.z += u[i].z; b.w += u[i].w; }
+      }
   }
-  const float r[4] = {a.x, a.y, a.z, a.w}, u[4] = {b.x, b.y, b.z, b.w};
+  const float r[4] = {a.x, a.y, a.z, a.w}, up[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const size_t o = (size_t)m * ldo + c + i;
-    if (EPI == EPI_SILU_MUL) ((bf16_t *)out)[o] = (bf16_t)(r[i] / (1.0f + __expf(-r[i])) * u[i]);
+    if (EPI == EPI_SILU_MUL) ((bf16_t *)out)[o] = (bf16_t)(r[i] / (1.0f + __expf(-r[i])) * up[i]);
+    else if (EPI == EPI_ADD_F32) ((float *)out)[o] = old[i] + r[i];
     else store_out<bf16_t, EPI>(out, o, r[i]);
   }
 }
@@ -808,13 +877,19 @@ bool gemm_fuses_silu_mul(int dtype, const void *A, const void *W, int N, int K, 
   return dtype == FOCUS_BF16 && K % 64 == 0 && N % 2 == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)W & 15) == 0;
 }
 
+bool gemm_fuses_rmsnorm(int dtype, const float *x, const void *norm_w, const void *W, int N, int K, int rows_cap) {
+  return dtype == FOCUS_F32 && takes_f32(x, W, N, K, rows_cap) && ((uintptr_t)norm_w & 15) == 0;
+}
+void gemm_of_rmsnorm(hipStream_t s, const float *x, const void *norm_w, float eps, const void *W, int N, int K, Rows rows, int epilogue, void *out, int ldo) {
+  if (rows.cap > 0) launch_f32<true>(s, x, (const float *)W, N, K, rows, epilogue, (float *)out, ldo, (const float *)norm_w, eps);
+}
+
 void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, Rows rows, int epilogue,
           void *out, int ldo, Warm warm, Scratch scratch) {
   if (rows.cap <= 0) return;
   if (dtype == FOCUS_F32) {
     if (!takes_f32(A, W, N, K, rows.cap)) launch_valu<float>(s, A, W, N, K, rows, epilogue, out, ldo);
-    else if (K >= 512) launch_f32<8>(s, (const float *)A, (const float *)W, N, K, rows, epilogue, (float *)out, ldo);
-    else launch_f32<4>(s, (const float *)A, (const float *)W, N, K, rows, epilogue, (float *)out, ldo);
+    else launch_f32<false>(s, (const float *)A, (const float *)W, N, K, rows, epilogue, (float *)out, ldo);
     return;
   }
   const bool aligned = K % 64 == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)W & 15) == 0;
