@@ -865,14 +865,14 @@ int focus_step(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int32_t *s
   void *normed = ctx->at<char>(pl.off_normed);
   const bool norm_inside = fk::gemm_fuses_rmsnorm(g.dtype, resid_p, ctx->final_norm, ctx->lm_head, g.vocab, g.hidden, packed.rows.cap);
   if (!norm_inside) { Timed t(ctx, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid_p, ctx->final_norm, normed, g.hidden, g.rms_eps, packed.rows); }
-  // without a logits output the projection reduces every row to (max, sum exp, arg-max) triples per column range in its epilogue
-  // and the logits never reach memory; the triples take the place of the logits in the workspace
+  // the projection reduces every row to (max, sum exp, arg-max) triples per column range in its epilogue, and without a logits output the
+  // logits never reach memory; the triples take the place of the logits in the workspace
   int conf_slots = 0;
   bool fused_conf = false;
-  if (!o.logits && !norm_inside) {
+  if (!norm_inside) {
     Timed t(ctx, s, FOCUS_KC_GEMM);
     fused_conf = fk::gemm_conf_partials(s, g.dtype, normed, ctx->lm_head, g.vocab, g.hidden, packed.rows, ctx->at<float>(pl.off_logits),
-                                        (size_t)ctx->plan.max_rows * g.vocab * 4, &conf_slots);
+                                        (size_t)ctx->plan.max_rows * g.vocab * 4, &conf_slots, o.logits);
   }
   if (!fused_conf)
     norm_and_project(ctx, s, resid_p, norm_inside ? ctx->final_norm : nullptr, normed, ctx->lm_head, g.vocab, packed.rows, fk::EPI_STORE_F32, logits, g.vocab, fk::Warm(), ctx->scratch());

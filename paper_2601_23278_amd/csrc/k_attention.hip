@@ -533,20 +533,9 @@ __device__ __forceinline__ int combine_splits(const AttnArgs &a, int r) {     //
   return min((a.st.prefix_len[slot] + a.ri.B + chunk - 1) / chunk, a.launch_splits);
 }
 constexpr int kCombineFew = 16;
-__device__ __forceinline__ void combine_few(const AttnArgs &a, int r, int hq, int col) {   // by 32 lanes
+__device__ __forceinline__ void combine_few(const AttnArgs &a, int r, int hq, int nsplit, int col) {   // by 32 lanes
   const size_t pi = ((size_t)r * a.n_q_heads + hq) * a.launch_splits;
-  // the partials of the first four splits are asked for before the chain row -> sequence -> length says how many the row has
-  float2 ml = *(const float2 *)(a.part_ml + (pi + min(col, a.launch_splits - 1)) * 2);
-  float4 v[4];
-  auto load = [&](int s0, int n) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = *(const float4 *)(a.part_o + (pi + min(s0 + i, n - 1)) * 128 + col * 4);
-  };
-  load(0, a.launch_splits);
-  loads_asked_for();
-  const int nsplit = combine_splits(a, r);
-  if (nsplit <= 1) return;
-  if (col >= nsplit) ml = make_float2(-INFINITY, 0.f);
+  const float2 ml = col < nsplit ? *(const float2 *)(a.part_ml + (pi + col) * 2) : make_float2(-INFINITY, 0.f);
   float mm = ml.x;
   for (int o = 16; o > 0; o >>= 1) mm = fmaxf(mm, __shfl_xor(mm, o));
   const float w = ml.x == -INFINITY ? 0.f : exp2f(ml.x - mm);
@@ -554,7 +543,9 @@ __device__ __forceinline__ void combine_few(const AttnArgs &a, int r, int hq, in
   for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o);
   float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int s0 = 0; s0 < nsplit; s0 += 4) {
-    if (s0 > 0) load(s0, nsplit);
+    float4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = *(const float4 *)(a.part_o + (pi + min(s0 + i, nsplit - 1)) * 128 + col * 4);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float ws = s0 + i < nsplit ? __shfl(w, s0 + i, 32) : 0.f;
@@ -568,21 +559,20 @@ __device__ __forceinline__ void combine_few(const AttnArgs &a, int r, int hq, in
 }
 __global__ __launch_bounds__(256) void k_attn_combine_few(AttnArgs a) {
   const int r = blockIdx.x, hq = blockIdx.y * 8 + (threadIdx.x >> 5);
-  if (hq < a.n_q_heads) combine_few(a, r, hq, threadIdx.x & 31);
+  const int nsplit = combine_splits(a, r);
+  if (nsplit > 1 && hq < a.n_q_heads) combine_few(a, r, hq, nsplit, threadIdx.x & 31);
 }
 __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
   __shared__ float wsh[256], osh[8][128], red[8];
   const int r = blockIdx.x, hq = blockIdx.y, tid = threadIdx.x, grp = tid >> 5, col = tid & 31;
-  const size_t pi = ((size_t)r * a.n_q_heads + hq) * a.launch_splits;
-  const float m0 = a.part_ml[(pi + min(tid, a.launch_splits - 1)) * 2];
-  loads_asked_for();
   const int nsplit = combine_splits(a, r);
   if (nsplit <= kCombineFew) {       // the order of the sums is the sequence's, whichever of the two the launch has
-    if (nsplit > 1 && __builtin_amdgcn_readfirstlane(tid >> 6) == 0) combine_few(a, r, hq, col);   // both halves alike
+    if (nsplit > 1 && __builtin_amdgcn_readfirstlane(tid >> 6) == 0) combine_few(a, r, hq, nsplit, col);   // both halves alike
     return;
   }
-  float mm = tid < nsplit ? m0 : -INFINITY;
-  for (int s = tid + 256; s < nsplit; s += 256) mm = fmaxf(mm, a.part_ml[(pi + s) * 2]);
+  const size_t pi = ((size_t)r * a.n_q_heads + hq) * a.launch_splits;
+  float mm = -INFINITY;
+  for (int s = tid; s < nsplit; s += 256) mm = fmaxf(mm, a.part_ml[(pi + s) * 2]);
   for (int o = 32; o > 0; o >>= 1) mm = fmaxf(mm, __shfl_xor(mm, o));
   if ((tid & 63) == 0) red[tid >> 6] = mm;
   __syncthreads();

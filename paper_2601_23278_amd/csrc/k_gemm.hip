@@ -403,7 +403,7 @@ constexpr int kNonTemporal = 2;      // cache policy of a load (NT bit): what is
 template <int BM, int EPI, int BN = 256, bool ONE = false>
 __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W, int N, int K,
                                                       Rows rows, void *out, int ldo, int tiles_m, int tiles_n, const void *warm,
-                                                      unsigned warm_bytes, int splits, size_t split_stride) {
+                                                      unsigned warm_bytes, int splits, size_t split_stride, float *logits) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer-resource builtins exist in the device pass only
   // splits > 1: the K range is cut into `splits` parts, one workgroup each; part s writes its fp32 sums to
   // out + s * split_stride and a second kernel adds the parts in order (EPI is then EPI_STORE_F32 or EPI_PARTIAL_SILU)
@@ -612,11 +612,31 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__
     }
     return;
   }
-  if (EPI == EPI_CONF) {
+  if (EPI == EPI_CONF || EPI == EPI_CONF_LOGITS) {
     // per row: (maximum, sum exp(x - maximum), lowest column of the maximum) over this wavefront's WN columns.  The accumulators
     // hold a row spread over 32 lanes; each 32 x WN patch goes through a private LDS area (the operand stages are free: every
     // load has landed) and comes back with two lanes per row, each holding half of the row's columns in order, so that the
     // reductions run inside a lane and one exchange with the neighbour lane finishes them.
+    if (EPI == EPI_CONF_LOGITS) {
+      // the products themselves are wanted too, [M, N] (276 rows x 151936: 58 us less than reading them again); the descriptor ends at the
+      // last valid row, as below
+      const __amdgpu_buffer_rsrc_t rs_l = __builtin_amdgcn_make_buffer_rsrc(logits + (size_t)m0 * N, 0, (unsigned)min(BM, M - m0) * (unsigned)N * 4u, 0x00020000);
+      unsigned at[TN];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int gn = n0 + wn + j * 32 + ecol;
+        at[j] = gn < N ? ((unsigned)(erow - m0) * (unsigned)N + (unsigned)gn) * 4u : 0x80000000u;
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][r]), rs_l, at[j], (unsigned)(i * 32 + 8 * (r >> 2) + (r & 3)) * (unsigned)N * 4u, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    }
     constexpr int XS = WN + 4;                               // padded row: two lanes per row read 16-byte pieces
     static_assert(NW * 32 * XS * 4 <= 2 * (BM + BN) * 128, "transpose area");
     lds_barrier();                                           // everybody's loads have landed, nobody reads operands any more
@@ -758,11 +778,11 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float *__restrict__
 
 template <int BM, int EPI, int BN = 256, bool ONE = false>
 static bool launch_pipe(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, int K, Rows rows, void *out, int ldo, Warm warm, int splits = 1,
-                        size_t split_stride = 0) {
+                        size_t split_stride = 0, float *logits = nullptr) {
   constexpr int kLds = (pipe_stages_a(BM) * BM + kPipeStagesW * BN) * 128;
   constexpr bool SILU_W = EPI == EPI_SILU_MUL || EPI == EPI_PARTIAL_SILU;
-  if constexpr (!ONE && BM <= 128 && (EPI == EPI_CONF || EPI == EPI_STORE_F32))      // the vocabulary projection of few rows
-    if (rows.expected() <= BM && splits == 1) return launch_pipe<BM, EPI, BN, true>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
+  if constexpr (!ONE && BM <= 128 && (EPI == EPI_CONF || EPI == EPI_CONF_LOGITS || EPI == EPI_STORE_F32 || EPI == EPI_PARTIAL_SILU))      // projections of few rows
+    if (rows.expected() <= BM) return launch_pipe<BM, EPI, BN, true>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride, logits);
   static bool ready = false;             // the dynamic LDS size has to be allowed once per kernel
   if (!ready) {
     if (hipFuncSetAttribute((const void *)k_gemm_pipe<BM, EPI, BN, ONE>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess) return false;
@@ -771,13 +791,13 @@ static bool launch_pipe(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, 
   const int tiles_m = (rows.cap + BM - 1) / BM, tiles_n = SILU_W ? (N / 2 + BN / 2 - 1) / (BN / 2) : (N + BN - 1) / BN;
   const int grid = ((tiles_m * tiles_n * splits + 7) / 8) * 8;
   k_gemm_pipe<BM, EPI, BN, ONE><<<grid, 256, kLds, s>>>(a, w, N, K, rows, out, ldo, tiles_m, tiles_n, warm.ptr, (unsigned)std::min<size_t>(warm.bytes, 0x7fffffffu),
-                                                   splits, split_stride);
+                                                   splits, split_stride, logits);
   return true;
 }
 
 template <int BM>
 static bool launch_pipe_epi(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, int K, Rows rows, int epi, void *out, int ldo, Warm warm, int splits,
-                            size_t split_stride) {
+                            size_t split_stride, float *logits) {
   switch (epi) {
     case EPI_STORE: return launch_pipe<BM, EPI_STORE>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
     case EPI_ADD_F32: return launch_pipe<BM, EPI_ADD_F32>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
@@ -785,6 +805,9 @@ static bool launch_pipe_epi(hipStream_t s, const bf16_t *a, const bf16_t *w, int
     case EPI_SILU_MUL: return launch_pipe<BM, EPI_SILU_MUL>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
     case EPI_PARTIAL_SILU: return launch_pipe<BM, EPI_PARTIAL_SILU>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
     case EPI_CONF: return launch_pipe<BM, EPI_CONF>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
+    case EPI_CONF_LOGITS:
+      if constexpr (BM < 256) return launch_pipe<BM, EPI_CONF_LOGITS>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride, logits);
+      else return false;
   }
   return false;
 }
@@ -793,21 +816,21 @@ static bool launch_pipe_epi(hipStream_t s, const bf16_t *a, const bf16_t *w, int
 struct PipeShape { int bm, bn, splits; };
 
 static bool launch_shape(hipStream_t s, PipeShape p, const void *A, const void *W, int N, int K, Rows rows, int epi, void *out, int ldo, Warm warm,
-                         size_t split_stride = 0) {
+                         size_t split_stride = 0, float *logits = nullptr) {
   const bf16_t *a = (const bf16_t *)A, *w = (const bf16_t *)W;
   if (p.bn == 192)
     return epi == EPI_STORE     ? launch_pipe<256, EPI_STORE, 192>(s, a, w, N, K, rows, out, ldo, warm)
            : epi == EPI_ADD_F32 ? launch_pipe<256, EPI_ADD_F32, 192>(s, a, w, N, K, rows, out, ldo, warm)
                                 : launch_pipe<256, EPI_STORE_F32, 192>(s, a, w, N, K, rows, out, ldo, warm);
   switch (p.bm) {
-    case 64: return launch_pipe_epi<64>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
-    case 96: return launch_pipe_epi<96>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
-    case 128: return launch_pipe_epi<128>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
-    case 160: return launch_pipe_epi<160>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
-    case 192: return launch_pipe_epi<192>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
-    case 224: return launch_pipe_epi<224>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
+    case 64: return launch_pipe_epi<64>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
+    case 96: return launch_pipe_epi<96>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
+    case 128: return launch_pipe_epi<128>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
+    case 160: return launch_pipe_epi<160>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
+    case 192: return launch_pipe_epi<192>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
+    case 224: return launch_pipe_epi<224>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
   }
-  return launch_pipe_epi<256>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride);
+  return launch_pipe_epi<256>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
 }
 
 // The shape with the least estimated time.  A compute unit takes one tile at a time and spends about 0.30 + 0.0046 BM us (0.08 more at
@@ -862,14 +885,15 @@ static bool takes_pipe(int N, int K, int rows_cap) {   // byte offsets of rows, 
 }
 
 bool gemm_conf_partials(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, Rows rows, float *part, size_t part_bytes,
-                        int *n_slots) {
+                        int *n_slots, float *logits) {
   if (rows.cap <= 0 || dtype != FOCUS_BF16 || K % 64 || (((uintptr_t)A | (uintptr_t)W) & 15) || !takes_pipe(N, K, rows.cap)) return false;
   if ((long)((rows.expected() + 127) / 128) * ((N + 255) / 256) < 160) return false;   // a small vocabulary: K-split and materialised logits
   const PipeShape p = pipe_shape(N, K, rows, EPI_CONF, 0);
+  if (logits && p.bm == 256) return false;                         // the epilogue that also stores does not fit the registers at that height
   const int slots = (N + 255) / 256 * (p.bm == 256 ? 2 : 4);       // one per wavefront column
   if ((size_t)rows.cap * slots * 12 > part_bytes) return false;
   *n_slots = slots;
-  return launch_shape(s, p, A, W, N, K, rows, EPI_CONF, part, slots, Warm());
+  return launch_shape(s, p, A, W, N, K, rows, logits ? EPI_CONF_LOGITS : EPI_CONF, part, slots, Warm(), 0, logits);
 }
 
 bool gemm_fuses_silu_mul(int dtype, const void *A, const void *W, int N, int K, int rows_cap) {
@@ -898,6 +922,18 @@ void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, 
   // weight slabs in flight each) with K cut so that about one workgroup per CU exists (64 rows x 4096 x 4096 16.4 us, 21 with two)
   const int est = rows.expected();
   const bool pipe = takes_pipe(N, K, rows.cap);
+  // Up to 32 rows, weights of 96 MB and more in at least 32 column tiles: 64-row tiles of the pipelined kernel with parts of 16 slabs keep
+  // more loads in flight (8 rows x 24576 x 4096 41.4 us by the expert-projection kernel, 36.8 in this; x 12288 27.0 and 21.3, x 32768 58 and
+  // 47; 32 rows x 24576 42.3 and 39.2; from 64 rows on either may be the faster one, and so with fewer weights)
+  if (pipe && scratch.ptr && N % 8 == 0 && rows.cap <= 32 && (double)N * K >= 48e6 && N >= 32 * 256 && K % 2048 == 0 &&
+      (size_t)(K / 1024) * rows.cap * N * 4 <= scratch.bytes) {
+    const bool silu = epilogue == EPI_SILU_MUL;
+    const int parts = K / 1024;
+    if (launch_shape(s, PipeShape{64, 256, parts}, A, W, N, K, rows, silu ? EPI_PARTIAL_SILU : EPI_STORE_F32, scratch.ptr, N, Warm(), (size_t)rows.cap * N)) {
+      launch_reduce(s, N, rows, epilogue, out, ldo, parts, (const float *)scratch.ptr);
+      return;
+    }
+  }
   if (pipe && scratch.ptr && N % 8 == 0 && rows.cap <= 128 && (epilogue == EPI_SILU_MUL ? (N / 2 + 127) / 128 : (N + 255) / 256) < 160) {
     const int nk = K / 64, tn = epilogue == EPI_SILU_MUL ? (N / 2 + 63) / 64 : (N + 127) / 128;
     int splits = 1;

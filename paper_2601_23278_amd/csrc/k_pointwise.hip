@@ -354,21 +354,26 @@ void iota_rows(hipStream_t s, int32_t *row_map, int32_t *cu, int n_seq, int B, i
 // spread of prefix lengths, starting the long sequences first keeps the tail of the launch short.
 __global__ __launch_bounds__(256) void k_length_order(int n_seq, int B, const int32_t *seq_slot, SlotState st, int32_t *order, AttnCut cut0, AttnCut cut1,
                                                       int32_t *chunk) {
-  __shared__ int lens[256];
+  // the lengths go through the LDS 256 at a time and come back four at a time: one after the other, each a wait, 256 took 20 us
+  __shared__ int4 lens[64];
   const int b = blockIdx.x * 256 + threadIdx.x;
   const int len = st.prefix_len[slot_of(seq_slot, min(b, n_seq - 1), st)];
   int rank = 0, longest = 0;
   for (int o0 = 0; o0 < n_seq; o0 += 256) {
-    // a read per thread instead of one after the other in every thread (256 sequences: 20 us)
-    const int mine = st.prefix_len[slot_of(seq_slot, min(o0 + (int)threadIdx.x, n_seq - 1), st)];
+    const int o = o0 + threadIdx.x, mine = o < n_seq ? st.prefix_len[slot_of(seq_slot, o, st)] : -1;
     __syncthreads();
-    lens[threadIdx.x] = mine;
+    ((int *)lens)[threadIdx.x] = mine;
     __syncthreads();
-    const int n = min(256, n_seq - o0);
-    for (int i = 0; i < n; ++i) {
-      const int lo = lens[i];
-      rank += (lo > len || (lo == len && o0 + i < b)) ? 1 : 0;
-      longest = max(longest, lo);
+    const int quads = (min(256, n_seq - o0) + 3) / 4;
+#pragma unroll 8
+    for (int i = 0; i < quads; ++i) {
+      const int4 v = lens[i];
+      const int lo[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        rank += (lo[e] > len || (lo[e] == len && o0 + 4 * i + e < b)) ? 1 : 0;      // (beyond the last sequence: -1, never before anything)
+        longest = max(longest, lo[e]);
+      }
     }
   }
   if (b < n_seq) order[rank] = b;

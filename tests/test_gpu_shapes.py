@@ -183,6 +183,12 @@ def test_k_parts_of_a_row_count_only_the_device_knows(vocab):
     compare_steps(wl, 1, 2e-2, exact=False, k_override=[b % 7 for b in range(66)], row_hint=(200, 6))
 
 
+@pytest.mark.parametrize("batch,block,ffn", [(1, 32, 12288), (1, 5, 12352), (11, 3, 12288)])
+def test_projections_of_few_rows_with_many_weights(batch, block, ffn):
+    """Gate/up of 100 MB: 32 and 5 rows in two parts of 16 slabs, the last column tile with columns missing; 33 rows are one too many."""
+    compare_steps(small_bf16(batch=batch, block_size=block, hidden=2048, ffn=ffn, n_q_heads=2, n_kv_heads=1, n_layers=2, steps=1), 1, 2e-2, exact=False)
+
+
 @pytest.mark.parametrize("shape", [dict(n_q_heads=17, n_kv_heads=17, batch=3), dict(n_q_heads=40, n_kv_heads=4, batch=2, block_size=64, prefix_hi=70),
                                    dict(n_q_heads=1, n_kv_heads=1, batch=300, block_size=2, hidden=64, ffn=64, vocab=64, prefill="synthetic")])
 def test_head_sums_and_packing(shape):
