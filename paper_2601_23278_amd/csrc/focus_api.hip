@@ -230,6 +230,7 @@ struct focus_ctx {
   int n_timed = 0;
   hipStream_t last_stream = nullptr;
   int max_total = 0;                   // host-side bound of prefix_len + B over all sequences that were ever installed
+  std::vector<int> slot_total;         // prefix_len + B with which each slot was last installed (0: never); blocks that became prefix are not in it
   int hint_rows = 0, hint_rows_per_seq = 0;   // focus_set_row_hint: expected packed rows of a step / per sequence (0: none)
 
   template <typename T> T *at(size_t off) const { return (T *)(ws + off); }
@@ -329,6 +330,7 @@ struct RowSet {        // a set of rows the layers run on
   const int32_t *order;   // bf16 models: attention launch order (longest sequence first),
   fk::AttnCut cut;        // shape of the attention launches (attention_cut()) and the split length that length_order() wrote for it
   const int32_t *chunk;
+  int mean_total = 0, longest_total = 0;   // the host's idea of the sequences' lengths (expected_lengths())
   const Plan *pl = nullptr;   // the buffers of the layers and the state of the sequences, where they are not the context's own (prefill)
   fk::SlotState st = {};
 };
@@ -340,14 +342,14 @@ fk::AttnCut attention_cut(const focus_ctx *c, int max_total, int n_seq, int rows
   const size_t room = c->plan.part_entries / std::max<size_t>(1, (size_t)rows_cap * g.n_q_heads);      // entries: rows * H_q * splits
   cut.splits = (int)std::max<size_t>(1, std::min<size_t>(room, fk::attention_parts(max_total, cut.groups, cut.pairs, importance)));
   const int chunk = fk::attention_chunk(max_total, cut);
-  cut.splits = (max_total + chunk - 1) / chunk;      // no workgroups without tokens where max_total is the real length (they cannot warm anything)
+  cut.splits = (max_total + chunk - 1) / chunk;      // no workgroups without tokens where max_total is the real length
   return cut;
 }
 
 // RMSNorm of rows of the residual stream -> projection of the result (through `normed`, unless one launch does both).
 // norm_w null: `normed` holds the normalised rows already.
 void norm_and_project(focus_ctx *c, hipStream_t s, const float *resid, const void *norm_w, void *normed, const void *w, int n, fk::Rows rows, int epilogue, void *out,
-                      int ldo, fk::Warm warm, fk::Scratch scratch) {
+                      int ldo, fk::Scratch scratch) {
   const focus_config &g = c->cfg;
   if (norm_w && fk::gemm_fuses_rmsnorm(g.dtype, resid, norm_w, w, n, g.hidden, rows.cap)) {
     Timed t(c, s, FOCUS_KC_GEMM);
@@ -355,7 +357,17 @@ void norm_and_project(focus_ctx *c, hipStream_t s, const float *resid, const voi
     return;
   }
   if (norm_w) { Timed t(c, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid, norm_w, normed, g.hidden, g.rms_eps, rows); }
-  { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, normed, w, n, g.hidden, rows, epilogue, out, ldo, warm, scratch); }
+  { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, normed, w, n, g.hidden, rows, epilogue, out, ldo, scratch); }
+}
+
+// Mean and largest length of the sequences as they were installed: of slots 0 .. n_seq - 1, or, where the list of slots is on the device, of
+// all that ever were.
+void expected_lengths(const focus_ctx *c, int n_seq, const int32_t *seq_slot, RowSet &rs) {
+  long sum = 0, known = 0;
+  const int n = seq_slot ? c->cfg.max_batch : n_seq;
+  for (int i = 0; i < n; ++i)
+    if (c->slot_total[i] > 0) { sum += c->slot_total[i]; ++known; rs.longest_total = std::max(rs.longest_total, c->slot_total[i]); }
+  rs.mean_total = known ? (int)(sum / known) : 0;
 }
 
 // rmsnorm -> QKV projection -> rotary + K/V write, for every row of the set (App. C ordering).
@@ -367,13 +379,13 @@ void layer_qkv(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, const float
   const size_t es = esize(g.dtype);
   char *normed = c->at<char>(pl.off_normed), *qkv = c->at<char>(pl.off_qkv);
   norm_and_project(c, s, resid, c->attn_norm[l], normed, (const char *)c->w_qkv[l] + skip * es * g.hidden, qkv_w - skip, rs.rows, fk::EPI_STORE, qkv + skip * es, qkv_w,
-                   fk::Warm(), c->layer_scratch(pl));
+                   c->layer_scratch(pl));
   { Timed t(c, s, FOCUS_KC_KV_WRITE);
     fk::rope_kv_write(s, g.dtype, qkv, g.n_q_heads, rs.rows, rs.ri, rs.pl ? rs.st : c->slots(), c->kv_layer(l), c->at<float2>(pl.off_rope), rs.n_seq, rs.cu); }
 }
 
 void swiglu_ffn(focus_ctx *c, hipStream_t s, const RowSet &rs, const void *norm_w, void *normed, const void *w_gate_up, const void *w_down, int ffn,
-                float *resid, fk::Warm warm_after);
+                float *resid);
 void moe_ffn(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid, void *normed);
 
 // attention -> O projection (+residual) -> rmsnorm -> feed-forward (+residual).
@@ -393,39 +405,36 @@ void layer_rest(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *res
     a.part_o = c->plan.part_entries ? c->at<float>(c->plan.off_part_o) : nullptr;
     a.part_ml = c->plan.part_entries ? c->at<float>(c->plan.off_part_ml) : nullptr;
     a.order = rs.order;
-    a.warm = fk::Warm{c->w_o[l], (size_t)g.hidden * q_w * esize(g.dtype)};
-    a.launch_splits = rs.cut.splits; a.chunk = rs.chunk;
+    a.launch_splits = rs.cut.splits; a.chunk = rs.chunk; a.mean_total = rs.mean_total; a.longest_total = rs.longest_total;
     a.imp_partial = imp_partial; a.imp_pool_k = g.maxpool_k;
     if (fk::attention(s, a)) imp_partial = nullptr; }
   if (imp_partial) {
     Timed t(c, s, FOCUS_KC_IMPORTANCE);
     fk::importance(s, g.dtype, q, rs.cu, rs.n_seq, g.block_size, g.n_q_heads, g.n_kv_heads, g.head_dim, g.maxpool_k, rs.ri.seq_slot, c->slots(), c->kv_layer(l), imp_partial);
   }
-  { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, attn, c->w_o[l], g.hidden, q_w, rs.rows, fk::EPI_ADD_F32, resid, g.hidden, fk::Warm(), c->layer_scratch(pl)); }
-  const size_t qkv_bytes = (size_t)(g.n_q_heads + 2 * g.n_kv_heads) * g.head_dim * g.hidden * esize(g.dtype);
-  const fk::Warm next_qkv = l + 1 < g.n_layers ? fk::Warm{c->w_qkv[l + 1], qkv_bytes} : fk::Warm();
+  { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, attn, c->w_o[l], g.hidden, q_w, rs.rows, fk::EPI_ADD_F32, resid, g.hidden, c->layer_scratch(pl)); }
   if (c->moe_layer(l)) {
     { Timed t(c, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid, c->mlp_norm[l], normed, g.hidden, g.rms_eps, rs.rows); }
     moe_ffn(c, s, l, rs, resid, normed);
     return;
   }
-  swiglu_ffn(c, s, rs, c->mlp_norm[l], normed, c->w_gate_up[l], c->w_down[l], g.ffn, resid, next_qkv);
+  swiglu_ffn(c, s, rs, c->mlp_norm[l], normed, c->w_gate_up[l], c->w_down[l], g.ffn, resid);
 }
 
 // SwiGLU feed-forward, added to the residual stream: (RMSNorm, where norm_w is given, else `normed` holds its result) -> gate/up -> SiLU*up -> down.
 void swiglu_ffn(focus_ctx *c, hipStream_t s, const RowSet &rs, const void *norm_w, void *normed, const void *w_gate_up, const void *w_down, int ffn,
-                float *resid, fk::Warm warm_after) {
+                float *resid) {
   const focus_config &g = c->cfg;
   const Plan &pl = rs.pl ? *rs.pl : c->plan;
   void *gate_up = c->at<char>(pl.off_gate_up), *act = c->at<char>(pl.off_act);
   if (fk::gemm_fuses_silu_mul(g.dtype, normed, w_gate_up, 2 * ffn, g.hidden, rs.rows.cap)) {
     norm_and_project(c, s, resid, norm_w, normed, w_gate_up, 2 * ffn, rs.rows, fk::EPI_SILU_MUL, act, ffn,
-                     fk::Warm{w_down, (size_t)g.hidden * ffn * esize(g.dtype)}, c->layer_scratch(pl));
+                     c->layer_scratch(pl));
   } else {
-    norm_and_project(c, s, resid, norm_w, normed, w_gate_up, 2 * ffn, rs.rows, fk::EPI_STORE, gate_up, 2 * ffn, fk::Warm(), c->layer_scratch(pl));
+    norm_and_project(c, s, resid, norm_w, normed, w_gate_up, 2 * ffn, rs.rows, fk::EPI_STORE, gate_up, 2 * ffn, c->layer_scratch(pl));
     { Timed t(c, s, FOCUS_KC_POINTWISE); fk::silu_mul(s, g.dtype, gate_up, act, ffn, rs.rows); }
   }
-  { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, act, w_down, g.hidden, ffn, rs.rows, fk::EPI_ADD_F32, resid, g.hidden, warm_after, c->layer_scratch(pl)); }
+  { Timed t(c, s, FOCUS_KC_GEMM); fk::gemm(s, g.dtype, act, w_down, g.hidden, ffn, rs.rows, fk::EPI_ADD_F32, resid, g.hidden, c->layer_scratch(pl)); }
 }
 
 // Mixture-of-experts feed-forward on normalised rows, added to the residual stream: router logits -> picks and weights ->
@@ -449,11 +458,11 @@ void moe_ffn(focus_ctx *c, hipStream_t s, int l, const RowSet &rs, float *resid,
   a.out_experts = c->route_by_row_id && c->out_route_experts ? c->out_route_experts + (size_t)l * plane : nullptr;
   a.out_weights = c->route_by_row_id && c->out_route_weights ? c->out_route_weights + (size_t)l * plane : nullptr;
   { Timed t(c, s, FOCUS_KC_GEMM);
-    fk::gemm(s, g.dtype, normed, c->w_router[l], g.n_experts, g.hidden, rs.rows, fk::EPI_STORE_F32, c->at<float>(pl.off_moe_logits), g.n_experts, fk::Warm(), c->layer_scratch(pl)); }
+    fk::gemm(s, g.dtype, normed, c->w_router[l], g.n_experts, g.hidden, rs.rows, fk::EPI_STORE_F32, c->at<float>(pl.off_moe_logits), g.n_experts, c->layer_scratch(pl)); }
   { Timed t(c, s, FOCUS_KC_ROUTE); fk::moe_route(s, a); fk::moe_group(s, a); }
   { Timed t(c, s, FOCUS_KC_EXPERTS); fk::moe_experts(s, a); }
   // the shared expert adds into the residual stream before the routed sum (both orders are the same sum)
-  if (g.shared_ffn > 0) swiglu_ffn(c, s, rs, nullptr, normed, c->w_shared_gate_up[l], c->w_shared_down[l], g.shared_ffn, resid, fk::Warm());
+  if (g.shared_ffn > 0) swiglu_ffn(c, s, rs, nullptr, normed, c->w_shared_gate_up[l], c->w_shared_down[l], g.shared_ffn, resid);
   { Timed t(c, s, FOCUS_KC_ROUTE); fk::moe_combine(s, a); }
 }
 
@@ -466,6 +475,7 @@ void order_sequences(focus_ctx *c, hipStream_t s, RowSet &rs) {
   fk::length_order(s, rs.n_seq, g.block_size, rs.ri.seq_slot, c->slots(), order, rs.cut, rs.cut, chunk);
   rs.order = order;
   rs.chunk = chunk;
+  expected_lengths(c, rs.n_seq, rs.ri.seq_slot, rs);
 }
 
 int check_batch(focus_ctx *ctx, int n_seq) {
@@ -538,6 +548,7 @@ int focus_init(const focus_config *cfg, const focus_weights *w, void *kv_pool, s
   c->plan = plan;
   c->ws = (char *)workspace;
   c->kv_pool = (char *)kv_pool;
+  c->slot_total.assign(cfg->max_batch, 0);
   c->embed = w->embed; c->lm_head = w->lm_head; c->final_norm = w->final_norm;
   c->attn_norm.assign(w->attn_norm, w->attn_norm + cfg->n_layers);
   c->w_qkv.assign(w->w_qkv, w->w_qkv + cfg->n_layers);
@@ -646,6 +657,7 @@ int focus_set_state(focus_ctx *ctx, int32_t slot, const focus_seq_state *st) {
     if (st->tokens[p] < 0 || st->tokens[p] >= ctx->cfg.vocab) return fail(ctx, FOCUS_EINVAL, "token id %d at position %d outside the vocabulary", st->tokens[p], p);
   HIP_TRY(ctx, hipDeviceSynchronize());
   if (st->prefix_len + B > ctx->max_total) ctx->max_total = st->prefix_len + B;
+  ctx->slot_total[slot] = st->prefix_len + B;
   HIP_TRY(ctx, hipMemcpy(s.prefix_len + slot, &st->prefix_len, 4, hipMemcpyHostToDevice));
   HIP_TRY(ctx, hipMemcpy(s.total_steps + slot, &st->total_steps, 4, hipMemcpyHostToDevice));
   HIP_TRY(ctx, hipMemcpy(s.token_sum + slot, &st->token_sum, 8, hipMemcpyHostToDevice));
@@ -700,6 +712,7 @@ int focus_prefill_kv(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int3
       if (prompt_tokens[i] < 0 || prompt_tokens[i] >= g.vocab) return fail(ctx, FOCUS_EINVAL, "prompt token %lld outside the vocabulary", i);
   }
   ctx->max_total = (max_len + B > ctx->max_total) ? max_len + B : ctx->max_total;
+  for (int b = 0; b < n_seq; ++b) ctx->slot_total[slots[b]] = lens[b] + B;
   fk::SlotState st = ctx->slots();
   int32_t *d_len = ctx->at<int32_t>(pl.off_prompt_len), *d_off = ctx->at<int32_t>(pl.off_prompt_off);
   int32_t *d_slots = ctx->at<int32_t>(pl.off_slot_list);
@@ -747,7 +760,7 @@ int focus_prefill_kv(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int3
         start += B;
       }
       const fk::AttnCut cut = attention_cut(ctx, last_start + B, nv, rows, B);
-      RowSet rs{{rows, total}, {row_map, nullptr, B}, nv, cu, B, order, cut, chunk, &lp, vst};
+      RowSet rs{{rows, total}, {row_map, nullptr, B}, nv, cu, B, order, cut, chunk, 0, 0, &lp, vst};
       fk::prefill_blocks(s, v0, nv, n_seq, B, d_slots, st, ctx->at<int32_t>(pl.off_prompt), d_off, d_len, vst, table_row, keep);
       fk::scan_compact(s, nv, B, keep, cu, row_map, total);
       if (g.dtype == FOCUS_BF16) fk::length_order(s, nv, B, nullptr, vst, order, cut, cut, chunk);
@@ -811,6 +824,8 @@ int focus_step(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int32_t *s
               attention_cut(ctx, max_total, n_seq, T0, B, g.importance_mode == 0), chunk};
   RowSet packed{{cap, total, ctx->hint_rows}, {row_map, seq_slot, B}, n_seq, cu, rows_per_seq, order,
                 attention_cut(ctx, max_total, n_seq, cap, rows_per_seq), chunk + 1};
+  expected_lengths(ctx, n_seq, seq_slot, packed);
+  full.mean_total = packed.mean_total; full.longest_total = packed.longest_total;
   { Timed t(ctx, s, FOCUS_KC_POINTWISE);
     if (dc) {
       fk::uncached_bits(s, n_seq, B, seq_slot, st, uncached);
@@ -875,7 +890,7 @@ int focus_step(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int32_t *s
                                         (size_t)ctx->plan.max_rows * g.vocab * 4, &conf_slots, o.logits);
   }
   if (!fused_conf)
-    norm_and_project(ctx, s, resid_p, norm_inside ? ctx->final_norm : nullptr, normed, ctx->lm_head, g.vocab, packed.rows, fk::EPI_STORE_F32, logits, g.vocab, fk::Warm(), ctx->scratch());
+    norm_and_project(ctx, s, resid_p, norm_inside ? ctx->final_norm : nullptr, normed, ctx->lm_head, g.vocab, packed.rows, fk::EPI_STORE_F32, logits, g.vocab, ctx->scratch());
   {
     Timed t(ctx, s, FOCUS_KC_DECODE);
     if (fused_conf) fk::confidence_from_partials(s, ctx->at<float>(pl.off_logits), conf_slots, packed.rows, conf, amax);

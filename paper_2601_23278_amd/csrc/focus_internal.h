@@ -92,39 +92,16 @@ bool gemm_fuses_silu_mul(int dtype, const void *A, const void *W, int N, int K, 
 void embed(hipStream_t s, int dtype, const void *table, int hidden, Rows rows, RowIndex ri, SlotState st,
            int mask_id, float *resid);
 void rmsnorm(hipStream_t s, int dtype, const float *x, const void *w, void *y, int hidden, float eps, Rows rows);
-// Memory the kernel may touch on the side so that the next kernel finds it in the memory-side cache (a hint: kernels
-// that cannot do it ignore it).
-struct Warm {
-  const void *ptr = nullptr;
-  size_t bytes = 0;
-};
 // Device memory a projection may use for the fp32 partial sums of a K-split launch (none: no such launches).
 struct Scratch {
   void *ptr = nullptr;
   size_t bytes = 0;
 };
 void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, Rows rows, int epilogue,
-          void *out, int ldo, Warm warm = Warm(), Scratch scratch = Scratch());
+          void *out, int ldo, Scratch scratch = Scratch());
 // RMSNorm of rows of the residual stream and a projection of the result in one launch; only where gemm_fuses_rmsnorm() (small fp32 models)
 bool gemm_fuses_rmsnorm(int dtype, const float *x, const void *norm_w, const void *W, int N, int K, int rows_cap);
 void gemm_of_rmsnorm(hipStream_t s, const float *x, const void *norm_w, float eps, const void *W, int N, int K, Rows rows, int epilogue, void *out, int ldo);
-// Warm-up helpers: one dword of every 128-byte line of workgroup `share`'s part of `shares`.  They return a value the caller must keep
-// alive (e.g. store it under a condition that never holds).
-__device__ __forceinline__ unsigned warm_share(const void *ptr, size_t bytes, long share, long shares, int n_threads) {
-  const size_t lines = (bytes + 127) / 128, per = (lines + shares - 1) / shares;
-  const size_t l0 = (size_t)share * per, l1 = l0 + per < lines ? l0 + per : lines;
-  unsigned acc = 0;
-  for (size_t l = l0 + threadIdx.x; l < l1; l += n_threads) acc ^= __builtin_nontemporal_load((const unsigned *)((const char *)ptr + l * 128));
-  return acc;
-}
-// For kernels with one-dimensional grids of short workgroups: the workgroups of the last round (the last min(grid, 256) in launch
-// order) share the work.
-__device__ __forceinline__ unsigned warm_touch(const void *ptr, size_t bytes, int n_threads) {
-  if (!ptr || !bytes) return 0;
-  const long n_groups = (long)gridDim.x, id = blockIdx.x;
-  const long shares = n_groups < 256 ? n_groups : 256, share = id - (n_groups - shares);
-  return share < 0 ? 0 : warm_share(ptr, bytes, share, shares, n_threads);
-}
 // Rotates q and k rows of the fused qkv buffer in place and stores k, v of every row into its cache slot.
 // n_seq, cu: the row range of every batch entry (rows cu[b] .. cu[b + 1]), or 0 / null when not known.
 void rope_kv_write(hipStream_t s, int dtype, void *qkv, int n_q_heads, Rows rows, RowIndex ri, SlotState st,
@@ -147,7 +124,7 @@ struct AttnArgs {
   int launch_splits;             // splits the launch has workgroups (and the partials room) for
   const int32_t *chunk;          // tokens of a split, written by length_order() from the lengths themselves
   const int32_t *order;          // batch entries sorted by descending prefix length (longest first), or null
-  Warm warm;                     // weights of the projection that follows (bf16 kernel only)
+  int mean_total, longest_total; // the host's idea of the sequences' lengths (0: none): decides how many workgroups run at once, nothing else
   // Eq. 2 fused into this pass (the layer below the eviction layer, whose attention runs over the whole block anyway): when not
   // null, the workgroup that holds a sequence's last K/V range also reduces the in-block score tile of its query heads to
   // imp_partial[b, h, j] (the layout importance() writes).  attention() says whether it did.

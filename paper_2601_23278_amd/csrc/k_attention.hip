@@ -205,12 +205,6 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
   unsigned char *const lds = IMP ? lds_imp : lds_fixed;
   const int Hkv = a.kv.n_kv_heads, Hq = a.n_q_heads, g = Hq / Hkv;
   const int groups = a.n_seq * Hkv, split = blockIdx.x / groups, group = blockIdx.x % groups;
-  if (split >= a.launch_splits) {                        // a workgroup beyond the attention's own: it only warms the next weights
-    const int n_warm = (int)gridDim.x - groups * a.launch_splits;
-    const unsigned acc = warm_share(a.warm.ptr, a.warm.bytes, (int)blockIdx.x - groups * a.launch_splits, n_warm, NW * 64);
-    if (acc == 0x9e3779b9u && a.n_seq < 0) ((unsigned *)a.out)[0] = acc;   // never true: keeps the loads
-    return;
-  }
   const int chunk = *a.chunk;
   const int bo = group / Hkv, hk = group % Hkv;
   const int b = a.order ? a.order[bo] : bo;
@@ -511,11 +505,6 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
       }
     }
   }
-  // the last workgroups to start (the shortest sequences), once through their own K/V, pull the next projection's
-  // weights into the memory-side cache: any earlier and the K/V stream would push them out again (workgroups without K/V that did it
-  // at once cost 23 contexts of up to 1500 tokens 3 us a launch and gained the projection nothing)
-  const unsigned warm_acc = (int)gridDim.x > groups * a.launch_splits ? 0u : warm_touch(a.warm.ptr, a.warm.bytes, NW * 64);
-  if (warm_acc == 0x9e3779b9u && a.n_seq < 0) ((unsigned *)a.out)[0] = warm_acc;   // never true: keeps the loads
 }
 
 // Merge of the K/V splits of one (row, head): out = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M).  Latency-bound: one thread per
@@ -634,19 +623,31 @@ template <typename T> static void launch_rows(hipStream_t s, const AttnArgs &a, 
   else run(narrow ? k_attn_row<T, 1> : k_attn_row<T, 2>, 256);
 }
 
+// Workgroups of one or two wavefronts that a compute unit runs at once, set by LDS that they ask for and do not use.  Four of one wavefront
+// stream faster than the five there is room for (256 sequences x 8 heads, up to 4096 tokens 411 -> 400 us; 1536 tokens each 270 -> 253).
+// Uncut sequences of uneven lengths that would all start at once are better run in two rounds: who ends early makes room for the next, and
+// no compute unit is left with one long sequence alone (us at four / two: 1024 groups, 512..4096 tokens 232 / 204, 256..2048 126 / 113;
+// 640 groups 173 / 153; log-uniform to 16000, 2048 groups 894 / 783).  Even or short ones are not (1024 groups of 1536 tokens 125 / 135,
+// 768 121 and 97; 100..300 tokens 34 / 39), and 1025 to 1536 groups make two rounds of three (1536 tokens each 207 -> 196, 256..2048 the same).
+static int attention_resident(int groups, const AttnArgs &a) {
+  if (a.launch_splits > 1 || a.mean_total <= 0) return 4;
+  if (groups > 512 && groups <= 1024) return a.mean_total >= 768 && a.longest_total >= 1.45 * a.mean_total ? 2 : 4;
+  if (groups > 1024 && groups <= 2048 && a.longest_total >= 2.5 * a.mean_total) return 2;
+  return groups > 1024 && groups <= 1536 ? 3 : 4;
+}
+template <int NW> static void launch_attn_few(hipStream_t s, dim3 grid, const AttnArgs &a) {
+  static const int pads[] = {49152, 20480, NW == 1 ? 8192 : 0};          // beside the 32 KB of the tiles: two, three, four of 160 KB
+  static const bool ready = hipFuncSetAttribute((const void *)k_attn_mfma<NW>, hipFuncAttributeMaxDynamicSharedMemorySize, pads[0]) == hipSuccess;
+  k_attn_mfma<NW><<<grid, NW * 64, ready ? pads[attention_resident(a.n_seq * a.kv.n_kv_heads, a) - 2] : 0, s>>>(a);
+}
+
 bool attention(hipStream_t s, const AttnArgs &a) {
   if (a.rows.cap <= 0 || a.n_seq <= 0) return false;
   const int g = a.n_q_heads / a.kv.n_kv_heads;
   const bool mfma = a.dtype == FOCUS_BF16 && a.kv.head_dim == 128 && a.kv.page_size == 64 && a.q_stride % 8 == 0 && a.part_o != nullptr;
   if (mfma) {
     const int R = a.max_rows_per_seq * g, nw = attention_wavefronts(R);
-    // One workgroup per (sequence, kv head, split), and, when these are too few to pull the next weights in on the side (less than one
-    // per CU), workgroups of their own for that, sixteen 128-byte lines per thread: the launch leaves most CUs and most of the memory
-    // bandwidth idle anyway.  (One request, 1149 tokens: 16 workgroups warming 33 MB of weights on the side took 160 us.)
-    const int n_attn = a.n_seq * a.kv.n_kv_heads * a.launch_splits;
-    const size_t lines = a.warm.ptr ? (a.warm.bytes + 127) / 128 : 0;
-    const int n_warm = n_attn < 256 ? (int)std::min<size_t>(512, (lines + nw * 64 * 16 - 1) / (nw * 64 * 16)) : 0;
-    const dim3 grid(n_attn + n_warm);
+    const dim3 grid(a.n_seq * a.kv.n_kv_heads * a.launch_splits);       // one workgroup per (sequence, kv head, split)
     bool fused = false;
     // importance rides along when the group size divides the 32 pairs of a wavefront (rows of one head are then the lanes with
     // equal lane % g) and the score patches fit the LDS
@@ -658,8 +659,8 @@ bool attention(hipStream_t s, const AttnArgs &a) {
       else fused = small ? launch_attn_imp<8, 32>(s, grid, a, g) : launch_attn_imp<8, 64>(s, grid, a, g);
     }
     if (!fused) {
-      if (nw == 1) k_attn_mfma<1><<<grid, 64, 0, s>>>(a);
-      else if (nw == 2) k_attn_mfma<2><<<grid, 128, 0, s>>>(a);
+      if (nw == 1) launch_attn_few<1>(s, grid, a);
+      else if (nw == 2) launch_attn_few<2>(s, grid, a);
       else if (nw == 4) k_attn_mfma<4><<<grid, 256, 0, s>>>(a);
       else k_attn_mfma<8><<<grid, 512, 0, s>>>(a);
     }

@@ -402,8 +402,8 @@ constexpr int kNonTemporal = 2;      // cache policy of a load (NT bit): what is
 // 8 rows 217 us, 232 with plain loads; 128 rows 233 and 248; with two and more rows of tiles it is the same or slower, 374 -> 382)
 template <int BM, int EPI, int BN = 256, bool ONE = false>
 __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W, int N, int K,
-                                                      Rows rows, void *out, int ldo, int tiles_m, int tiles_n, const void *warm,
-                                                      unsigned warm_bytes, int splits, size_t split_stride, float *logits) {
+                                                      Rows rows, void *out, int ldo, int tiles_m, int tiles_n, int splits,
+                                                      size_t split_stride, float *logits) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer-resource builtins exist in the device pass only
   // splits > 1: the K range is cut into `splits` parts, one workgroup each; part s writes its fp32 sums to
   // out + s * split_stride and a second kernel adds the parts in order (EPI is then EPI_STORE_F32 or EPI_PARTIAL_SILU)
@@ -423,8 +423,8 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__
   constexpr int L0 = (NI + 3) / 4, L1 = (NI - L0 + 2) / 3, L2 = (NI - L0 - L1 + 1) / 2, L3 = NI - L0 - L1 - L2;
   static_assert(L0 <= NMF && TM + TN <= NMF, "one load and one fragment read per MFMA at most");
   // Loads that may still be on their way at the barrier.  The slab that comes next was asked for in the window before this one, but with
-  // two stages its rows in this window: so those behind them, all of this window's or the weights, and the warm-up loads that end windows.
-  constexpr int FLY = SA > 2 ? NI + 2 : IB + 1;
+  // two stages its rows in this window: so those behind them, all of this window's or the weights.
+  constexpr int FLY = SA > 2 ? NI : IB;
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_pipe[];
   unsigned char *const lds = lds_pipe;
   const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
@@ -435,7 +435,6 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__
   const int per_xcd = (total + 7) / 8;
   const int work = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (blockIdx.x / 8 >= per_xcd || work >= total) return;
-  const int live_grid = per_xcd * 8;
   const int tile = work / splits, split = work % splits;
   constexpr int GROUP = 8;
   const int in_group = tile % (GROUP * tiles_n), first_m = (tile / (GROUP * tiles_n)) * GROUP;
@@ -465,23 +464,6 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__
     const int wrow = SILU_W ? ((r >> 5) & 1) * (N / 2) + n0 + (r / 64) * 32 + (r & 31) : n0 + r;
     vob[q] = (unsigned)wrow * (unsigned)K * 2u + k_base + c * 16;
   }
-  // Optional: touch `warm_bytes` bytes at `warm` (the weights of the next projection) so that they wait in the memory-side
-  // cache; weights are read once per step and a projection that finds them in HBM runs up to 1.5 times longer.  A
-  // workgroup's share is spread over its slabs: on a "hit" slab each wavefront reads one dword of 64
-  // consecutive 128-byte lines.  The loads go through a descriptor of exactly warm_bytes, so shares beyond the end (and
-  // all of them when there is nothing to warm) are out of range and move no data.  A result is folded into a dummy value
-  // one slab later, when the load has long returned, so nothing waits for it.
-  __amdgpu_buffer_rsrc_t rs_p = __builtin_amdgcn_make_buffer_rsrc((void *)warm, 0, warm_bytes, 0x00020000);
-  // only the workgroups of the last round (one workgroup per CU) take part: what earlier rounds fetch is pushed out of the
-  // cache again by the kernel's own traffic before the next kernel starts
-  const int warm_groups = min(live_grid, 256), warm_rank = (int)blockIdx.x - (live_grid - warm_groups);
-  constexpr unsigned HIT = NW * 8192;   // bytes per hit: NW wavefronts x 64 lines
-  const unsigned warm_hits = warm_rank < 0 ? 0u : ((warm_bytes + warm_groups - 1) / warm_groups + HIT - 1) / HIT;
-  const int warm_stride = warm_hits ? max(1, nk / (int)warm_hits) : 1;
-  unsigned warm_off = (unsigned)max(warm_rank, 0) * (warm_hits * HIT), warm_left = warm_hits;
-  int warm_next = 0;
-  unsigned warm_sink = 0, warm_even = 0, warm_odd = 0;
-  const unsigned warm_lane = lane * 128 + wave * 8192;
   // load instruction i (A: 0 .. IA-1, W: IA .. NI-1) of the slabs at byte offsets so_a, so_w into the stages at byte offsets st_a, st_w
   auto gl = [&](int i, unsigned so_a, int st_a, unsigned so_w, int st_w) {
     if (i < IA)
@@ -513,19 +495,16 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__
     else fb[slot][f < TM ? 0 : f - TM] = *(const bf16x8 *)(pb[ks] + st_w + (f < TM ? 0 : f - TM) * 4096);
   };
   auto slab_off = [&](int kt) { return kt < nk ? (unsigned)kt * (BK * 2) : 0x80000000u; };   // beyond the last slab nothing is moved
-  // before the loop: the rows of slabs 0 .. SA - 2 and the weights of slabs 0 .. SW - 2, a warm-up load that moves nothing as at the end of
-  // every window (the waits count it), and the first k-step's share of the window that ends at the first barrier
+  // before the loop: the rows of slabs 0 .. SA - 2 and the weights of slabs 0 .. SW - 2, and the first k-step's share of the window that
+  // ends at the first barrier
 #pragma unroll
   for (int q = 0; q < SW - 1; ++q)
 #pragma unroll
     for (int i = 0; i < NI; ++i)
       if (i >= IA || q < SA - 1) gl(i, slab_off(q), q * ASTAGE, slab_off(q), q * WSTAGE);
-  __builtin_amdgcn_sched_barrier(0);
-  warm_odd = __builtin_amdgcn_raw_buffer_load_b32(rs_p, warm_lane, 0x80000000u, 0);
-  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int i = 0; i < L0; ++i) gl(i, slab_off(SA - 1), (SA - 1) * ASTAGE, slab_off(SW - 1), (SW - 1) * WSTAGE);
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(L0 + 1 + (SW - 2) * IB + (SA - 2) * IA));   // slab 0 has landed
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(L0 + (SW - 2) * IB + (SA - 2) * IA));   // slab 0 has landed
   asm volatile("s_barrier" ::: "memory");
 #pragma unroll
   for (int s = 0; s < TM + TN; ++s) rd(s, 0, 0, 0, 0);
@@ -545,37 +524,21 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__
   }
   int ra = 0, rw = 0;                                       // stages of the slab that is multiplied
   int la = (SA - 1) * ASTAGE, lw = (SW - 1) * WSTAGE;       // stages that are filled: the ones the slab before it has left
-  // one slab; its warm-up load goes out behind all loads of its window, and what it returned is folded two windows later
-#define FK_SLAB(kt, warm_value)                                                                         \
-  {                                                                                                     \
-    unsigned so_a = slab_off((kt) + SA - 1), so_w = slab_off((kt) + SW - 1);                            \
-    FK_STEP(0, 1, ra, rw, L1, L0, so_a, la, so_w, lw)                                                   \
-    FK_STEP(1, 2, ra, rw, L2, L0 + L1, so_a, la, so_w, lw)                                              \
-    FK_STEP(0, 3, ra, rw, L3, L0 + L1 + L2, so_a, la, so_w, lw)                                         \
-    {                                                                                                   \
-      const bool hit = (kt) == warm_next && warm_left > 0;                                              \
-      const unsigned so = hit ? warm_off : 0x80000000u;                                                 \
-      warm_sink ^= warm_value;                                                                          \
-      warm_value = __builtin_amdgcn_raw_buffer_load_b32(rs_p, warm_lane, so, 0);                        \
-      warm_off += hit ? HIT : 0u; warm_left -= hit ? 1u : 0u; warm_next += hit ? warm_stride : 0;       \
-      __builtin_amdgcn_sched_barrier(0);                                                                \
-    }                                                                                                   \
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(FLY));   /* this wavefront's part of the next slab has landed */ \
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   /* ... and everyone's; everyone has read all of this slab */ \
-    la = ra; lw = rw;                                                                                   \
-    ra = ra == (SA - 1) * ASTAGE ? 0 : ra + ASTAGE;                                                     \
-    rw = rw == (SW - 1) * WSTAGE ? 0 : rw + WSTAGE;                                                     \
-    so_a = slab_off((kt) + SA); so_w = slab_off((kt) + SW);                                             \
-    FK_STEP(1, 0, ra, rw, L0, 0, so_a, la, so_w, lw)                                                    \
+  for (int kt = 0; kt < nk; ++kt) {
+    unsigned so_a = slab_off(kt + SA - 1), so_w = slab_off(kt + SW - 1);
+    FK_STEP(0, 1, ra, rw, L1, L0, so_a, la, so_w, lw)
+    FK_STEP(1, 2, ra, rw, L2, L0 + L1, so_a, la, so_w, lw)
+    FK_STEP(0, 3, ra, rw, L3, L0 + L1 + L2, so_a, la, so_w, lw)
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(FLY));                     // this wavefront's part of the next slab has landed
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // ... and everyone's; everyone has read all of this slab
+    la = ra; lw = rw;
+    ra = ra == (SA - 1) * ASTAGE ? 0 : ra + ASTAGE;
+    rw = rw == (SW - 1) * WSTAGE ? 0 : rw + WSTAGE;
+    so_a = slab_off(kt + SA); so_w = slab_off(kt + SW);
+    FK_STEP(1, 0, ra, rw, L0, 0, so_a, la, so_w, lw)
   }
-  for (int kt = 0; kt < nk; kt += 2) {
-    FK_SLAB(kt, warm_even)
-    FK_SLAB(kt + 1, warm_odd)
-  }
-#undef FK_SLAB
 #undef FK_STEP
   __builtin_amdgcn_s_waitcnt(0x0F70);
-  if ((warm_sink ^ warm_even ^ warm_odd) == 0x9e3779b9u && warm_bytes == 1) ((unsigned *)out)[0] = warm_sink;   // keeps the warm-up loads alive; never true
   // epilogue: accumulator register r of lane l is C[8 * (r / 4) + 4 * (l / 32) + r % 4][l % 32] of its 32x32 tile.
   // A tile that lies inside the matrix takes the path without per-element bounds checks.
   const bool inside = m0 + BM <= M && n0 + (SILU_W ? BN / 2 : BN) <= (SILU_W ? N / 2 : N);
@@ -777,12 +740,12 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float *__restrict__
 }
 
 template <int BM, int EPI, int BN = 256, bool ONE = false>
-static bool launch_pipe(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, int K, Rows rows, void *out, int ldo, Warm warm, int splits = 1,
+static bool launch_pipe(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, int K, Rows rows, void *out, int ldo, int splits = 1,
                         size_t split_stride = 0, float *logits = nullptr) {
   constexpr int kLds = (pipe_stages_a(BM) * BM + kPipeStagesW * BN) * 128;
   constexpr bool SILU_W = EPI == EPI_SILU_MUL || EPI == EPI_PARTIAL_SILU;
   if constexpr (!ONE && BM <= 128 && (EPI == EPI_CONF || EPI == EPI_CONF_LOGITS || EPI == EPI_STORE_F32 || EPI == EPI_PARTIAL_SILU))      // projections of few rows
-    if (rows.expected() <= BM) return launch_pipe<BM, EPI, BN, true>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride, logits);
+    if (rows.expected() <= BM) return launch_pipe<BM, EPI, BN, true>(s, a, w, N, K, rows, out, ldo, splits, split_stride, logits);
   static bool ready = false;             // the dynamic LDS size has to be allowed once per kernel
   if (!ready) {
     if (hipFuncSetAttribute((const void *)k_gemm_pipe<BM, EPI, BN, ONE>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess) return false;
@@ -790,23 +753,22 @@ static bool launch_pipe(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, 
   }
   const int tiles_m = (rows.cap + BM - 1) / BM, tiles_n = SILU_W ? (N / 2 + BN / 2 - 1) / (BN / 2) : (N + BN - 1) / BN;
   const int grid = ((tiles_m * tiles_n * splits + 7) / 8) * 8;
-  k_gemm_pipe<BM, EPI, BN, ONE><<<grid, 256, kLds, s>>>(a, w, N, K, rows, out, ldo, tiles_m, tiles_n, warm.ptr, (unsigned)std::min<size_t>(warm.bytes, 0x7fffffffu),
-                                                   splits, split_stride, logits);
+  k_gemm_pipe<BM, EPI, BN, ONE><<<grid, 256, kLds, s>>>(a, w, N, K, rows, out, ldo, tiles_m, tiles_n, splits, split_stride, logits);
   return true;
 }
 
 template <int BM>
-static bool launch_pipe_epi(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, int K, Rows rows, int epi, void *out, int ldo, Warm warm, int splits,
+static bool launch_pipe_epi(hipStream_t s, const bf16_t *a, const bf16_t *w, int N, int K, Rows rows, int epi, void *out, int ldo, int splits,
                             size_t split_stride, float *logits) {
   switch (epi) {
-    case EPI_STORE: return launch_pipe<BM, EPI_STORE>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
-    case EPI_ADD_F32: return launch_pipe<BM, EPI_ADD_F32>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
-    case EPI_STORE_F32: return launch_pipe<BM, EPI_STORE_F32>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
-    case EPI_SILU_MUL: return launch_pipe<BM, EPI_SILU_MUL>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
-    case EPI_PARTIAL_SILU: return launch_pipe<BM, EPI_PARTIAL_SILU>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
-    case EPI_CONF: return launch_pipe<BM, EPI_CONF>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride);
+    case EPI_STORE: return launch_pipe<BM, EPI_STORE>(s, a, w, N, K, rows, out, ldo, splits, split_stride);
+    case EPI_ADD_F32: return launch_pipe<BM, EPI_ADD_F32>(s, a, w, N, K, rows, out, ldo, splits, split_stride);
+    case EPI_STORE_F32: return launch_pipe<BM, EPI_STORE_F32>(s, a, w, N, K, rows, out, ldo, splits, split_stride);
+    case EPI_SILU_MUL: return launch_pipe<BM, EPI_SILU_MUL>(s, a, w, N, K, rows, out, ldo, splits, split_stride);
+    case EPI_PARTIAL_SILU: return launch_pipe<BM, EPI_PARTIAL_SILU>(s, a, w, N, K, rows, out, ldo, splits, split_stride);
+    case EPI_CONF: return launch_pipe<BM, EPI_CONF>(s, a, w, N, K, rows, out, ldo, splits, split_stride);
     case EPI_CONF_LOGITS:
-      if constexpr (BM < 256) return launch_pipe<BM, EPI_CONF_LOGITS>(s, a, w, N, K, rows, out, ldo, warm, splits, split_stride, logits);
+      if constexpr (BM < 256) return launch_pipe<BM, EPI_CONF_LOGITS>(s, a, w, N, K, rows, out, ldo, splits, split_stride, logits);
       else return false;
   }
   return false;
@@ -815,22 +777,22 @@ static bool launch_pipe_epi(hipStream_t s, const bf16_t *a, const bf16_t *w, int
 // Shape of a pipelined launch: tile height, tile width and parts of K.
 struct PipeShape { int bm, bn, splits; };
 
-static bool launch_shape(hipStream_t s, PipeShape p, const void *A, const void *W, int N, int K, Rows rows, int epi, void *out, int ldo, Warm warm,
+static bool launch_shape(hipStream_t s, PipeShape p, const void *A, const void *W, int N, int K, Rows rows, int epi, void *out, int ldo,
                          size_t split_stride = 0, float *logits = nullptr) {
   const bf16_t *a = (const bf16_t *)A, *w = (const bf16_t *)W;
   if (p.bn == 192)
-    return epi == EPI_STORE     ? launch_pipe<256, EPI_STORE, 192>(s, a, w, N, K, rows, out, ldo, warm)
-           : epi == EPI_ADD_F32 ? launch_pipe<256, EPI_ADD_F32, 192>(s, a, w, N, K, rows, out, ldo, warm)
-                                : launch_pipe<256, EPI_STORE_F32, 192>(s, a, w, N, K, rows, out, ldo, warm);
+    return epi == EPI_STORE     ? launch_pipe<256, EPI_STORE, 192>(s, a, w, N, K, rows, out, ldo)
+           : epi == EPI_ADD_F32 ? launch_pipe<256, EPI_ADD_F32, 192>(s, a, w, N, K, rows, out, ldo)
+                                : launch_pipe<256, EPI_STORE_F32, 192>(s, a, w, N, K, rows, out, ldo);
   switch (p.bm) {
-    case 64: return launch_pipe_epi<64>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
-    case 96: return launch_pipe_epi<96>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
-    case 128: return launch_pipe_epi<128>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
-    case 160: return launch_pipe_epi<160>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
-    case 192: return launch_pipe_epi<192>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
-    case 224: return launch_pipe_epi<224>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
+    case 64: return launch_pipe_epi<64>(s, a, w, N, K, rows, epi, out, ldo, p.splits, split_stride, logits);
+    case 96: return launch_pipe_epi<96>(s, a, w, N, K, rows, epi, out, ldo, p.splits, split_stride, logits);
+    case 128: return launch_pipe_epi<128>(s, a, w, N, K, rows, epi, out, ldo, p.splits, split_stride, logits);
+    case 160: return launch_pipe_epi<160>(s, a, w, N, K, rows, epi, out, ldo, p.splits, split_stride, logits);
+    case 192: return launch_pipe_epi<192>(s, a, w, N, K, rows, epi, out, ldo, p.splits, split_stride, logits);
+    case 224: return launch_pipe_epi<224>(s, a, w, N, K, rows, epi, out, ldo, p.splits, split_stride, logits);
   }
-  return launch_pipe_epi<256>(s, a, w, N, K, rows, epi, out, ldo, warm, p.splits, split_stride, logits);
+  return launch_pipe_epi<256>(s, a, w, N, K, rows, epi, out, ldo, p.splits, split_stride, logits);
 }
 
 // The shape with the least estimated time.  A compute unit takes one tile at a time and spends about 0.30 + 0.0046 BM us (0.08 more at
@@ -893,7 +855,7 @@ bool gemm_conf_partials(hipStream_t s, int dtype, const void *A, const void *W, 
   const int slots = (N + 255) / 256 * (p.bm == 256 ? 2 : 4);       // one per wavefront column
   if ((size_t)rows.cap * slots * 12 > part_bytes) return false;
   *n_slots = slots;
-  return launch_shape(s, p, A, W, N, K, rows, logits ? EPI_CONF_LOGITS : EPI_CONF, part, slots, Warm(), 0, logits);
+  return launch_shape(s, p, A, W, N, K, rows, logits ? EPI_CONF_LOGITS : EPI_CONF, part, slots, 0, logits);
 }
 
 bool gemm_fuses_silu_mul(int dtype, const void *A, const void *W, int N, int K, int rows_cap) {
@@ -909,7 +871,7 @@ void gemm_of_rmsnorm(hipStream_t s, const float *x, const void *norm_w, float ep
 }
 
 void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, Rows rows, int epilogue,
-          void *out, int ldo, Warm warm, Scratch scratch) {
+          void *out, int ldo, Scratch scratch) {
   if (rows.cap <= 0) return;
   if (dtype == FOCUS_F32) {
     if (!takes_f32(A, W, N, K, rows.cap)) launch_valu<float>(s, A, W, N, K, rows, epilogue, out, ldo);
@@ -929,7 +891,7 @@ void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, 
       (size_t)(K / 1024) * rows.cap * N * 4 <= scratch.bytes) {
     const bool silu = epilogue == EPI_SILU_MUL;
     const int parts = K / 1024;
-    if (launch_shape(s, PipeShape{64, 256, parts}, A, W, N, K, rows, silu ? EPI_PARTIAL_SILU : EPI_STORE_F32, scratch.ptr, N, Warm(), (size_t)rows.cap * N)) {
+    if (launch_shape(s, PipeShape{64, 256, parts}, A, W, N, K, rows, silu ? EPI_PARTIAL_SILU : EPI_STORE_F32, scratch.ptr, N, (size_t)rows.cap * N)) {
       launch_reduce(s, N, rows, epilogue, out, ldo, parts, (const float *)scratch.ptr);
       return;
     }
@@ -949,8 +911,8 @@ void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, 
   if (pipe) {
     const PipeShape p = pipe_shape(N, K, rows, epilogue, scratch.ptr ? scratch.bytes : 0);
     if (p.splits == 1) {
-      if (launch_shape(s, p, A, W, N, K, rows, epilogue, out, ldo, warm)) return;
-    } else if (launch_shape(s, p, A, W, N, K, rows, epilogue == EPI_SILU_MUL ? EPI_PARTIAL_SILU : EPI_STORE_F32, scratch.ptr, N, warm, (size_t)rows.cap * N)) {
+      if (launch_shape(s, p, A, W, N, K, rows, epilogue, out, ldo)) return;
+    } else if (launch_shape(s, p, A, W, N, K, rows, epilogue == EPI_SILU_MUL ? EPI_PARTIAL_SILU : EPI_STORE_F32, scratch.ptr, N, (size_t)rows.cap * N)) {
       launch_reduce(s, N, rows, epilogue, out, ldo, p.splits, (const float *)scratch.ptr);
       return;
     }

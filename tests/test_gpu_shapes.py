@@ -18,6 +18,15 @@ def test_attention_context_splits_and_their_merge(prefix, batch, block):
     lengths = dict(prefix_lo=prefix, prefix_hi=prefix, prefix_dist="fixed") if batch == 1 else dict(prefix_lo=5, prefix_hi=prefix)
     compare_steps(small_bf16(batch=batch, n_q_heads=4, n_kv_heads=1, n_layers=3, block_size=block, steps=1, **lengths), 1, 2e-2, exact=False)
 
+@pytest.mark.parametrize("kv_heads,lo,hi,rows", [(65, 500, 1500, 3), (65, 900, 900, 3), (120, 300, 1300, 3), (130, 130, 3000, 2), (65, 500, 1500, 30)])
+def test_attention_rounds_of_uneven_sequences(kv_heads, lo, hi, rows):
+    """520, 960 and 1040 (sequence, kv head) pairs, uneven and even, one and two wavefronts each: two, three and four workgroups per
+    compute unit."""
+    wl = small_bf16(batch=8, n_q_heads=kv_heads, n_kv_heads=kv_heads, hidden=256, ffn=256, vocab=512, mask_token_id=511, n_layers=2, block_size=32,
+                    keep_ratio=rows / 32, prefix_lo=lo, prefix_hi=hi, steps=1)
+    compare_steps(wl, 1, 2e-2, exact=False)
+
+
 @pytest.mark.parametrize("block,prefix", [(32, 1100), (16, 1000)])
 def test_a_step_does_not_depend_on_what_the_context_held_before(block, prefix):
     """Bitwise: one request in a fresh context; after a long request was in another slot; after many attempts to finalise its block, which
