@@ -366,7 +366,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
           pf[2 * u + (r >> 3)][r & 7] = (bf16_t)p;
         }
       l = l * corr + ls;
-      // the 64 output accumulators are rescaled only when some row's maximum moved (after the first tiles it rarely does)
+      // the 64 output accumulators are rescaled only when some row's maximum moved (tile t moves one of 32 with probability 1 - (1 - 1/t)^32)
       if (__builtin_amdgcn_ballot_w64(corr != 1.0f) != 0) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
