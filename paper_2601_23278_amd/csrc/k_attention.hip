@@ -709,6 +709,7 @@ __global__ __launch_bounds__(256) void k_importance(ImpArgs a) {
   const int stride = (Hq + 2 * Hkv) * D;
   const int r0 = a.cu[b], nq = min(a.cu[b + 1] - r0, B);
   const T *base = (const T *)a.qkv + (size_t)r0 * stride;
+#pragma unroll 4
   for (int i = threadIdx.x; i < B * D; i += 256) {
     int j = i / D, d = i % D;
     ks[j * (D + 1) + d] = to_f(block_key_row<T>(a, slot, hk, j)[d]);
@@ -721,44 +722,66 @@ __global__ __launch_bounds__(256) void k_importance(ImpArgs a) {
     const int i = pair / B, j = pair % B;
     const T *qi = base + (size_t)i * stride + (size_t)h * D;
     const float *kj = ks + j * (D + 1);
-    constexpr int VE = 16 / sizeof(T);            // the query row is read in 16-byte pieces
+    constexpr int VE = 16 / sizeof(T), NP = 64 / VE;            // the query row is read in 16-byte pieces, 64 values (D is a multiple) at a time
     float acc = 0.f;
-    for (int d0 = 0; d0 < D; d0 += VE) {
-      T qv[VE];
-      *(u32x4 *)qv = *(const u32x4 *)(qi + d0);
+    for (int d0 = 0; d0 < D; d0 += 64) {
+      u32x4 piece[NP];
 #pragma unroll
-      for (int e = 0; e < VE; ++e) acc += to_f(qv[e]) * kj[d0 + e];
+      for (int v = 0; v < NP; ++v) piece[v] = *(const u32x4 *)(qi + d0 + v * VE);
+#pragma unroll
+      for (int v = 0; v < NP; ++v) {
+        T qv[VE];
+        __builtin_memcpy(qv, &piece[v], 16);
+#pragma unroll
+        for (int e = 0; e < VE; ++e) acc += to_f(qv[e]) * kj[d0 + v * VE + e];
+      }
     }
     S[i][j] = acc * scale;
   }
   __syncthreads();
   if ((int)threadIdx.x < nq) {
     const int row = threadIdx.x;
+    // sixteen values of the row at a time, so that reads and exponentials lie side by side; the sums keep their order (with the query row in
+    // pieces of 64 values, above: 16 x 16 scores of 64-wide heads 7.1 -> 6.1 us)
+    constexpr int U = 16;
     float m = -INFINITY;                        // max of the pooled row equals max of the row
-    for (int j = 0; j < B; ++j) m = fmaxf(m, S[row][j]);
-    float sum = 0.f;
-    {
-      float a = -INFINITY, c0 = S[row][0];
-      for (int j = 0; j < B; ++j) {
-        float nx = (j + 1 < B) ? S[row][j + 1] : -INFINITY;
-        float pooled = pool_k == 3 ? fmaxf(fmaxf(a, c0), nx) : c0;
-        sum += __expf(pooled - m);
-        a = c0; c0 = nx;
-      }
+    for (int j0 = 0; j0 < B; j0 += U) {
+      float v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = S[row][min(j0 + u, B - 1)];
+#pragma unroll
+      for (int u = 0; u < U; ++u) m = fmaxf(m, v[u]);
     }
-    float inv = 1.0f / sum;
-    float a = -INFINITY, c0 = S[row][0];
-    for (int j = 0; j < B; ++j) {
-      float nx = (j + 1 < B) ? S[row][j + 1] : -INFINITY;
-      float pooled = pool_k == 3 ? fmaxf(fmaxf(a, c0), nx) : c0;
-      S[row][j] = __expf(pooled - m) * inv;
-      a = c0; c0 = nx;
+    float sum = 0.f;
+    auto exps = [&](int j0, float before, float (&ex)[U]) {     // of the pooled values j0 ..; before: the value left of them
+      float v[U + 1];
+#pragma unroll
+      for (int u = 0; u <= U; ++u) v[u] = j0 + u < B ? S[row][j0 + u] : -INFINITY;
+#pragma unroll
+      for (int u = 0; u < U; ++u) ex[u] = __expf((pool_k == 3 ? fmaxf(fmaxf(u > 0 ? v[u - 1] : before, v[u]), v[u + 1]) : v[u]) - m);
+      return v[U - 1];
+    };
+    float before = -INFINITY, ex[U];
+    for (int j0 = 0; j0 < B; j0 += U) {
+      before = exps(j0, before, ex);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (j0 + u < B) sum += ex[u];
+    }
+    const float inv = 1.0f / sum;
+    before = -INFINITY;
+    for (int j0 = 0; j0 < B; j0 += U) {
+      if (B > U) before = exps(j0, before, ex);                 // (a block of up to sixteen still has them)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (j0 + u < B) S[row][j0 + u] = ex[u] * inv;
     }
   }
   __syncthreads();
   if ((int)threadIdx.x < B) {
     const int j = threadIdx.x;
     float col = 0.f;
+#pragma unroll 8
     for (int ii = 0; ii < nq; ++ii) col += S[ii][j];
     partial[((size_t)b * Hq + h) * B + j] = col;
   }
