@@ -351,7 +351,7 @@ fk::AttnCut attention_cut(const focus_ctx *c, int max_total, int n_seq, int rows
 void norm_and_project(focus_ctx *c, hipStream_t s, const float *resid, const void *norm_w, void *normed, const void *w, int n, fk::Rows rows, int epilogue, void *out,
                       int ldo, fk::Scratch scratch) {
   const focus_config &g = c->cfg;
-  if (norm_w && fk::gemm_fuses_rmsnorm(g.dtype, resid, norm_w, w, n, g.hidden, rows.cap)) {
+  if (norm_w && fk::gemm_fuses_rmsnorm(g.dtype, resid, norm_w, w, n, g.hidden, rows.cap, epilogue)) {
     Timed t(c, s, FOCUS_KC_GEMM);
     fk::gemm_of_rmsnorm(s, resid, norm_w, g.rms_eps, w, n, g.hidden, rows, epilogue, out, ldo);
     return;
@@ -878,7 +878,7 @@ int focus_step(focus_ctx *ctx, void *hip_stream, int32_t n_seq, const int32_t *s
 
   // decode and verify
   void *normed = ctx->at<char>(pl.off_normed);
-  const bool norm_inside = fk::gemm_fuses_rmsnorm(g.dtype, resid_p, ctx->final_norm, ctx->lm_head, g.vocab, g.hidden, packed.rows.cap);
+  const bool norm_inside = fk::gemm_fuses_rmsnorm(g.dtype, resid_p, ctx->final_norm, ctx->lm_head, g.vocab, g.hidden, packed.rows.cap, fk::EPI_STORE_F32);
   if (!norm_inside) { Timed t(ctx, s, FOCUS_KC_POINTWISE); fk::rmsnorm(s, g.dtype, resid_p, ctx->final_norm, normed, g.hidden, g.rms_eps, packed.rows); }
   // the projection reduces every row to (max, sum exp, arg-max) triples per column range in its epilogue, and without a logits output the
   // logits never reach memory; the triples take the place of the logits in the workspace

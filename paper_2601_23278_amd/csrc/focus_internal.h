@@ -100,7 +100,7 @@ struct Scratch {
 void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, Rows rows, int epilogue,
           void *out, int ldo, Scratch scratch = Scratch());
 // RMSNorm of rows of the residual stream and a projection of the result in one launch; only where gemm_fuses_rmsnorm() (small fp32 models)
-bool gemm_fuses_rmsnorm(int dtype, const float *x, const void *norm_w, const void *W, int N, int K, int rows_cap);
+bool gemm_fuses_rmsnorm(int dtype, const float *x, const void *norm_w, const void *W, int N, int K, int rows_cap, int epilogue);
 void gemm_of_rmsnorm(hipStream_t s, const float *x, const void *norm_w, float eps, const void *W, int N, int K, Rows rows, int epilogue, void *out, int ldo);
 // Rotates q and k rows of the fused qkv buffer in place and stores k, v of every row into its cache slot.
 // n_seq, cu: the row range of every batch entry (rows cu[b] .. cu[b + 1]), or 0 / null when not known.

@@ -74,18 +74,19 @@ static void launch_valu(hipStream_t s, const void *A, const void *W, int N, int 
 // ---------------------------------------------------------------------------------------------
 // fp32 on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 products, fp32 sums).  The fp32 models are small, so a launch is bound by
 // latency: 64 x 64 tiles gave 64 rows x 256 columns four workgroups that walked K = 1024 alone (65 us).  Here a tile is 16 rows x 16
-// columns and the workgroup's wavefronts share its K: wavefront w takes the 16-wide K pieces w, w + NW, ..., four in flight, straight from
-// global memory (a 16-byte load per operand feeds four products; both operands permute k alike), and the partial tiles are added in
-// wavefront order through LDS: 5.2 us.
+// columns and the workgroup's wavefronts share its K: wavefront w takes the 16-wide K pieces w, w + NW, ..., U = four in flight, straight
+// from global memory (a 16-byte load per operand feeds four products; both operands permute k alike), and the partial tiles are added in
+// wavefront order through LDS: 5.2 us.  (Eight in flight hold twice the registers: 512 rows of a 512-wide model 985 us a step, 863 with four.)
 // SiLU*up: the workgroup computes the gate and the up tile of the same columns and stores silu(gate) * up.
 // NORM: A holds rows of the residual stream and the product is that of their RMSNorm: each workgroup first adds up the squares of its rows
-// (for 256 columns in the order of k_rmsnorm, so that the sums are the same bit for bit) and scales the rows it holds in registers.  The
-// norm's own launch, 2.8 to 3.5 us in a chain of such launches, is gone; these take up to 0.5 us more.
+// (for 256 columns in the order of k_rmsnorm, so that the sums are the same bit for bit) and scales the rows it holds in registers, so it
+// has to hold all of K at once: NW * U pieces.  The norm's own launch, 2.8 to 3.5 us in a chain of such launches, is gone; what every
+// workgroup does again for its rows decides whether that pays (gemm_fuses_rmsnorm).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-template <int NW, int EPI, bool NORM>
+template <int NW, int U, int EPI, bool NORM>
 __global__ __launch_bounds__(NW * 64) void k_gemm_f32(const float *__restrict__ A, const float *__restrict__ W, int N, int K, Rows rows,
                                                       float *out, int ldo, const float *__restrict__ norm_w, float eps) {
-  constexpr int NB = EPI == EPI_SILU_MUL ? 2 : 1, U = NW;        // (K = 1024 with eight wavefronts: one trip)
+  constexpr int NB = EPI == EPI_SILU_MUL ? 2 : 1;
   __shared__ f32x4 part[NB][NW][64];
   __shared__ float squares[NORM ? NW : 1][64];
   const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
@@ -118,34 +119,27 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_f32(const float *__restrict__ 
   loads_asked_for();
   float inv = 0.f;                                        // of row r
   if (NORM) {
-    float ss = 0.f;
-    for (int c = wave; c * 16 < K; c += NW * U) {
-      if (c != wave) load(c);
-      float q[U];
+    float q[U], qw[NW];
 #pragma unroll
-      for (int u = 0; u < U; ++u) q[u] = va[u][0] * va[u][0] + va[u][1] * va[u][1] + va[u][2] * va[u][2] + va[u][3] * va[u][3];
+    for (int u = 0; u < U; ++u) q[u] = va[u][0] * va[u][0] + va[u][1] * va[u][1] + va[u][2] * va[u][2] + va[u][3] * va[u][3];
 #pragma unroll
-      for (int h = U / 2; h > 0; h /= 2)
+    for (int h = U / 2; h > 0; h /= 2)
 #pragma unroll
-        for (int u = 0; u < h; ++u) q[u] += q[u + h];
-      ss += q[0];
-    }
-    squares[wave][lane] = ss;
+      for (int u = 0; u < h; ++u) q[u] += q[u + h];
+    squares[wave][lane] = q[0];
     __syncthreads();
-    float q[NW];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) q[w] = squares[w][lane];
+    for (int w = 0; w < NW; ++w) qw[w] = squares[w][lane];
 #pragma unroll
     for (int h = NW / 2; h > 0; h /= 2)
 #pragma unroll
-      for (int w = 0; w < h; ++w) q[w] += q[w + h];
-    ss = q[0] + __shfl_xor(q[0], 32);
+      for (int w = 0; w < h; ++w) qw[w] += qw[w + h];
+    float ss = qw[0] + __shfl_xor(qw[0], 32);
     ss += __shfl_xor(ss, 16);
     inv = 1.0f / sqrtf(ss / (float)K + eps);
   }
-  const bool one_trip = K <= NW * U * 16;                 // (more than one: the squares have used the registers)
   for (int c = wave; c * 16 < K; c += NW * U) {
-    if (c != wave || (NORM && !one_trip)) load(c);
+    if (c != wave) load(c);
     if (NORM)
 #pragma unroll
       for (int u = 0; u < U; ++u)
@@ -179,18 +173,13 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_f32(const float *__restrict__ 
   }
 }
 
-template <int NW, bool NORM>
-static void launch_f32(hipStream_t s, const float *A, const float *W, int N, int K, Rows rows, int epi, float *out, int ldo, const float *norm_w, float eps) {
-  const dim3 grid(((epi == EPI_SILU_MUL ? N / 2 : N) + 15) / 16, (rows.cap + 15) / 16);
-  if (epi == EPI_SILU_MUL) k_gemm_f32<NW, EPI_SILU_MUL, NORM><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo, norm_w, eps);
-  else if (epi == EPI_ADD_F32) k_gemm_f32<NW, EPI_ADD_F32, NORM><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo, norm_w, eps);
-  else k_gemm_f32<NW, EPI_STORE_F32, NORM><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo, norm_w, eps);
-}
-template <bool NORM>
+template <int NW, int U, bool NORM>
 static void launch_f32(hipStream_t s, const float *A, const float *W, int N, int K, Rows rows, int epi, float *out, int ldo, const float *norm_w = nullptr,
                        float eps = 0.f) {
-  if (K >= 512) launch_f32<8, NORM>(s, A, W, N, K, rows, epi, out, ldo, norm_w, eps);
-  else launch_f32<4, NORM>(s, A, W, N, K, rows, epi, out, ldo, norm_w, eps);
+  const dim3 grid(((epi == EPI_SILU_MUL ? N / 2 : N) + 15) / 16, (rows.cap + 15) / 16);
+  if (epi == EPI_SILU_MUL) k_gemm_f32<NW, U, EPI_SILU_MUL, NORM><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo, norm_w, eps);
+  else if (epi == EPI_ADD_F32) k_gemm_f32<NW, U, EPI_ADD_F32, NORM><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo, norm_w, eps);
+  else k_gemm_f32<NW, U, EPI_STORE_F32, NORM><<<grid, NW * 64, 0, s>>>(A, W, N, K, rows, out, ldo, norm_w, eps);
 }
 // 16-byte loads need K a multiple of 4 and aligned operands.  A workgroup reads its operands without sharing them, so from about 1024
 // tiles of 64 x 64 on k_gemm_valu is the faster one (rows x N x K, us, valu / this: 64 x 1024 x 1024 136 / 6, 1024 x 1024 x 1024
@@ -863,11 +852,21 @@ bool gemm_fuses_silu_mul(int dtype, const void *A, const void *W, int N, int K, 
   return dtype == FOCUS_BF16 && K % 64 == 0 && N % 2 == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)W & 15) == 0;
 }
 
-bool gemm_fuses_rmsnorm(int dtype, const float *x, const void *norm_w, const void *W, int N, int K, int rows_cap) {
-  return dtype == FOCUS_F32 && takes_f32(x, W, N, K, rows_cap) && ((uintptr_t)norm_w & 15) == 0;
+// The norm belongs into the projection where a workgroup holds all of K at once and there are few workgroups to do it again: with 512 columns
+// up to about 1024 (a step of 128 rows, 4 layers, 321 us fused and 329 apart; 256 rows 508 and 510, 512 rows 886 and 863), with 1024 columns,
+// whose pieces fill the registers, 256 (16 rows 294 and 305, 32 rows 402 and 383); with 256 columns always (8 rows 140 and 158, 512 rows 359
+// and 378, 2048 rows 1065 and 1069).  K in several trips, each row read twice, never paid (2048 columns, 64 rows: 1483 and 940).
+bool gemm_fuses_rmsnorm(int dtype, const float *x, const void *norm_w, const void *W, int N, int K, int rows_cap, int epilogue) {
+  if (dtype != FOCUS_F32 || !takes_f32(x, W, N, K, rows_cap) || ((uintptr_t)norm_w & 15)) return false;
+  const long tiles = (long)((rows_cap + 15) / 16) * (((epilogue == EPI_SILU_MUL ? N / 2 : N) + 15) / 16);
+  return K <= 256 || (K <= 512 && tiles <= 1024) || (K <= 1024 && tiles <= 256);
 }
 void gemm_of_rmsnorm(hipStream_t s, const float *x, const void *norm_w, float eps, const void *W, int N, int K, Rows rows, int epilogue, void *out, int ldo) {
-  if (rows.cap > 0) launch_f32<true>(s, x, (const float *)W, N, K, rows, epilogue, (float *)out, ldo, (const float *)norm_w, eps);
+  if (rows.cap <= 0) return;
+  const float *w = (const float *)W, *nw = (const float *)norm_w;
+  if (K <= 256) launch_f32<4, 4, true>(s, x, w, N, K, rows, epilogue, (float *)out, ldo, nw, eps);
+  else if (K <= 512) launch_f32<8, 4, true>(s, x, w, N, K, rows, epilogue, (float *)out, ldo, nw, eps);
+  else launch_f32<8, 8, true>(s, x, w, N, K, rows, epilogue, (float *)out, ldo, nw, eps);
 }
 
 void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, Rows rows, int epilogue,
@@ -875,7 +874,8 @@ void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, 
   if (rows.cap <= 0) return;
   if (dtype == FOCUS_F32) {
     if (!takes_f32(A, W, N, K, rows.cap)) launch_valu<float>(s, A, W, N, K, rows, epilogue, out, ldo);
-    else launch_f32<false>(s, (const float *)A, (const float *)W, N, K, rows, epilogue, (float *)out, ldo);
+    else if (K >= 512) launch_f32<8, 4, false>(s, (const float *)A, (const float *)W, N, K, rows, epilogue, (float *)out, ldo);
+    else launch_f32<4, 4, false>(s, (const float *)A, (const float *)W, N, K, rows, epilogue, (float *)out, ldo);
     return;
   }
   const bool aligned = K % 64 == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)W & 15) == 0;

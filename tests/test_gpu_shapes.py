@@ -69,6 +69,15 @@ def test_fp32_projections_and_attention(shape):
     compare_steps(fi.workload("c1_tiny", **dict(shape, **budget)), 2, 1e-3, exact=True)
 
 
+@pytest.mark.parametrize("hidden,batch,block,vocab", [(256, 2, 9, 1030), (264, 1, 16, 1030), (512, 2, 16, 8000), (512, 3, 16, 8200), (520, 1, 16, 4090), (1024, 1, 16, 4096),
+                                                      (1024, 1, 17, 4096), (1032, 1, 7, 300)])
+def test_fp32_rmsnorm_inside_the_projections_and_apart(hidden, batch, block, vocab):
+    """Both sides of gemm_fuses_rmsnorm: all of K held by four wavefronts (256 columns), eight (512) and eight with twice the pieces (1024), with
+    remainders of each, and launches of one tile more than a fused one may have."""
+    wl = fi.workload("c1_tiny", hidden=hidden, ffn=136, vocab=vocab, batch=batch, block_size=block, keep_ratio=1.0, prefill="synthetic")
+    compare_steps(wl, 1, 1e-3, exact=True)
+
+
 @pytest.mark.parametrize("shape", [dict(page_size=16, block_size=5), dict(page_size=16, block_size=32), dict(head_dim=64, block_size=32), dict(head_dim=64, page_size=16, block_size=5),
                                    dict(page_size=16, n_q_heads=16, n_kv_heads=4, batch=8, keep_ratio=1.0, prefill="synthetic"),                    # 4096 (row, head) pairs
                                    dict(head_dim=64, page_size=32, n_q_heads=32, n_kv_heads=8, batch=8, keep_ratio=1.0, prefill="synthetic")])       # 8192
