@@ -24,8 +24,10 @@ struct Rows {
 };
 
 // Launches of few rows are bound by their chains of loads: what a kernel reads whatever the row count (its buffers hold `cap` rows) is asked
-// for before the count is looked at (gather of 8 rows 5.5 -> 3.9 us, merge of attention splits 4.9 -> 4.6).  Loads above this line stay
-// above it, and nothing waits for them here.
+// for before the count is looked at (gather of 8 rows 5.5 -> 3.9 us).  A word or two at any size, but whole rows only in launches of at most
+// kFewRows: a larger bound may be a whole block per sequence of which a tenth is there, and the rest would be read for nothing.
+// Loads above this line stay above it, and nothing waits for them here.
+constexpr int kFewRows = 128;
 __device__ __forceinline__ void loads_asked_for() { asm volatile("" ::: "memory"); }
 
 // Device arrays indexed by sequence slot.

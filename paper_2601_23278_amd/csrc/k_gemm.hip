@@ -683,48 +683,57 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__
 #endif
 }
 
-// Adds the fp32 partial sums of a K-split projection in split order and applies the epilogue.
-template <int EPI>
+// Adds the fp32 partial sums of a K-split projection in split order and applies the epilogue.  Bound by the partial sums.  The row count may
+// lie far below the bound that the parts are laid out for, so it is read first, and workgroups are launched for the expected rows (722 of 8192
+// rows, 4096 columns: 102 us when every row of the bound was read before the count, 11.5 now).  FEW (at most kFewRows rows): one trip, its
+// loads before the count; a step of one request gains half a percent.
+template <int EPI, bool FEW>
 __global__ __launch_bounds__(256) void k_splitk_reduce(const float *__restrict__ part, int splits, size_t split_stride, Rows rows, int N,
                                                        void *out, int ldo) {
   constexpr int U = 4;
   const int ncol = EPI == EPI_SILU_MUL ? N / 2 : N, per_row = ncol / 4;
-  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-  const int m = (int)(idx / per_row), c = (int)(idx % per_row) * 4, mc = min(m, rows.cap - 1);
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a, v[U], u[U];
-  const float *p = part + (size_t)mc * N + c;
-  auto load = [&](int s0) {
+  size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+  float4 v[U], u[U];
+  float old[4];
+  auto load = [&](int m, int c, int s0) {
 #pragma unroll
     for (int i = 0; i < U; ++i) {
-      const float *q = p + (size_t)min(s0 + i, splits - 1) * split_stride;
+      const float *q = part + (size_t)m * N + c + (size_t)min(s0 + i, splits - 1) * split_stride;
       v[i] = *(const float4 *)q;
       if (EPI == EPI_SILU_MUL) u[i] = *(const float4 *)(q + N / 2);
     }
+    if (EPI == EPI_ADD_F32 && s0 == 0)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) old[i] = ((const float *)out)[(size_t)m * ldo + c + i];
   };
-  load(0);
-  float old[4];
-  if (EPI == EPI_ADD_F32)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) old[i] = ((const float *)out)[(size_t)mc * ldo + c + i];
-  loads_asked_for();
-  const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
-  if (m >= M) return;
-  for (int s0 = 0; s0 < splits; s0 += U) {
-    if (s0 > 0) load(s0);
-#pragma unroll
-    for (int i = 0; i < U; ++i)
-      if (s0 + i < splits) {
-        a.x += v[i].x; a.y += v[i].y; a.z += v[i].z; a.w += v[i].w;
-        if (EPI == EPI_SILU_MUL) { b.x += u[i].x; b.y += u[i].y; b.z += u[i].z; b.w += u[i].w; }
-      }
+  if (FEW) {
+    load(min((int)(idx / per_row), rows.cap - 1), (int)(idx % per_row) * 4, 0);
+    loads_asked_for();
   }
-  const float r[4] = {a.x, a.y, a.z, a.w}, up[4] = {b.x, b.y, b.z, b.w};
+  const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
+  for (;; idx += (size_t)gridDim.x * 256) {             // (more rows than were expected: further trips)
+    const int m = (int)(idx / per_row), c = (int)(idx % per_row) * 4;
+    if (m >= M) return;
+    if (!FEW) load(m, c, 0);
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+    for (int s0 = 0; s0 < splits; s0 += U) {
+      if (s0 > 0) load(m, c, s0);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const size_t o = (size_t)m * ldo + c + i;
-    if (EPI == EPI_SILU_MUL) ((bf16_t *)out)[o] = (bf16_t)(r[i] / (1.0f + __expf(-r[i])) * up[i]);
-    else if (EPI == EPI_ADD_F32) ((float *)out)[o] = old[i] + r[i];
-    else store_out<bf16_t, EPI>(out, o, r[i]);
+      for (int i = 0; i < U; ++i)
+        if (s0 + i < splits) {
+          a.x += v[i].x; a.y += v[i].y; a.z += v[i].z; a.w += v[i].w;
+          if (EPI == EPI_SILU_MUL) { b.x += u[i].x; b.y += u[i].y; b.z += u[i].z; b.w += u[i].w; }
+        }
+    }
+    const float r[4] = {a.x, a.y, a.z, a.w}, up[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const size_t o = (size_t)m * ldo + c + i;
+      if (EPI == EPI_SILU_MUL) ((bf16_t *)out)[o] = (bf16_t)(r[i] / (1.0f + __expf(-r[i])) * up[i]);
+      else if (EPI == EPI_ADD_F32) ((float *)out)[o] = old[i] + r[i];
+      else store_out<bf16_t, EPI>(out, o, r[i]);
+    }
+    if (FEW) return;
   }
 }
 
@@ -821,14 +830,18 @@ static PipeShape pipe_shape(int N, int K, Rows rows, int epi, size_t scratch_byt
 // K-split launch for problems with too few tiles to occupy the chip (few rows: the projection is bound by streaming W,
 // and a CU cannot pull more than a fraction of a percent of the HBM bandwidth on its own): `splits` workgroups per tile
 // write fp32 partial sums to the scratch buffer, k_splitk_reduce adds them in a fixed order.
-static void launch_reduce(hipStream_t s, int N, Rows rows, int epi, void *out, int ldo, int splits, const float *scratch) {
+template <bool FEW> static void launch_reduce(hipStream_t s, int N, Rows rows, int epi, void *out, int ldo, int splits, const float *scratch) {
   const size_t stride = (size_t)rows.cap * N;
-  const size_t quads = (size_t)rows.cap * ((epi == EPI_SILU_MUL ? N / 2 : N) / 4);
+  const size_t quads = (size_t)(FEW ? rows.cap : rows.expected()) * ((epi == EPI_SILU_MUL ? N / 2 : N) / 4);
   const unsigned grid = (unsigned)((quads + 255) / 256);
-  if (epi == EPI_SILU_MUL) k_splitk_reduce<EPI_SILU_MUL><<<grid, 256, 0, s>>>(scratch, splits, stride, rows, N, out, ldo);
-  else if (epi == EPI_STORE) k_splitk_reduce<EPI_STORE><<<grid, 256, 0, s>>>(scratch, splits, stride, rows, N, out, ldo);
-  else if (epi == EPI_ADD_F32) k_splitk_reduce<EPI_ADD_F32><<<grid, 256, 0, s>>>(scratch, splits, stride, rows, N, out, ldo);
-  else k_splitk_reduce<EPI_STORE_F32><<<grid, 256, 0, s>>>(scratch, splits, stride, rows, N, out, ldo);
+  if (epi == EPI_SILU_MUL) k_splitk_reduce<EPI_SILU_MUL, FEW><<<grid, 256, 0, s>>>(scratch, splits, stride, rows, N, out, ldo);
+  else if (epi == EPI_STORE) k_splitk_reduce<EPI_STORE, FEW><<<grid, 256, 0, s>>>(scratch, splits, stride, rows, N, out, ldo);
+  else if (epi == EPI_ADD_F32) k_splitk_reduce<EPI_ADD_F32, FEW><<<grid, 256, 0, s>>>(scratch, splits, stride, rows, N, out, ldo);
+  else k_splitk_reduce<EPI_STORE_F32, FEW><<<grid, 256, 0, s>>>(scratch, splits, stride, rows, N, out, ldo);
+}
+static void launch_reduce(hipStream_t s, int N, Rows rows, int epi, void *out, int ldo, int splits, const float *scratch) {
+  if (rows.cap <= kFewRows) launch_reduce<true>(s, N, rows, epi, out, ldo, splits, scratch);
+  else launch_reduce<false>(s, N, rows, epi, out, ldo, splits, scratch);
 }
 
 static bool takes_pipe(int N, int K, int rows_cap) {   // byte offsets of rows, and inside an fp32 output tile, within 32 bits; an even number of slabs

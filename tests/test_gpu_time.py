@@ -1,11 +1,11 @@
 """Times that a dispatch rule or a row bound must not cost: each test sets a path against the same work on another path of the same library,
 in one process, so that no figure depends on the card; the bounds lie between what the two sides measured with and without the fault."""
-import numpy as np
 import pytest
 import torch
 
 import focus_inputs as fi
-from test_gpu_parity import DEV, Outs, _pk
+from paper_2601_23278_amd.binding import KC_GEMM
+from test_gpu_parity import DEV, _pk, small_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -37,6 +37,44 @@ def step_us(sess, repeats=12, tries=5, **step):
         torch.cuda.synchronize()
         best = min(best, begin.elapsed_time(end) * 1e3 / repeats)
     return best
+
+
+def class_us(sess, kernel_class, tries=6, **step):
+    """Microseconds of the launches of a class in a first denoising step, the best of a few tries."""
+    f, best = sess.focus, 1e30
+    f.focus_set_timing(True)
+    for _ in range(tries):
+        f.focus_prefill_kv(sess.prefix_lens, sess.page_tables, None)
+        f.focus_step(len(sess.seq_ids), **step)
+        best = min(best, f.focus_get_kernel_time(kernel_class)[0] * 1e3)
+    f.focus_set_timing(False)
+    return best
+
+
+def packed_layer_us(kernel_class, rows, **model):
+    """The class's time in one layer of `rows` packed rows whose count only the device knows: of 8192 rows that there can be, and of 256."""
+    us = {}
+    for batch in (128, 4):
+        per_seq = -(-rows // batch)
+        k = torch.tensor([max(0, min(per_seq, rows - b * per_seq)) for b in range(batch)], dtype=torch.int32, device=DEV)
+        assert int(k.sum()) == rows
+        at = {}
+        for layers in (2, 8):
+            wl = small_bf16(batch=batch, block_size=64, n_layers=layers, budget_mode=3, prefix_lo=3, prefix_hi=70, steps=1, **model)
+            sess = open_context(wl)
+            sess.focus.focus_set_row_hint(rows, per_seq)
+            at[layers] = class_us(sess, kernel_class, k_override=k)
+            sess.focus.focus_free()
+        us[batch * 64] = (at[8] - at[2]) / 6
+    print(rows, us, flush=True)
+    return us
+
+
+def test_adding_k_parts_costs_by_the_rows_there_are():
+    """200 rows, K of QKV, gate/up and down in four parts.  Read for every row there can be, the parts made that 386 us a layer
+    instead of 93."""
+    us = packed_layer_us(KC_GEMM, 200, hidden=4096, n_q_heads=2, n_kv_heads=1, ffn=4096, vocab=36000, mask_token_id=35999)
+    assert us[8192] <= 2 * us[256], us
 
 
 @pytest.mark.parametrize("hidden,batch,block", [(256, 8, 32), (512, 16, 32), (1024, 1, 16), (1024, 8, 32), (2048, 2, 32)])
