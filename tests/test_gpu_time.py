@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import focus_inputs as fi
-from paper_2601_23278_amd.binding import KC_GEMM
+from paper_2601_23278_amd.binding import KC_GEMM, KC_KV_WRITE
 from test_gpu_parity import DEV, _pk, small_bf16
 
 pytestmark = pytest.mark.gpu
@@ -75,6 +75,13 @@ def test_adding_k_parts_costs_by_the_rows_there_are():
     instead of 93."""
     us = packed_layer_us(KC_GEMM, 200, hidden=4096, n_q_heads=2, n_kv_heads=1, ffn=4096, vocab=36000, mask_token_id=35999)
     assert us[8192] <= 2 * us[256], us
+
+
+def test_rotation_and_kv_write_cost_by_the_rows_there_are():
+    """200 rows of 40 heads.  V of many short sequences is written by more workgroups, so that with 8192 rows that there can be a layer takes 9.7
+    us, with 256 13.7; reading queries and keys of every row there can be made the former 15.7."""
+    us = packed_layer_us(KC_KV_WRITE, 200, hidden=512, n_q_heads=32, n_kv_heads=8, ffn=512, vocab=512, mask_token_id=511)
+    assert us[8192] <= 0.92 * us[256], us
 
 
 @pytest.mark.parametrize("hidden,batch,block", [(256, 8, 32), (512, 16, 32), (1024, 1, 16), (1024, 8, 32), (2048, 2, 32)])
