@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import focus_inputs as fi
-from paper_2601_23278_amd.binding import KC_GEMM, KC_KV_WRITE
+from paper_2601_23278_amd.binding import KC_ATTENTION, KC_GEMM, KC_KV_WRITE
 from test_gpu_parity import DEV, _pk, small_bf16
 
 pytestmark = pytest.mark.gpu
@@ -82,6 +82,13 @@ def test_rotation_and_kv_write_cost_by_the_rows_there_are():
     us, with 256 13.7; reading queries and keys of every row there can be made the former 15.7."""
     us = packed_layer_us(KC_KV_WRITE, 200, hidden=512, n_q_heads=32, n_kv_heads=8, ffn=512, vocab=512, mask_token_id=511)
     assert us[8192] <= 0.92 * us[256], us
+
+
+def test_attention_off_the_matrix_cores_costs_by_the_rows_there_are():
+    """200 rows of 32 heads on the fallback path: 133 us a layer where there can be 8192 rows, 121 where 256; 264 when the query of every row
+    there can be was read."""
+    us = packed_layer_us(KC_ATTENTION, 200, hidden=512, n_q_heads=32, n_kv_heads=32, head_dim=64, ffn=512, vocab=512, mask_token_id=511)
+    assert us[8192] <= 1.5 * us[256], us
 
 
 @pytest.mark.parametrize("hidden,batch,block", [(256, 8, 32), (512, 16, 32), (1024, 1, 16), (1024, 8, 32), (2048, 2, 32)])
