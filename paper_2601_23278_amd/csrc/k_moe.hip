@@ -192,7 +192,7 @@ enum { GG_DOWN = 0, GG_GATE_UP = 1, GG_DENSE_PARTIAL = 2, GG_DENSE_PARTIAL_SILU 
 
 #define FK_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }   // s_waitcnt vmcnt(n) only
-constexpr int kNonTemporal = 2;      // cache policy of the weight loads (NT bit): every weight is read once, past the caches
+constexpr int kNonTemporal = 2;      // cache policy of a load (NT bit): what is read once goes past the caches
 constexpr int kGroupLds = (2 * kMoeTileRows + 3 * 128) * 128;
 
 template <int MODE>
@@ -248,11 +248,20 @@ __global__ __launch_bounds__(256, 2) void k_group_gemm(GroupGemm g) {
     for (int q = 0; q < IA; ++q)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, FK_LDS_PTR(lds + stage * ASTAGE + (wave * IA + q) * 1024), 16, voa[q], so, 0, 0);
   };
+  // An expert of up to one tile of rows has its weights read once, past the caches; each further tile reads them again (8192 rows, 256 picks
+  // an expert: 700 us a layer past the caches, 535 through them; 64 picks: 270 and 280).
+  const bool once = DENSE || g.count[e] <= BM;
   auto issue_w = [&](int kt, int stage) {
     const unsigned so = kt < nk ? (unsigned)kt * 128u : 0x80000000u;
+    if (once) {
 #pragma unroll
-    for (int q = 0; q < IB; ++q)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, FK_LDS_PTR(lds + WBASE + stage * WSTAGE + (wave * IB + q) * 1024), 16, vob[q], so, 0, kNonTemporal);
+      for (int q = 0; q < IB; ++q)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, FK_LDS_PTR(lds + WBASE + stage * WSTAGE + (wave * IB + q) * 1024), 16, vob[q], so, 0, kNonTemporal);
+    } else {
+#pragma unroll
+      for (int q = 0; q < IB; ++q)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, FK_LDS_PTR(lds + WBASE + stage * WSTAGE + (wave * IB + q) * 1024), 16, vob[q], so, 0, 0);
+    }
   };
   f32x16 acc[2][2];
 #pragma unroll

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import focus_inputs as fi
-from paper_2601_23278_amd.binding import KC_ATTENTION, KC_GEMM, KC_KV_WRITE
+from paper_2601_23278_amd.binding import KC_ATTENTION, KC_EXPERTS, KC_GEMM, KC_KV_WRITE
 from test_gpu_parity import DEV, _pk, small_bf16
 
 pytestmark = pytest.mark.gpu
@@ -89,6 +89,25 @@ def test_attention_off_the_matrix_cores_costs_by_the_rows_there_are():
     there can be was read."""
     us = packed_layer_us(KC_ATTENTION, 200, hidden=512, n_q_heads=32, n_kv_heads=32, head_dim=64, ffn=512, vocab=512, mask_token_id=511)
     assert us[8192] <= 1.5 * us[256], us
+
+
+def test_experts_of_several_row_tiles_do_not_read_their_weights_anew():
+    """256 experts with 128 rows each, one tile, and with 256 on average: 1.69 times the time of the expert projections,
+    2.12 when each of the two or three tiles read the weights past the caches."""
+    us = {}
+    for batch in (128, 256):
+        wl = small_bf16(batch=batch, keep_ratio=1.0, n_layers=3, hidden=2048, n_q_heads=2, n_kv_heads=1, ffn=256, vocab=512, mask_token_id=511, prefix_lo=3, prefix_hi=30,
+                        steps=1, n_experts=256, experts_per_token=8, expert_ffn=512, first_moe_layer=1)
+        sess = open_context(wl)
+        rows = batch * 32
+        routes = torch.arange(rows * 8, dtype=torch.int32, device=DEV) % 256
+        if batch == 256:
+            routes = torch.rand(rows, 256, device=DEV, generator=torch.Generator(DEV).manual_seed(5)).topk(8, dim=1).indices.to(torch.int32)
+        sess.focus.focus_set_route_override(routes.reshape(1, rows, 8).expand(3, -1, -1).contiguous())
+        us[rows // 32] = class_us(sess, KC_EXPERTS)
+        sess.focus.focus_free()
+    print(us, flush=True)
+    assert us[256] <= 1.9 * us[128], us
 
 
 @pytest.mark.parametrize("hidden,batch,block", [(256, 8, 32), (512, 16, 32), (1024, 1, 16), (1024, 8, 32), (2048, 2, 32)])
