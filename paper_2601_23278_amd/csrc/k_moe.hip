@@ -187,6 +187,7 @@ struct GroupGemm {
   Rows rows;
   int tiles_m, splits;
   size_t split_stride;
+  bool past_caches;            // ... whose weights are read past the caches
 };
 enum { GG_DOWN = 0, GG_GATE_UP = 1, GG_DENSE_PARTIAL = 2, GG_DENSE_PARTIAL_SILU = 3 };
 
@@ -250,7 +251,7 @@ __global__ __launch_bounds__(256, 2) void k_group_gemm(GroupGemm g) {
   };
   // An expert of up to one tile of rows has its weights read once, past the caches; each further tile reads them again (8192 rows, 256 picks
   // an expert: 700 us a layer past the caches, 535 through them; 64 picks: 270 and 280).
-  const bool once = DENSE || g.count[e] <= BM;
+  const bool once = DENSE ? g.past_caches : g.count[e] <= BM;
   auto issue_w = [&](int kt, int stage) {
     const unsigned so = kt < nk ? (unsigned)kt * 128u : 0x80000000u;
     if (once) {
@@ -380,6 +381,10 @@ bool gemm_stream_partial(hipStream_t s, const void *A, const void *W, int N, int
   g.tiles_n = silu ? (N / 2 + 63) / 64 : (N + 127) / 128;
   g.out = part; g.ldo = N; g.rows = rows; g.tiles_m = (rows.cap + kMoeTileRows - 1) / kMoeTileRows; g.splits = splits;
   g.split_stride = (size_t)rows.cap * N;
+  // Layers of matrices under 16 MB find their weights in the memory-side cache from one step to the next, or in part (us a step, past the
+  // caches / through them: 8 layers of 512 columns, 128 rows 643 / 632, of 1024 columns 96 rows 712 / 693, 128 rows 731 / 716).  From there on
+  // it is the other way round for up to 32 rows and even beyond (limit of 64 MB instead: 2048 columns, 8 rows 676 / 713, 32 rows 788 / 812).
+  g.past_caches = (size_t)N * K * 2 >= (size_t)16 << 20;
   return silu ? launch_group<GG_DENSE_PARTIAL_SILU>(s, g, g.tiles_m) : launch_group<GG_DENSE_PARTIAL>(s, g, g.tiles_m);
 }
 
