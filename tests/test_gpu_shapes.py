@@ -13,17 +13,26 @@ pytestmark = pytest.mark.gpu
                                                 (8928, 1, 32), (2144, 3, 24)])
 def test_attention_context_splits_and_their_merge(prefix, batch, block):
     """Few sequences: the context is cut into 1, 1, 2, 16 and 17 ranges of two K/V tiles (both merge kernels at their border), 12 and 48 of
-    three, 70 of two, and the launch has workgroups that only warm the next weights.  The last case mixes lengths, so sequences with one
-    range and with many share a launch.  The bf16 bound of the parity tests."""
+    three, 70 of two.  The last case mixes lengths, so sequences with one range and with many share a launch.  The bf16 bound of the parity tests."""
     lengths = dict(prefix_lo=prefix, prefix_hi=prefix, prefix_dist="fixed") if batch == 1 else dict(prefix_lo=5, prefix_hi=prefix)
     compare_steps(small_bf16(batch=batch, n_q_heads=4, n_kv_heads=1, n_layers=3, block_size=block, steps=1, **lengths), 1, 2e-2, exact=False)
 
-@pytest.mark.parametrize("kv_heads,lo,hi,rows", [(65, 500, 1500, 3), (65, 900, 900, 3), (120, 300, 1300, 3), (130, 130, 3000, 2), (65, 500, 1500, 30)])
-def test_attention_rounds_of_uneven_sequences(kv_heads, lo, hi, rows):
-    """520, 960 and 1040 (sequence, kv head) pairs, uneven and even, one and two wavefronts each: two, three and four workgroups per
-    compute unit."""
-    wl = small_bf16(batch=8, n_q_heads=kv_heads, n_kv_heads=kv_heads, hidden=256, ffn=256, vocab=512, mask_token_id=511, n_layers=2, block_size=32,
-                    keep_ratio=rows / 32, prefix_lo=lo, prefix_hi=hi, steps=1)
+
+@pytest.mark.parametrize("kv_heads,group,rows,lo,hi,dist,resident", [(65, 1, 3, 200, 2500, "uniform", 2), (65, 2, 20, 200, 2500, "uniform", 2), (65, 1, 3, 900, 900, "uniform", 4),
+                                                                     (65, 2, 20, 900, 900, "uniform", 4), (120, 1, 3, 300, 1300, "uniform", 4), (130, 1, 3, 500, 1500, "uniform", 3),
+                                                                     (130, 2, 20, 500, 1500, "uniform", 3), (130, 1, 2, 100, 3000, "loguniform", 2)])
+def test_attention_rounds_of_uneven_sequences(kv_heads, group, rows, lo, hi, dist, resident):
+    """520, 960 and 1040 (sequence, kv head) pairs, uneven and even, of one wavefront (up to 32 rows x query heads of the group) and of two: two,
+    three and four workgroups per compute unit."""
+    wl = small_bf16(batch=8, n_q_heads=kv_heads * group, n_kv_heads=kv_heads, hidden=256, ffn=256, vocab=512, mask_token_id=511, n_layers=2, block_size=32,
+                    keep_ratio=rows / 32, prefix_lo=lo, prefix_hi=hi, prefix_dist=dist, steps=1)
+    totals, groups = [x + 32 for x in wl.prefix_lens()], 8 * kv_heads       # the rule of attention_resident(), so that the lengths cannot drift off it
+    mean, ratio = sum(totals) // 8, max(totals) * 8 / sum(totals)
+    if groups <= 1024:
+        assert resident == (2 if mean >= 768 and ratio > 1.5 else 4) and (resident == 2 or ratio < 1.4)
+    else:
+        assert resident == (2 if ratio > 2.55 else 3) and (resident == 2 or ratio < 2.4)
+    assert 512 < groups <= 1536 and max(totals) < 4096 and (rows * group <= 32) == (group == 1)
     compare_steps(wl, 1, 2e-2, exact=False)
 
 
