@@ -241,8 +241,11 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(AttnArgs a) {
   // slot (row, position p) fetches the chunk that belongs there.  K block = 4 token rows x 16 chunks,
   // chunk c of token t sits at position c ^ (t & 15); V^T block = 8 d rows x 8 chunks, chunk c of row d at
   // position c ^ ((d >> 1) & 7).  Both make the 16 rows that one LDS read cycle serves hit 16 distinct
-  // 16-byte bank groups.  A tile is read by this workgroup only and with the rest does not fit any cache, so it is read past them
-  // (256 sequences of up to 4096 tokens, 8 rows: 456 -> 411 us, 6.1 TB/s; 128 of up to 2048 146 -> 127; 32 rows 507 -> 491).
+  // 16-byte bank groups.  In a step a tile is read by this workgroup only and with the rest does not fit any cache, so it is read past them
+  // (256 sequences of up to 4096 tokens, 8 rows: 456 -> 411 us, 6.1 TB/s; 128 of up to 2048 146 -> 127; 32 rows 507 -> 491).  Eight
+  // wavefronts are not bound by the stream and take the same time either way (64 contexts of up to 32768 tokens, 64 rows, six layers 6.86 ms
+  // and 6.87).  The blocks of a prompt share their tiles; that is no loss either (4 prompts of 4096 tokens, three layers 16.79 and 16.81 ms,
+  // one of 32768, two layers, 43.9 and 43.8).
   const size_t page_bytes = (size_t)2 * Hkv * P * D * 2;
   const unsigned char *pool = (const unsigned char *)a.kv.base;
   const size_t k_head = (size_t)hk * P * D * 2, v_head = ((size_t)Hkv * P * D + (size_t)hk * D * P) * 2;
@@ -632,6 +635,9 @@ template <typename T> static void launch_rows(hipStream_t s, const AttnArgs &a, 
 // no compute unit is left with one long sequence alone (us at four / two: 1024 groups, 512..4096 tokens 232 / 204, 256..2048 126 / 113;
 // 640 groups 173 / 153; log-uniform to 16000, 2048 groups 894 / 783).  Even or short ones are not (1024 groups of 1536 tokens 125 / 135,
 // 768 121 and 97; 100..300 tokens 34 / 39), and 1025 to 1536 groups make two rounds of three (1536 tokens each 207 -> 196, 256..2048 the same).
+// Where the lines of uneven lie (longest / mean; four layers, us at four / two): 1024 groups of 1540 tokens on average, 1.14 610 / 618, 1.26 639 /
+// 620, 1.42 653 / 618, 1.67 632 / 605; 768 groups of 830, 1.29 318 / 329, 1.40 329 / 327, 1.59 330 / 316.  At three / two, 1120 groups: 1.61 857 /
+// 885, 2.43 812 / 739, 3.25 992 / 908; at four / two, 1600 groups: 1.65 1148 / 1202, 2.36 1124 / 1096, 2.85 1398 / 1258.
 static int attention_resident(int groups, const AttnArgs &a) {
   if (a.launch_splits > 1 || a.mean_total <= 0) return 4;
   if (groups > 512 && groups <= 1024) return a.mean_total >= 768 && a.longest_total >= 1.45 * a.mean_total ? 2 : 4;

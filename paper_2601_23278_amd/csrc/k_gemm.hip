@@ -431,7 +431,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__
   const int m0 = (first_m + in_group % gsz) * BM, n0 = (in_group / gsz) * (SILU_W ? BN / 2 : BN);
   if (m0 >= M) return;
   out = (void *)((float *)out + (size_t)split * split_stride);   // (split is 0 unless the output is fp32 partial sums)
-  const int nk = K / BK / splits;                                 // slabs of this workgroup; even (checked by the host)
+  const int nk = K / BK / splits;                                 // slabs of this workgroup
   const unsigned k_base = (unsigned)split * (unsigned)nk * (BK * 2);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave / WCOLS) * WM, wn = (wave % WCOLS) * WN;
@@ -817,7 +817,8 @@ static PipeShape pipe_shape(int N, int K, Rows rows, int epi, size_t scratch_byt
   for (int bm : heights) {
     const long tiles = (long)((est + bm - 1) / bm) * (silu ? (N / 2 + 127) / 128 : (N + 255) / 256);
     for (int splits = 1; splits <= 16; splits *= 2) {
-      // an even number of slabs per part, at least four; sums in 16-byte pieces
+      // at least four slabs per part; an even number of them, which the kernel does not need but every shape that was measured had; sums in
+      // 16-byte pieces
       if (splits > 1 && (nk % (splits * 2) || nk / splits < 4 || N % 8 || (size_t)splits * rows.cap * N * 4 > scratch_bytes)) break;
       consider(PipeShape{bm, 256, splits}, tiles, 0.30 + 0.0046 * bm + (bm == 64 ? 0.075 : 0));
     }
@@ -844,7 +845,9 @@ static void launch_reduce(hipStream_t s, int N, Rows rows, int epi, void *out, i
   else launch_reduce<false>(s, N, rows, epi, out, ldo, splits, scratch);
 }
 
-static bool takes_pipe(int N, int K, int rows_cap) {   // byte offsets of rows, and inside an fp32 output tile, within 32 bits; an even number of slabs
+// Byte offsets of rows, and inside an fp32 output tile, within 32 bits.  An even number of slabs: the kernel takes any, but no shape with an odd
+// number was measured, and those stay with k_gemm_mfma.
+static bool takes_pipe(int N, int K, int rows_cap) {
   return (double)std::max(rows_cap + 256, N + 256) * K * 2 < 4.0e9 && K % 128 == 0 && N <= 1 << 21;
 }
 
@@ -899,7 +902,8 @@ void gemm(hipStream_t s, int dtype, const void *A, const void *W, int N, int K, 
   const bool pipe = takes_pipe(N, K, rows.cap);
   // Up to 32 rows, weights of 96 MB and more in at least 32 column tiles: 64-row tiles of the pipelined kernel with parts of 16 slabs keep
   // more loads in flight (8 rows x 24576 x 4096 41.4 us by the expert-projection kernel, 36.8 in this; x 12288 27.0 and 21.3, x 32768 58 and
-  // 47; 32 rows x 24576 42.3 and 39.2; from 64 rows on either may be the faster one, and so with fewer weights)
+  // 47; 32 rows x 24576 42.3 and 39.2; from 64 rows on either may be the faster one, and so with fewer weights).  Whole pairs of parts: measured
+  // with two, four and more.
   if (pipe && scratch.ptr && N % 8 == 0 && rows.cap <= 32 && (double)N * K >= 48e6 && N >= 32 * 256 && K % 2048 == 0 &&
       (size_t)(K / 1024) * rows.cap * N * 4 <= scratch.bytes) {
     const bool silu = epilogue == EPI_SILU_MUL;

@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256, 2) void k_group_gemm(GroupGemm g) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, FK_LDS_PTR(lds + stage * ASTAGE + (wave * IA + q) * 1024), 16, voa[q], so, 0, 0);
   };
   // An expert of up to one tile of rows has its weights read once, past the caches; each further tile reads them again (8192 rows, 256 picks
-  // an expert: 700 us a layer past the caches, 535 through them; 64 picks: 270 and 280).
+  // an expert: 846 us a layer past the caches, 670 through them; 64 picks: 339 and 350).
   const bool once = DENSE ? g.past_caches : g.count[e] <= BM;
   auto issue_w = [&](int kt, int stage) {
     const unsigned so = kt < nk ? (unsigned)kt * 128u : 0x80000000u;
