@@ -187,7 +187,6 @@ struct GroupGemm {
   Rows rows;
   int tiles_m, splits;
   size_t split_stride;
-  bool past_caches;            // ... whose weights are read past the caches
 };
 enum { GG_DOWN = 0, GG_GATE_UP = 1, GG_DENSE_PARTIAL = 2, GG_DENSE_PARTIAL_SILU = 3 };
 
@@ -196,7 +195,8 @@ constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); } 
 constexpr int kNonTemporal = 2;      // cache policy of a load (NT bit): what is read once goes past the caches
 constexpr int kGroupLds = (2 * kMoeTileRows + 3 * 128) * 128;
 
-template <int MODE>
+// PAST (dense modes): the weights are read past the caches
+template <int MODE, bool PAST = true>
 __global__ __launch_bounds__(256, 2) void k_group_gemm(GroupGemm g) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer-resource builtins exist in the device pass only
   constexpr bool GATE_UP = MODE == GG_GATE_UP || MODE == GG_DENSE_PARTIAL_SILU, DENSE = MODE >= GG_DENSE_PARTIAL;
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(256, 2) void k_group_gemm(GroupGemm g) {
   };
   // An expert of up to one tile of rows has its weights read once, past the caches; each further tile reads them again (8192 rows, 256 picks
   // an expert: 846 us a layer past the caches, 670 through them; 64 picks: 339 and 350).
-  const bool once = DENSE ? g.past_caches : g.count[e] <= BM;
+  const bool once = DENSE ? PAST : g.count[e] <= BM;
   auto issue_w = [&](int kt, int stage) {
     const unsigned so = kt < nk ? (unsigned)kt * 128u : 0x80000000u;
     if (once) {
@@ -360,15 +360,15 @@ __global__ __launch_bounds__(256) void k_group_gemm_valu(const T *A, const int32
   else ((float *)out)[(size_t)row * ldo + col] = d0;
 }
 
-template <int MODE>
+template <int MODE, bool PAST = true>
 static bool launch_group(hipStream_t s, const GroupGemm &g, int n_tile_slots) {
   constexpr int kLds = kGroupLds;
   static bool ready = false;             // the dynamic LDS size has to be allowed once per kernel
   if (!ready) {
-    if (hipFuncSetAttribute((const void *)k_group_gemm<MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess) return false;
+    if (hipFuncSetAttribute((const void *)k_group_gemm<MODE, PAST>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess) return false;
     ready = true;
   }
-  k_group_gemm<MODE><<<((n_tile_slots * g.tiles_n * (MODE >= GG_DENSE_PARTIAL ? g.splits : 1) + 7) / 8) * 8, 256, kLds, s>>>(g);
+  k_group_gemm<MODE, PAST><<<((n_tile_slots * g.tiles_n * (MODE >= GG_DENSE_PARTIAL ? g.splits : 1) + 7) / 8) * 8, 256, kLds, s>>>(g);
   return true;
 }
 
@@ -384,8 +384,9 @@ bool gemm_stream_partial(hipStream_t s, const void *A, const void *W, int N, int
   // Layers of matrices under 16 MB find their weights in the memory-side cache from one step to the next, or in part (us a step, past the
   // caches / through them: 8 layers of 512 columns, 128 rows 643 / 632, of 1024 columns 96 rows 712 / 693, 128 rows 731 / 716).  From there on
   // it is the other way round for up to 32 rows and even beyond (limit of 64 MB instead: 2048 columns, 8 rows 676 / 713, 32 rows 788 / 812).
-  g.past_caches = (size_t)N * K * 2 >= (size_t)16 << 20;
-  return silu ? launch_group<GG_DENSE_PARTIAL_SILU>(s, g, g.tiles_m) : launch_group<GG_DENSE_PARTIAL>(s, g, g.tiles_m);
+  if ((size_t)N * K * 2 >= (size_t)16 << 20)
+    return silu ? launch_group<GG_DENSE_PARTIAL_SILU>(s, g, g.tiles_m) : launch_group<GG_DENSE_PARTIAL>(s, g, g.tiles_m);
+  return silu ? launch_group<GG_DENSE_PARTIAL_SILU, false>(s, g, g.tiles_m) : launch_group<GG_DENSE_PARTIAL, false>(s, g, g.tiles_m);
 }
 
 void moe_experts(hipStream_t s, const MoeArgs &a) {
