@@ -229,10 +229,10 @@ __device__ __forceinline__ void rope_kv_write_row(int r, bf16_t *qkv, int Hq, Ro
 // 128-byte line (one write transaction instead of eight).
 __device__ __forceinline__ void v_write_group(int b, int hk, const bf16_t *qkv, int Hq, const int32_t *cu, RowIndex ri, SlotState st, KvLayer kv) {
   const int D = kv.head_dim, Hkv = kv.n_kv_heads, P = kv.page_size, stride = (Hq + 2 * Hkv) * D;
-  const int r0 = cu[b], nr = cu[b + 1] - r0;
-  if (nr <= 0) return;
   const int slot = slot_of(ri.seq_slot, b, st);
-  const int L = st.prefix_len[slot];
+  const int L = st.prefix_len[slot], r0 = cu[b], nr = cu[b + 1] - r0;
+  loads_asked_for();
+  if (nr <= 0) return;
   const int32_t *pt = pages_of(st, slot);
   for (int rb = 0; rb < nr; rb += 8) {
     const int r = rb + (threadIdx.x & 7);
