@@ -684,9 +684,13 @@ __global__ __launch_bounds__(256, 1) void k_gemm_pipe(const bf16_t *__restrict__
 }
 
 // Adds the fp32 partial sums of a K-split projection in split order and applies the epilogue.  Bound by the partial sums.  The row count may
-// lie far below the bound that the parts are laid out for, so it is read first, and workgroups are launched for the expected rows (722 of 8192
-// rows, 4096 columns: 102 us when every row of the bound was read before the count, 11.5 now).  FEW (at most kFewRows rows): one trip, its
-// loads before the count; a step of one request gains half a percent.
+// lie far below the bound that the parts are laid out for, so it is read first (722 of 8192 rows, 4096 columns: 102 us when every row of the
+// bound was read before the count, 11.5 now).  There are workgroups for the expected rows, at most the kReduceGroups that run at once: each
+// waits for the count once, not in every round (1600 rows 18.9 us, 20.4 with all workgroups).  The first kReduceEarly of them ask for their loads
+// before the count, 10 MB for two parts, so that memory is busy meanwhile.  FEW (at most kFewRows rows): one trip, all loads before the count; a
+// step of one request gains half a percent.
+constexpr size_t kReduceGroups = 2048;
+constexpr unsigned kReduceEarly = 512;
 template <int EPI, bool FEW>
 __global__ __launch_bounds__(256) void k_splitk_reduce(const float *__restrict__ part, int splits, size_t split_stride, Rows rows, int N,
                                                        void *out, int ldo) {
@@ -706,15 +710,15 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float *__restrict__
 #pragma unroll
       for (int i = 0; i < 4; ++i) old[i] = ((const float *)out)[(size_t)m * ldo + c + i];
   };
-  if (FEW) {
-    load(min((int)(idx / per_row), rows.cap - 1), (int)(idx % per_row) * 4, 0);
-    loads_asked_for();
-  }
+  bool early = FEW || blockIdx.x < kReduceEarly;
+  if (early) load(min((int)(idx / per_row), rows.cap - 1), (int)(idx % per_row) * 4, 0);
+  loads_asked_for();
   const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
-  for (;; idx += (size_t)gridDim.x * 256) {             // (more rows than were expected: further trips)
+  for (;; idx += (size_t)gridDim.x * 256) {
     const int m = (int)(idx / per_row), c = (int)(idx % per_row) * 4;
     if (m >= M) return;
-    if (!FEW) load(m, c, 0);
+    if (!early) load(m, c, 0);
+    early = false;
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
     for (int s0 = 0; s0 < splits; s0 += U) {
       if (s0 > 0) load(m, c, s0);
@@ -834,7 +838,7 @@ static PipeShape pipe_shape(int N, int K, Rows rows, int epi, size_t scratch_byt
 template <bool FEW> static void launch_reduce(hipStream_t s, int N, Rows rows, int epi, void *out, int ldo, int splits, const float *scratch) {
   const size_t stride = (size_t)rows.cap * N;
   const size_t quads = (size_t)(FEW ? rows.cap : rows.expected()) * ((epi == EPI_SILU_MUL ? N / 2 : N) / 4);
-  const unsigned grid = (unsigned)((quads + 255) / 256);
+  const unsigned grid = (unsigned)(FEW ? (quads + 255) / 256 : std::min((quads + 255) / 256, kReduceGroups));
   if (epi == EPI_SILU_MUL) k_splitk_reduce<EPI_SILU_MUL, FEW><<<grid, 256, 0, s>>>(scratch, splits, stride, rows, N, out, ldo);
   else if (epi == EPI_STORE) k_splitk_reduce<EPI_STORE, FEW><<<grid, 256, 0, s>>>(scratch, splits, stride, rows, N, out, ldo);
   else if (epi == EPI_ADD_F32) k_splitk_reduce<EPI_ADD_F32, FEW><<<grid, 256, 0, s>>>(scratch, splits, stride, rows, N, out, ldo);

@@ -201,14 +201,14 @@ def test_projections_of_57_to_512_rows(batch, block):
     compare_steps(small_bf16(batch=batch, block_size=block, keep_ratio=1.0, vocab=51176, mask_token_id=51175, n_layers=2, steps=1), 1, 2e-2, exact=False)
 
 
-@pytest.mark.parametrize("vocab,hint", [(300, 200), (9000, 200), (9000, 60)])
-def test_k_parts_of_a_row_count_only_the_device_knows(vocab, hint):
+@pytest.mark.parametrize("vocab,hint,most", [(300, 200, 7), (9000, 200, 7), (9000, 60, 7), (9000, 1105, 40)])
+def test_k_parts_of_a_row_count_only_the_device_knows(vocab, hint, most):
     """About 200 of 4224 rows stay.  O and down, which add to the residual stream, in four parts of K, which lie 4224 rows apart: 138 MB, beyond
     the buffer of the K parts but within the room of 9000 logits a row; with 300 there is neither and K is not cut.  With 60 rows expected the
-    launch that adds the parts makes further trips."""
+    launch that adds the parts makes further trips, and so with 1105, more than 2048 workgroups take in one."""
     wl = small_bf16(batch=66, block_size=64, hidden=2048, n_q_heads=16, n_kv_heads=1, ffn=4096, prefix_lo=3, prefix_hi=70, vocab=vocab, mask_token_id=vocab - 1,
                     n_layers=3, budget_mode=3, steps=1)
-    compare_steps(wl, 1, 2e-2, exact=False, k_override=[b % 7 for b in range(66)], row_hint=(hint, 6))
+    compare_steps(wl, 1, 2e-2, exact=False, k_override=[b % most for b in range(66)], row_hint=(hint, most - 1))
 
 
 @pytest.mark.parametrize("batch,block,ffn", [(1, 32, 12288), (1, 5, 12352), (11, 3, 12288)])
